@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -46,6 +47,51 @@ def _check_no_scratch(remarks: str):
                 raise RuntimeError("%s spills %d bytes per lane to scratch: reduce its register use" % (name, size))
 
 
+def _registers(text: str):
+    out = set()
+    for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", text):
+        if m.group(1):
+            out.update((m.group(1), k) for k in range(int(m.group(2)), int(m.group(3)) + 1))
+        else:
+            out.add((m.group(4), int(m.group(5))))
+    return out
+
+
+def _check_mfma_distances(asm_path: str):
+    """Part of the attention kernel's matrix instructions are inline assembly, whose wait states the compiler does not
+    keep: two between a vector write of an operand and the instruction that reads it, twelve between the instruction and
+    a vector (or memory) access to its result.  The source is laid out so that they are kept; what the register
+    allocator inserts in between is not under its control.  Refuse a build in which a distance is too short."""
+    name, writes, results = None, {}, []    # VALU writes: register -> wait states since; MFMA results: (registers, since)
+    for line in open(asm_path):
+        m = re.match(r"^(_Z\S+):", line)
+        if m:
+            name, writes, results = m.group(1), {}, []
+        text = line.split(";")[0].strip()
+        if not text or text.startswith(".") or text.endswith(":"):
+            continue
+        op, _, rest = text.partition(" ") if "\t" not in text else text.partition("\t")
+        operands = [_registers(o) for o in rest.split(",")]
+        mfma = "mfma" in op
+        if mfma:
+            if any(writes.get(r, 9) < 2 for o in operands[1:] for r in o):
+                raise RuntimeError("%s: operand written too shortly before: %s" % (name, text))
+            if any((operands[1] | operands[2]) & regs for regs, since in results if since < 12):
+                raise RuntimeError("%s: result of a matrix instruction read too early: %s" % (name, text))
+        elif op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_", "flat_")):
+            touched = set().union(*operands)
+            if any(touched & regs for regs, since in results if since < 12):
+                raise RuntimeError("%s: result of a matrix instruction accessed too early: %s" % (name, text))
+        states = int(rest) + 1 if op == "s_nop" else 1
+        writes = {r: since + states for r, since in writes.items() if since + states < 3}
+        results = [(regs, since + states) for regs, since in results if since + states < 12]
+        if mfma:
+            results.append((operands[0], 0))
+        elif op.startswith("v_") and not op.startswith("v_cmp"):
+            for o in operands[:2] if "swap" in op else operands[:1]:
+                writes.update((r, 0) for r in o)
+
+
 def build_library(verbose: bool = True, extra_flags=()) -> str:
     """Compile every source and link the shared library; always recompiles."""
     hipcc = _hipcc()
@@ -56,8 +102,9 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
     def compile_one(i):
         cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, SOURCES[i]), "-o", objs[i]]
         if SOURCES[i] == "polykv_attend_mfma.hip":
-            log = _run(cmd + ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"])
+            log = _run(cmd + ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics", "-save-temps=obj"])
             _check_no_scratch(log)
+            _check_mfma_distances(os.path.join(objdir, "polykv_attend_mfma-hip-amdgcn-amd-amdhsa-gfx950.s"))
             return "\n".join(l for l in log.splitlines() if "kernel-resource-usage" not in l)
         return _run(cmd)
 

@@ -126,12 +126,7 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
     }
     p.signs = pool->signs;
 
-    const bool mat_ok = matrix_kernel_supports(p.D, p.R, p.vcodec);
-    if (prm->kernel == POLYKV_KERNEL_MATRIX && !mat_ok) {
-        set_error("pool_attend: the matrix-core kernel does not support head_dim=%d rows=%d with this value codec", p.D, p.R);
-        return POLYKV_ESHAPE;
-    }
-    p.kernel = prm->kernel == POLYKV_KERNEL_AUTO ? (mat_ok ? POLYKV_KERNEL_MATRIX : POLYKV_KERNEL_VECTOR) : prm->kernel;
+    p.kernel = prm->kernel == POLYKV_KERNEL_AUTO ? POLYKV_KERNEL_MATRIX : prm->kernel;
     // Launch limits: the vector kernel and the tail kernel put their 4-row blocks on grid.z (at most 65,535).
     if (p.kernel == POLYKV_KERNEL_VECTOR && (p.R + 3) / 4 > 65535) {
         set_error("pool_attend: the vector kernel supports at most 262,140 query rows per KV head (got %d)", p.R);
@@ -177,7 +172,7 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             *n_groups = groups;
             return want;
         };
-        int block_rows = matrix_kernel_block_rows(p.D, p.vcodec);
+        int block_rows = matrix_kernel_block_rows(p.D);
         long groups = 0;
         long want = splits_for(block_rows, &groups);
         if (block_rows == 64 && p.R > 32 && groups * want < 256) {

@@ -3,15 +3,13 @@
 // One wave owns up to 64 query rows (NT tiles of 32) of one KV head and streams 32-token tile
 // records.  Per tile, with tokens as the MFMA M dimension and query rows as N:
 //
-//   staging  a lane's share of a record (its key-code runs, its token's scales, its value-code
-//            triplets -- every wave load one contiguous run) is loaded into registers one step ahead
-//            of its use, so each load has a whole step to land.
+//   staging  a lane's share of a record (its key-code runs, a token's scales, its value codes -- every wave load
+//            one contiguous run) is loaded into registers one step ahead of its use, piece by piece.
 //   pipeline two tiles are in flight per wave: the scores of the next tile are computed on the matrix
 //            cores while the vector ALUs run the softmax and value dequantization of the current one.
-//   scores   S^T[t, r] = sum_j sum_{k in block j} (code[t,k] * s[t,j]) * q[r,k].  The dequantized key
-//            code*s has up to 18 significant bits, so it is split exactly into two fp16 terms
-//            hi = fp16(code*s), lo = code*s - hi (one packed fma), each fed to the two K=16 MFMAs of a
-//            q8_0 block with fp32 accumulation: key dequantization stays exact.
+//   scores   S^T[t, r] = sum_j s[t,j] * (sum_{k in block j} code[t,k] * q[r,k]): the keys enter the matrix cores as
+//            their integer codes, exact in fp16, and the q8_0 block scales are applied in fp32 to the products of a
+//            block (two K=16 MFMAs) as they are summed.
 //   softmax  online, per row, in base-2 units; a row's reference only moves when the row's probabilities
 //            of one tile sum to more than 2^15 in a lane, so the accumulator rescale is rare, p fits
 //            fp16, and the common case takes no maximum over the scores at all.
@@ -20,9 +18,17 @@
 //            looked up with byte permutes.  The softmax denominator is summed from the very same
 //            fp16-rounded p with packed dot products.
 //
-// Why 32x32x16: a wave that interleaves MFMAs with vector work pays about 11.5 issue cycles per MFMA
-// whatever its shape and 4 per vector instruction, so the larger tile halves the MFMA share of the
-// issue time for the same arithmetic.
+// Why 32x32x16: a wave that interleaves MFMAs with vector work pays 5 to 8 issue cycles per MFMA whatever its shape and
+// 4 to 5 per vector instruction, so the larger tile halves the MFMA share of the issue time for the same arithmetic.
+//
+// What bounds it: power.  With random operands on the matrix cores the chip holds 1.6-1.9 of its 2.4 GHz, and the time
+// follows the energy of the instruction stream (a fit over variants of this kernel: an MFMA costs about as much as eight
+// vector instructions) more than its length.  Scaling the block products instead of the keys (the exact dequantized key
+// has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
+//   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
+//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us
+// and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
+//   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
 //
 // The accumulation stays in the rotated value domain; the inverse Walsh-Hadamard rotation is done
 // once per output row (sections "Compression Scheme" / "TurboQuant", dequantization), in this kernel
@@ -53,6 +59,20 @@ __device__ __forceinline__ float16v mfma32(const half8& a, const half8& b, const
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+// The same with the result in vector registers (the compiler gives the builtin's result to accumulation registers in
+// this kernel, which vector instructions cannot read): C = 0, and C = D.  The compiler does not know what is inside, so
+// the call sites keep the distances the instruction asks for: two instructions between the vector write of an operand
+// and the product that reads it, and at least twelve between the product and a vector read of its result.
+// WAIT: with two wait states of its own in front, where the query operand may have been moved just before.
+template <bool WAIT> __device__ __forceinline__ void mfma32_v0(float16v& d, const half8& a, const half8& b) {
+    if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+}
+template <bool WAIT> __device__ __forceinline__ void mfma32_v(float16v& d, const half8& a, const half8& b) {
+    if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+}
+
 // lane <-> lane ^ 32 combinations
 __device__ __forceinline__ float xor32_max(float x) {
     const uint32_t xi = __float_as_uint(x);
@@ -65,24 +85,13 @@ __device__ __forceinline__ float xor32_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// ---- tile staging: global -> registers, one step ahead ------------------------------------------
-// A lane's share of a tile record: its 16 bytes of every key block (the A operands of the block's two
-// K=16 slices), the scales of its token, and its value-code triplets.  Every load is one contiguous,
-// fully coalesced run across the wave (the record is stored in exactly this order).
-template <int D> struct RawK {
-    uint4v k[D / 32];      // [j]: codes of token m, block j: elements 8h..8h+7 (x, y) and 16+8h.. (z, w)
-    uint32_t sc[D / 64];   // fp16 scales of token m, blocks 0..NB-1 (unused with one scale per layer tensor)
-};
-template <int D, int VC> struct RawV {
-    uint32_t w[vc_bits(VC) == 3 ? D / 64 : 1][3];  // 3-bit codecs: the lane's code triplets
-    uint4v c[vc_bits(VC) == 8 ? D / 32 : 1];       // int8 codec: the lane's 16 code bytes of every coordinate group
-    // 4-bit codecs: one dword per coordinate group; 2-bit codecs: one per pair of groups
-    uint32_t n[vc_bits(VC) == 4 ? D / 16 : vc_bits(VC) == 2 ? D / 32 : 1];
-    // codecs with value scales: the scales of the lane's 16 tokens as fp16 pairs, in the order in which
-    // the lane holds their probabilities (tokens 8b + 4h + {0,1} in g[2b], + {2,3} in g[2b+1])
-    uint32_t g[vc_has_scale(VC) ? 8 : 1];
-};
-
+// ---- tile loads: global -> registers, one step ahead --------------------------------------------
+// A lane's share of a tile record: its 16 bytes of every key block (the A operands of the block's two K=16 slices), the
+// key scales of one token, its value codes.  Every load is one contiguous run across the wave (the record is stored in
+// exactly this order).  A piece is requested again, for the tile a step later, as soon as it has been used, so that one
+// set of registers is enough and every load has a whole step to arrive.  (Records staged in LDS with direct loads,
+// three tiles ahead, cost 5 % more time on the Llama-shaped pool: the loop is bound by power, not by latency.)
+//
 // The records of a KV head are read through a buffer resource: every load is "resource + wave-uniform byte
 // offset of the tile (a scalar register) + the lane's constant offset (a vector register that never changes)
 // + an immediate", so a step spends no vector instruction on addresses, and a load beyond the KV head's records
@@ -91,84 +100,139 @@ typedef __amdgpu_buffer_rsrc_t TileRsrc;
 __device__ __forceinline__ TileRsrc make_tile_rsrc(const uint8_t* unit_base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(unit_base), 0, bytes, 0x00020000);
 }
-template <int D, int KC> __device__ __forceinline__ void load_rawk(RawK<D>& r, TileRsrc rs, uint32_t tile, int lane) {
-    const uint32_t soff = Layout<D>::kscales_off + (uint32_t)(lane & 31) * (D / 32) * 2, koff = (uint32_t)lane * 16;
-    if (KC == 0) {
-        if (D == 64) {
-            r.sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, soff, tile, 0);
-        } else {
-#pragma unroll
-            for (int x = 0; x < D / 128; ++x) {
-                const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, soff + 8 * x, tile, 0);
-                r.sc[2 * x] = two[0];
-                r.sc[2 * x + 1] = two[1];
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < D / 32; ++j) r.k[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, koff + j * 1024, tile, 0);
-}
-template <int D, int VC, int KC>
-__device__ __forceinline__ void load_rawv(RawV<D, VC>& r, TileRsrc rs, uint32_t tile, int lane) {
-    using LY = Layout<D, VC, KC>;
-    constexpr int VB = vc_bits(VC);
-    if (VB == 4 || VB == 2) {
-        constexpr int ND = VB == 4 ? D / 16 : D / 32;  // dwords per lane, contiguous
-        const uint32_t voff = LY::vcodes_off + (uint32_t)lane * (ND * 4);
-        if constexpr (ND % 4 == 0) {
-#pragma unroll
-            for (int i = 0; i < ND; i += 4) {
-                const uint4v w = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 4 * i, tile, 0);
-                r.n[i] = w.x, r.n[i + 1] = w.y, r.n[i + 2] = w.z, r.n[i + 3] = w.w;
-            }
-        } else {
-            const auto w = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, tile, 0);  // ND == 2
-            r.n[0] = w[0], r.n[1] = w[1];
-        }
-    } else if (VB == 8) {
-        const uint32_t voff = LY::vcodes_off + (uint32_t)lane * 16;
-#pragma unroll
-        for (int g = 0; g < D / 32; ++g) r.c[g] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + g * 1024, tile, 0);
-    } else {
-        const uint32_t voff = LY::vcodes_off + (uint32_t)lane * 12;
-#pragma unroll
-        for (int q = 0; q < D / 64; ++q) {
-            const auto w = __builtin_amdgcn_raw_buffer_load_b96(rs, voff + q * 768, tile, 0);
-            r.w[q][0] = w[0], r.w[q][1] = w[1], r.w[q][2] = w[2];
-        }
-    }
-    if (vc_has_scale(VC)) {
-        const uint32_t goff = LY::vscales_off + (uint32_t)(lane >> 5) * 8;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, goff + 16 * b, tile, 0);
-            r.g[2 * b] = two[0];
-            r.g[2 * b + 1] = two[1];
-        }
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {   // f(integral_constant<int, 0 .. N-1>)
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
     }
 }
 
-// Half block (j, s) of a lane's key codes -> the exact two-term fp16 split of code * scale.  With one scale
-// per layer tensor (KC = 1) the scale is folded into the softmax scale instead: hi is the code itself, an
-// exact fp16 integer, and there is no second term.
-template <int D, int KC>
-__device__ __forceinline__ void key_split(const RawK<D>& rk, int j, int s, half8& hi, half8& lo) {
-    H8 a;
-    codes4_to_half(s == 0 ? rk.k[j].x : rk.k[j].z, a.u[0], a.u[1]);
-    codes4_to_half(s == 0 ? rk.k[j].y : rk.k[j].w, a.u[2], a.u[3]);
-    a.h = a.h - (_Float16)1152.0f;
-    if (KC == 1) {
-        hi = a.h;
-        return;
+// How the scores over q8_0 block keys are formed.
+//   FOLD (exact keys): the keys enter the matrix cores as their integer codes, every 32-element block has a product
+//     of its own, and the block scale (times softmax scale * log2 e) is applied to the block's products in fp32 as
+//     they are summed.  A score tile has its tokens in the accumulator's registers, the same 16 tokens for every
+//     lane of a half wave, so a scale is handed out by DPP: position i of each 16-lane row holds the scale of the
+//     token of register i, and one v_fmac with a row broadcast of lane i does the element.
+//   otherwise (one scale per layer tensor, whose scale rides on the softmax scale; keys rounded to fp16): one product
+//     over all blocks.
+__host__ __device__ constexpr bool fold_scales(int KC, bool K16) { return KC == 0 && !K16; }
+// A tile of scores, 16 per lane: the result of a product itself, or 16 separate numbers where the products are folded
+// (as one vector value they would have to sit in 16 consecutive registers, and the register allocator then copies).
+struct Scores16 {
+    float v[16];
+    __device__ __forceinline__ float& operator[](int i) { return v[i]; }
+    __device__ __forceinline__ float operator[](int i) const { return v[i]; }
+};
+template <bool FOLD> using ScoreTile = std::conditional_t<FOLD, Scores16, float16v>;
+
+// The records of a KV head as a lane reads them; `tile` is a record's byte offset.
+template <int D, int VC, int KC, bool K16> struct TileReader {
+    using LY = Layout<D, VC, KC>;
+    static constexpr int VB = vc_bits(VC);
+    static constexpr int NS = D / 64;             // dwords of key scales per token
+    static constexpr int NQ = D / 64;             // chunks of value codes: four coordinate groups each
+    static constexpr int CW = VB == 8 ? 8 : VB;   // dwords per lane and chunk
+    TileRsrc rs;
+    // the lane's offsets: key codes, key scales, value codes, value scales (opaque, so that the compiler adds what is
+    // constant in the instruction instead of keeping a register per load)
+    uint32_t k, s, v, g;
+
+    __device__ __forceinline__ TileReader(TileRsrc r, int lane) : rs(r) {
+        k = (uint32_t)lane * 16;
+        // FOLD: the scales of the token of accumulator register lane % 16 in the lane's half wave; else of the token
+        // whose key codes the lane holds
+        const int t = fold_scales(KC, K16) ? 8 * ((lane >> 2) & 3) + 4 * (lane >> 5) + (lane & 3) : lane & 31;
+        s = (uint32_t)t * (D / 32) * 2;
+        v = (uint32_t)lane * (VB == 8 ? 16 : VB == 3 ? 12 : VB == 4 ? D / 4 : D / 8);
+        g = (uint32_t)(lane >> 5) * 8;
+        asm volatile("" : "+v"(k), "+v"(v));
+        if (KC == 0) asm volatile("" : "+v"(s));
+        if (vc_has_scale(VC)) asm volatile("" : "+v"(g));
     }
-    union {
-        uint32_t u;
-        _Float16 h[2];
-    } s2;
-    s2.u = rk.sc[j >> 1];
-    const half8 sv = (half8)(s2.h[j & 1]);
-    hi = a.h * sv;
-    lo = __builtin_elementwise_fma(a.h, sv, -hi);  // exact remainder of the product
+    // key codes of token lane % 32, block j: elements 8h..8h+7 (x, y) and 16+8h.. (z, w), h = lane / 32
+    __device__ __forceinline__ uint4v kcodes(uint32_t tile, int j) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(rs, k + j * 1024, tile, 0);
+    }
+    // key scales, blocks 2x and 2x + 1
+    __device__ __forceinline__ void kscales(uint32_t tile, uint32_t (&sc)[NS]) const {
+        if (KC != 0) return;
+        if constexpr (NS == 1) {
+            sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, LY::kscales_off + s, tile, 0);
+        } else {
+#pragma unroll
+            for (int x = 0; x < NS; x += 2) {
+                const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::kscales_off + s + 4 * x, tile, 0);
+                sc[x] = two[0], sc[x + 1] = two[1];
+            }
+        }
+    }
+    // value codes of coordinate groups 4q .. 4q + 3
+    __device__ __forceinline__ void vcodes(uint32_t tile, int q, uint32_t (&w)[CW]) const {
+        if constexpr (VB == 8) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const uint4v c = __builtin_amdgcn_raw_buffer_load_b128(rs, LY::vcodes_off + v + (2 * q + x) * 1024, tile, 0);
+                w[4 * x] = c.x, w[4 * x + 1] = c.y, w[4 * x + 2] = c.z, w[4 * x + 3] = c.w;
+            }
+        } else if constexpr (VB == 3) {
+            const auto t = __builtin_amdgcn_raw_buffer_load_b96(rs, LY::vcodes_off + v + q * 768, tile, 0);
+            w[0] = t[0], w[1] = t[1], w[2] = t[2];
+        } else if constexpr (VB == 4) {
+            const uint4v c = __builtin_amdgcn_raw_buffer_load_b128(rs, LY::vcodes_off + v + 16 * q, tile, 0);
+            w[0] = c.x, w[1] = c.y, w[2] = c.z, w[3] = c.w;
+        } else {
+            const auto c = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::vcodes_off + v + 8 * q, tile, 0);
+            w[0] = c[0], w[1] = c[1];
+        }
+    }
+    // value scales of the lane's 16 tokens as fp16 pairs, in the order in which the lane holds their probabilities
+    // (tokens 8b + 4h + {0,1} in [2b], + {2,3} in [2b+1])
+    __device__ __forceinline__ void vscales(uint32_t tile, uint32_t (&sc)[8]) const {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::vscales_off + g + 16 * b, tile, 0);
+            sc[2 * b] = two[0], sc[2 * b + 1] = two[1];
+        }
+    }
+};
+
+__device__ __forceinline__ _Float16 half_of(uint32_t w, int odd) {   // the lower or upper fp16 of a dword
+    return __builtin_bit_cast(_Float16, (uint16_t)(odd ? w >> 16 : w));
+}
+
+// Half block s of a lane's 16 key codes -> the A operand of one score product: the codes as exact fp16 integers or, for
+// keys rounded to fp16 (K16), code * scale; sc2: the dword that holds the block's scale, odd: in its upper half.
+template <bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& raw, int s, uint32_t sc2, int odd) {
+    H8 a;
+    codes4_to_half(s == 0 ? raw.x : raw.z, a.u[0], a.u[1]);
+    codes4_to_half(s == 0 ? raw.y : raw.w, a.u[2], a.u[3]);
+    a.h = a.h - (_Float16)1152.0f;
+    if (!K16) return a.h;
+    return a.h * (half8)half_of(sc2, odd);
+}
+
+// S[i] += scale of register i's token * P[i], i = 8 X .. 8 X + 7 (see fold_scales)
+#define POLYKV_FOLD8(X, R0, R1, R2, R3, R4, R5, R6, R7)                                                              \
+    asm volatile("v_fmac_f32_dpp %0, %16, %8 row_newbcast:" R0 " row_mask:0xf bank_mask:0xf\n\t"                    \
+                 "v_fmac_f32_dpp %1, %16, %9 row_newbcast:" R1 " row_mask:0xf bank_mask:0xf\n\t"                    \
+                 "v_fmac_f32_dpp %2, %16, %10 row_newbcast:" R2 " row_mask:0xf bank_mask:0xf\n\t"                   \
+                 "v_fmac_f32_dpp %3, %16, %11 row_newbcast:" R3 " row_mask:0xf bank_mask:0xf\n\t"                   \
+                 "v_fmac_f32_dpp %4, %16, %12 row_newbcast:" R4 " row_mask:0xf bank_mask:0xf\n\t"                   \
+                 "v_fmac_f32_dpp %5, %16, %13 row_newbcast:" R5 " row_mask:0xf bank_mask:0xf\n\t"                   \
+                 "v_fmac_f32_dpp %6, %16, %14 row_newbcast:" R6 " row_mask:0xf bank_mask:0xf\n\t"                   \
+                 "v_fmac_f32_dpp %7, %16, %15 row_newbcast:" R7 " row_mask:0xf bank_mask:0xf"                       \
+                 : "+v"(S[X]), "+v"(S[X + 1]), "+v"(S[X + 2]), "+v"(S[X + 3]), "+v"(S[X + 4]), "+v"(S[X + 5]),        \
+                   "+v"(S[X + 6]), "+v"(S[X + 7])                                                                    \
+                 : "v"(P[X]), "v"(P[X + 1]), "v"(P[X + 2]), "v"(P[X + 3]), "v"(P[X + 4]), "v"(P[X + 5]),              \
+                   "v"(P[X + 6]), "v"(P[X + 7]), "v"(scale))
+template <typename SV> __device__ __forceinline__ void fold16(SV& S, const float16v& P, float scale) {
+    asm volatile("s_nop 1" : : "v"(scale));   // a DPP source must not have been written by the two instructions before
+    POLYKV_FOLD8(0, "0", "1", "2", "3", "4", "5", "6", "7");
+    POLYKV_FOLD8(8, "8", "9", "10", "11", "12", "13", "14", "15");
+}
+#undef POLYKV_FOLD8
+template <typename SV> __device__ __forceinline__ void fold_block(SV& S, const float16v& P, uint32_t sc2, int odd, float qscale) {
+    fold16(S, P, (float)half_of(sc2, odd) * qscale);
 }
 
 // Constants the main loop keeps in scalar registers.  As 32-bit literals they would double the size of every
@@ -188,49 +252,44 @@ __device__ __forceinline__ LoopConsts make_loop_consts() {
     return LoopConsts{m7, m3, m4, o.h};
 }
 
-// Value group G of a lane: eight 3-bit codes -> fp16 centroids, the A operand of one P.V product.
-template <int D, int VC>
-__device__ __forceinline__ void value_group(const RawV<D, VC>& rv, int G, H8& va, const LoopConsts& lc) {
-    if (vc_bits(VC) == 4) {
-        group8_b4(rv.n[G], va.u);
-        return;
+// Half hf (codes 4 hf .. 4 hf + 3) of coordinate group gi = 0..3 of a chunk of value codes -> fp16 centroids: half of
+// the A operand of one P.V product.
+template <int VC, int CW>
+__device__ __forceinline__ void value_half(const uint32_t (&w)[CW], int gi, int hf, H8& va, const LoopConsts& lc) {
+    uint32_t &o0 = va.u[2 * hf], &o1 = va.u[2 * hf + 1];
+    if constexpr (vc_bits(VC) == 4) {
+        half4_b4(w[gi], hf, o0, o1);
+    } else if constexpr (vc_bits(VC) == 2) {
+        half4_b2(w[gi >> 1], gi & 1, hf, o0, o1);
+    } else if constexpr (vc_bits(VC) == 8) {
+        // int8 codes -> exact fp16 integers (the scale rides on P)
+        codes4_to_half(w[4 * (gi >> 1) + 2 * (gi & 1) + hf], o0, o1);
+        va.p[2 * hf] = va.p[2 * hf] - (_Float16)1152.0f;
+        va.p[2 * hf + 1] = va.p[2 * hf + 1] - (_Float16)1152.0f;
+    } else {
+        lookup4(vcode_selector(w[0], w[1], w[2], gi, hf, lc.m7, lc.m3, lc.m4), o0, o1);
     }
-    if (vc_bits(VC) == 2) {
-        group8_b2(rv.n[G >> 1], G & 1, va.u);
-        return;
-    }
-    if (vc_bits(VC) == 8) {
-        // int8 codes of coordinate group G/2, token half G%2 -> exact fp16 integers (the scale rides on P)
-        const uint4v& c = rv.c[G >> 1];
-        codes4_to_half((G & 1) == 0 ? c.x : c.z, va.u[0], va.u[1]);
-        codes4_to_half((G & 1) == 0 ? c.y : c.w, va.u[2], va.u[3]);
-        va.h = va.h - (_Float16)1152.0f;
-        return;
-    }
-    uint32_t sel_a, sel_b;
-    vcode_selectors(rv.w[G >> 2][0], rv.w[G >> 2][1], rv.w[G >> 2][2], G & 3, lc.m7, lc.m3, lc.m4, sel_a, sel_b);
-    lookup4(sel_a, va.u[0], va.u[1]);
-    lookup4(sel_b, va.u[2], va.u[3]);
 }
 
-__device__ __forceinline__ float max16(const float16v& a) {
+template <typename SV> __device__ __forceinline__ float max16(const SV& a) {
     float m = fmaxf(fmaxf(a[0], a[1]), a[2]);
 #pragma unroll
     for (int i = 3; i < 15; i += 2) m = fmaxf(fmaxf(m, a[i]), a[i + 1]);
     return fmaxf(m, a[15]);
 }
 
-// Four scores of a row -> fp16 probabilities (packed pairs) and their sum into lsum (the tile's sum).  With
-// value scales (g != nullptr: the lane's RawV::g) the P.V operand is p * scale of its token (formed in fp32,
+// Four scores of a row -> fp16 probabilities (packed pairs) and their sum into lsum (the tile's sum).  FOLD: S holds
+// the exponents themselves (base-2 units, relative to the row's reference), else raw scores.  With value scales (g != nullptr: the lane's RawV::g) the P.V operand is p * scale of its token (formed in fp32,
 // rounded to fp16 once), at most 2^8 * 2^7; the denominator sums the plain, unrounded p.
-template <bool VS>
-__device__ __forceinline__ void exp4(const float16v& S, int c, float qscale, float mneg, H8 (&pb)[2], float& lsum,
+template <bool VS, bool FOLD, typename SV>
+__device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mneg, H8 (&pb)[2], float& lsum,
                                      const uint32_t* g, half2v one2, float* gmax = nullptr) {
 #pragma unroll
     for (int pr = 0; pr < 2; ++pr) {
         const int i = 4 * c + 2 * pr;
         half2v p2;
-        const float e0 = __builtin_amdgcn_exp2f(fmaf(S[i], qscale, mneg)), e1 = __builtin_amdgcn_exp2f(fmaf(S[i + 1], qscale, mneg));
+        const float e0 = __builtin_amdgcn_exp2f(FOLD ? S[i] : fmaf(S[i], qscale, mneg));
+        const float e1 = __builtin_amdgcn_exp2f(FOLD ? S[i + 1] : fmaf(S[i + 1], qscale, mneg));
         p2[0] = (_Float16)e0;
         p2[1] = (_Float16)e1;
         // The denominator sums the very numbers that enter the P.V product where those are the probabilities
@@ -253,79 +312,18 @@ __device__ __forceinline__ void exp4(const float16v& S, int c, float qscale, flo
     }
 }
 
-// The pool's last tile when it crosses the end of the pool, read straight from memory: scores, softmax
-// and PV one after the other, tokens >= T masked out.  Runs at most once per KV head.
-template <int D, int NT, int VC, int KC, bool K16>
-__device__ __forceinline__ void process_ragged_tile(TileRsrc rs, uint32_t lt, int tile, int T, float qscale,
-                                                 int lane, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
-                                                 float (&Lsum)[NT], float* m_ref, float (&mneg)[NT],
-                                                 const LoopConsts& lc) {
-    constexpr int NB = D / 32, NG = D / 16;
-    const int h = lane >> 5;
-    RawK<D> rk;
-    RawV<D, VC> rv;
-    load_rawk<D, KC>(rk, rs, lt, lane);
-    load_rawv<D, VC, KC>(rv, rs, lt, lane);
-    float16v S[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) S[nt][i] = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            half8 hi, lo;
-            key_split<D, KC>(rk, j, s, hi, lo);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                S[nt] = mfma32(hi, qb[nt][j][s], S[nt]);
-                if (KC == 0 && !K16) S[nt] = mfma32(lo, qb[nt][j][s], S[nt]);
-            }
-        }
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        if (tile * kTile + 8 * (i >> 2) + 4 * h + (i & 3) >= T) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) S[nt][i] = -INFINITY;
-        }
-    H8 pb[NT][2];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        // this path always re-references: cheap here, and it needs no vote
-        const float m_old = m_ref[32 * nt];
-        const float m_new = fmaxf(m_old, xor32_max(max16(S[nt])));
-        const float alpha = __builtin_amdgcn_exp2f((m_old - m_new) * qscale);
-        m_ref[32 * nt] = m_new;
-        mneg[nt] = -m_new * qscale;
-        Lsum[nt] *= alpha;
-#pragma unroll
-        for (int g = 0; g < D / 32; ++g) O[g][nt] *= alpha;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) exp4<vc_has_scale(VC)>(S[nt], c, qscale, mneg[nt], pb[nt], Lsum[nt], rv.g, lc.one2);
-    }
-#pragma unroll
-    for (int G = 0; G < NG; ++G) {
-        H8 va;
-        value_group<D, VC>(rv, G, va, lc);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) O[G >> 1][nt] = mfma32(va.h, pb[nt][G & 1].h, O[G >> 1][nt]);
-    }
-}
-
 // One software-pipelined step.  While the matrix cores compute the scores of tile B (the next tile),
 // the vector ALUs turn the scores of tile A (the current tile, computed one step earlier) into
 // probabilities and dequantize A's values; then the matrix cores accumulate A's P.V.  Keeping two
 // tiles in flight is what lets MFMA and VALU work overlap within a single wave: the MFMA stream of a
 // step never depends on vector work of the same tile that has not had a full step to complete.
 //
-//   rv, rk     tile A's value codes and tile B's key codes / scales, in registers
-//   rvN, rkN   the same for the next step, requested here from nextV (the tile after A) and nextK (the
-//              tile after B); the caller alternates the two register sets, so nothing is copied
-//   Sa         scores of tile A on entry, of tile B on exit
-// Only full tiles go through here; a ragged last tile is handled by process_ragged_tile.
+//   cur        what a step is handed by the one before: the scores of tile A and its values, tile B's first key operands,
+//              its key codes and scales; on exit the same for the next step, requested from nextV (tile B), nextK (the
+//              tile after B) and, for block 0, whose operands are formed at the end of the step before, nextK0
+//   masked     (LAST only: tile B may be the pool's last) tokens of tile B from `masked` on lie past the end of the pool
 //
-// Softmax bookkeeping: the reference m_ref (raw score units) of a row only moves when the row's probabilities
+// Softmax bookkeeping: the reference m_ref (base-2 units) of a row only moves when the row's probabilities
 // of a tile, taken against the old reference, sum to more than kRaiseSum = 2^15 in one of the row's two lanes --
 // with value scales: when that sum times the largest scale among the lane's tokens of the tile does.  Every operand
 // that reaches a P.V product (a probability, or a probability times its token's scale) is therefore at most 2^15:
@@ -336,107 +334,138 @@ __device__ __forceinline__ void process_ragged_tile(TileRsrc rs, uint32_t lt, in
 // Llama-shaped workload.
 constexpr float kRaiseSum = 32768.0f;
 
-template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B>
-__device__ __forceinline__ void pipeline_step(const RawV<D, VC>& rv, const RawK<D>& rk, RawV<D, VC>& rvN, RawK<D>& rkN,
-                                              TileRsrc rs, uint32_t nextK, uint32_t nextV, float qscale, int lane,
-                                              const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
-                                              float (&Lsum)[NT], float* m_ref, float (&mneg)[NT],
-                                              float16v (&Sa)[NT], const LoopConsts& lc) {
+template <int D, int NT, int VC, int KC, bool K16> struct StepState {
+    using TR = TileReader<D, VC, KC, K16>;
+    ScoreTile<fold_scales(KC, K16)> S[NT];         // scores of tile A
+    half8 kop[2];                                  // tile B: key operands of block 0, both halves,
+    uint4v k[D / 32];                              //   key codes (block 0: of the tile after B),
+    uint32_t sc[TR::NS];                           //   key scales
+    uint32_t v[TR::NQ][TR::CW];                    // tile A: value codes
+    uint32_t g[vc_has_scale(VC) ? 8 : 1];          //   and value scales
+    __device__ __forceinline__ void first_operands() {
+        kop[0] = key_operand<K16>(k[0], 0, sc[0], 0);
+        kop[1] = key_operand<K16>(k[0], 1, sc[0], 0);
+    }
+};
+
+template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST>
+__device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
+                                              uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, float qscale,
+                                              int lane, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
+                                              float (&Lsum)[NT], float* m_ref, float (&mneg)[NT], const LoopConsts& lc) {
+    using TR = TileReader<D, VC, KC, K16>;
     constexpr int NB = D / 32, NG = D / 16, MG = D / 32;
+    constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC);
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    float16v Sb[NT];
+    auto& Sa = cur.S;
+    ScoreTile<FOLD> Sb[NT];
     float lt[NT];   // this tile's probability sums, per lane
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) lt[nt] = 0.0f;
 
-    // The step is written as a sequence of slices.  Each slice pairs a batch of MFMAs whose operands
-    // are ready with the vector work that prepares the operands of the NEXT batch, and is closed by a
-    // scheduling barrier so that the compiler keeps the pairing; inside a slice the two streams are
-    // interleaved one MFMA to a few vector instructions.
-    constexpr int NQK = 2 * NB;   // half blocks of tile B: (j, s)
+    // The step is a sequence of short stretches, each one product (MFMA) followed by the vector work that shares its
+    // time; scheduling barriers keep the compiler from moving work across.
     constexpr int NCH = 4 * NT;   // probability chunks of tile A: 4 scores each
-    auto slice_end = [](auto mfmas, auto valus) {
-        constexpr int M = decltype(mfmas)::value, V = decltype(valus)::value;
-        constexpr int per = M > 0 ? (V + M - 1) / M : 0;
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (per > 0) __builtin_amdgcn_sched_group_barrier(0x402, per, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    using std::integral_constant;
-
-    // The next step's bytes are requested into the other set of registers as soon as the first score
-    // products are on the matrix cores (right here when the step has none): every load still has nearly the
-    // whole step to land, and the stretch in which the matrix cores wait for vector work stays short.
-    auto request_next = [&]() {
-        if (HAS_B) load_rawk<D, KC>(rkN, rs, nextK, lane);
-        load_rawv<D, VC, KC>(rvN, rs, nextV, lane);
-    };
-    if (!HAS_B) {
-        request_next();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-
+    auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
     H8 pb[NT][2];      // probabilities of tile A: B operands of the P.V products, [row tile][k slice]
-    half8 khi[2], klo[2];
-    H8 va[2];
-    float gmax = vc_has_scale(VC) ? 5.9604645e-8f : 1.0f;   // (not 0: an infinite sum times it must still say "move")
+    float gmax = VS ? 5.9604645e-8f : 1.0f;   // (not 0: an infinite sum times it must still say "move")
     auto exp_chunk = [&](int c) {
-        exp4<vc_has_scale(VC)>(Sa[c >> 2], c & 3, qscale, mneg[c >> 2], pb[c >> 2], lt[c >> 2], rv.g, lc.one2,
-                               vc_has_scale(VC) && c < 4 ? &gmax : nullptr);
+        exp4<VS, FOLD>(Sa[c >> 2], c & 3, qscale, mneg[c >> 2], pb[c >> 2], lt[c >> 2], cur.g, lc.one2,
+                       VS && c < 4 ? &gmax : nullptr);
     };
-    auto kdeq = [&](int k) { key_split<D, KC>(rk, k >> 1, k & 1, khi[k & 1], klo[k & 1]); };
-    auto qk = [&](int k) {
-        const int j = k >> 1, s = k & 1;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) Sb[nt] = mfma32(khi[k & 1], qb[nt][j][s], Sb[nt]);
-        if (KC == 0 && !K16) {   // the exact remainder term; dropped when the keys may be rounded to fp16
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) Sb[nt] = mfma32(klo[k & 1], qb[nt][j][s], Sb[nt]);
-        }
+    uint32_t sc_next[TR::NS], g_next[VS ? 8 : 1];   // scales of the tiles a step later
+    auto kdeq = [&](int k, half8& dst) {   // half block k's operand; after a block's second half its codes are reloaded
+        dst = key_operand<K16>(cur.k[k >> 1], k & 1, cur.sc[k >> 2], (k >> 1) & 1);
     };
-    auto vdeq = [&](int G) { value_group<D, VC>(rv, G, va[G & 1], lc); };
-    auto pv = [&](int G) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) O[G >> 1][nt] = mfma32(va[G & 1].h, pb[nt][G & 1].h, O[G >> 1][nt]);
+    auto scales_next = [&]() {
+        tr.kscales(nextK, sc_next);
+        if constexpr (VS) tr.vscales(nextV, g_next);
     };
+
+    // block j's products with row tile nt (FOLD): two of them take turns, one is folded while the other is formed
+    float16v P[FOLD ? 2 : 1];
+    constexpr int NU = NB * NT;
+    auto fold = [&](int u) { fold_block(Sb[u % NT], P[u & (FOLD ? 1 : 0)], cur.sc[u / NT >> 1], u / NT & 1, qscale); };
 
     if (HAS_B) {
+        if constexpr (FOLD) {
+            // Unit u: block u / NT with row tile u % NT, two products.  The operand of a half block is formed as soon as
+            // its predecessor's last product has been issued.
+            static_for<NU>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                constexpr int j = u / NT, nt = u % NT;
+                const bool last_nt = nt == NT - 1 && j + 1 < NB;
+                fence();
+                if (u == 0) mfma32_v0<true>(P[u & 1], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
+                else mfma32_v0<!LOOP>(P[u & 1], cur.kop[0], qb[nt][j][0]);
+                fence();
+                if (u == 0) scales_next();
+                if (j == 0) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+                    for (int i = 0; i < 16; ++i) Sb[nt][i] = mneg[nt];
+                }
+                if (last_nt) kdeq(2 * (j + 1), cur.kop[0]);
+                if (HAS_A) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) Sb[nt][i] = 0.0f;
-        // lead-in: only the vector work that the first products need
-        constexpr int lead = 0;
-        kdeq(0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int k = 0; k < NQK; ++k) {
-            qk(k);
-            if (k == 0) request_next();
-            if (k + 1 < NQK) kdeq(k + 1);
-            if (HAS_A) {
-                // spread the remaining probability chunks over the score slices
-                const int c0 = lead + (k * (NCH - lead)) / NQK, c1 = lead + ((k + 1) * (NCH - lead)) / NQK;
-#pragma unroll
-                for (int c = c0; c < c1; ++c) exp_chunk(c);
+                    for (int c = u * NCH / NU; c < (u + 1) * NCH / NU; ++c) exp_chunk(c);
+                }
+                fence();
+                if (u == 0) mfma32_v<true>(P[u & 1], cur.kop[1], qb[nt][j][1]);
+                else mfma32_v<!LOOP>(P[u & 1], cur.kop[1], qb[nt][j][1]);
+                fence();
+                if (u > 0) {
+                    if (!HAS_A) asm volatile("s_nop 15");   // (no probabilities in between)
+                    fence();
+                    fold(u - 1);
+                }
+                if (last_nt) {
+                    kdeq(2 * (j + 1) + 1, cur.kop[1]);
+                    cur.k[j + 1 < NB ? j + 1 : 0] = tr.kcodes(nextK, j + 1);
+                }
+                fence();
+            });
+            if (!HAS_A) {   // (else with the first product of P.V)
+                asm volatile("s_nop 15");
+                fence();
+                fold(NU - 1);
             }
-            slice_end(integral_constant<int, (KC == 0 && !K16 ? 2 : 1) * NT>{}, integral_constant<int, (HAS_A ? 28 : 16)>{});
+        } else {
+            constexpr int NQK = 2 * NB;   // half blocks
+            half8 kop2[2] = {cur.kop[0], cur.kop[1]};
+            static_for<NQK>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    fence();
+                    if (k == 0) mfma32_v0<true>(Sb[nt], kop2[0], qb[nt][0][0]);
+                    else if (k == 1) mfma32_v<true>(Sb[nt], kop2[1], qb[nt][0][1]);
+                    else mfma32_v<!LOOP || NT == 1>(Sb[nt], kop2[k & 1], qb[nt][k >> 1][k & 1]);
+                    fence();
+                    if (k == 0 && nt == 0) scales_next();
+                    // the operand two half blocks on, once this one's last product has been issued
+                    if (nt == NT - 1 && k + 2 < NQK) {
+                        kdeq(k + 2, kop2[k & 1]);
+                        if (k & 1) cur.k[(k + 2 < NQK ? k + 2 : 0) >> 1] = tr.kcodes(nextK, (k + 2) >> 1);
+                    }
+                    if (HAS_A) {
+                        const int u = k * NT + nt, N = NQK * NT;
+#pragma unroll
+                        for (int c = u * NCH / N; c < (u + 1) * NCH / N; ++c) exp_chunk(c);
+                    }
+                    fence();
+                }
+            });
+            if (!HAS_A) asm volatile("s_nop 15");
         }
     } else if (HAS_A) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) exp_chunk(c);
-        __builtin_amdgcn_sched_barrier(0);
     }
-
     if (HAS_A) {
-        // Does a row have to move its reference?  Rare after a row's first tiles (always at its very first tile,
-        // where the reference is -inf and every probability comes out as +inf).  The probabilities of the rows
-        // that move are then recomputed against the new reference; those of the other rows come out as they
-        // were.  Only the rows that outgrew their reference move it: a row's result depends on that row's
-        // scores alone, whatever other agents' rows share the wave.
+        // Does a row have to move its reference?  Rare after a row's first tiles.  The probabilities of the rows that
+        // move are then recomputed against the new reference; those of the other rows come out as they were.  Only the
+        // rows that outgrew their reference move it: a row's result depends on that row's scores alone, whatever other
+        // agents' rows share the wave.
         // gmax: the largest value scale among the lane's 16 tokens of this tile (1 without value scales), collected
         // by the chunks of row tile 0; the products probability x scale stay below kRaiseSum if the tile's sum of
         // probabilities times gmax does
@@ -447,25 +476,30 @@ __device__ __forceinline__ void pipeline_step(const RawV<D, VC>& rv, const RawK<
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const bool row_raise = !(xor32_max(lt[nt] * gmax) <= kRaiseSum);   // (+inf stays +inf through the max)
-                const float row_max = xor32_max(max16(Sa[nt]));
                 const float m_old = m_ref[32 * nt];
+                // the row's maximum in base-2 units (FOLD: the exponents are relative to the reference)
+                const float row_max = FOLD ? m_old + xor32_max(max16(Sa[nt])) : xor32_max(max16(Sa[nt])) * qscale;
                 const float m_new = row_raise ? fmaxf(m_old, row_max) : m_old;
                 if (!__any(m_new != m_old)) continue;   // no row of this row tile moves: it keeps what it has
-                const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f((m_old - m_new) * qscale);
-                const bool first = __all(m_old == -INFINITY);  // nothing accumulated yet: nothing to rescale
+                const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f(m_old - m_new);
                 m_ref[32 * nt] = m_new;
-                mneg[nt] = -m_new * qscale;
-                if (!first) {
-                    // The accumulators live in accumulation registers that vector instructions cannot read; an
-                    // MFMA with zero operands (D = 0*0 + C) carries them to vector registers and back, so the
-                    // hot path never copies them.
-                    Lsum[nt] *= alpha;
+                mneg[nt] = -m_new;
+                if constexpr (FOLD) {   // the exponents of both tiles in flight move along
 #pragma unroll
-                    for (int g = 0; g < MG; ++g) {
-                        float16v y = mfma32(zero8, zero8, O[g][nt]);
-                        y *= alpha;
-                        O[g][nt] = mfma32(zero8, zero8, y);
+                    for (int i = 0; i < 16; ++i) {
+                        Sa[nt][i] -= m_new - m_old;
+                        if (HAS_B) Sb[nt][i] -= m_new - m_old;
                     }
+                }
+                // The accumulators live in accumulation registers that vector instructions cannot read; an
+                // MFMA with zero operands (D = 0*0 + C) carries them to vector registers and back, so the
+                // hot path never copies them.
+                Lsum[nt] *= alpha;
+#pragma unroll
+                for (int g = 0; g < MG; ++g) {
+                    float16v y = mfma32(zero8, zero8, O[g][nt]);
+                    y *= alpha;
+                    O[g][nt] = mfma32(zero8, zero8, y);
                 }
                 lt[nt] = 0.0f;
 #pragma unroll
@@ -474,22 +508,53 @@ __device__ __forceinline__ void pipeline_step(const RawV<D, VC>& rv, const RawK<
         }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) Lsum[nt] += lt[nt];
-        vdeq(0);
-        __builtin_amdgcn_sched_barrier(0);
-    }
 
-    if (HAS_A) {
+        // ---- P.V.  Group G's operand is formed a little ahead of its first product; NVA operands take turns.
+        constexpr int NVA = FOLD && D == 128 && !VS ? 3 : 2;
+        H8 va[NVA];
+        auto vhalf = [&](int i) {   // the i-th half operand
+            if (i >= 2 * NG) return;
+            const int G = i >> 1;
+            value_half<VC>(cur.v[G >> 2], G & 3, i & 1, va[G % NVA], lc);
+            if (HAS_B && (i & 7) == 7) tr.vcodes(nextV, G >> 2, cur.v[G >> 2]);   // the chunk has been used up
+        };
+        vhalf(0);
+        vhalf(1);
+        if (NVA == 3) vhalf(2);
+        fence();
 #pragma unroll
         for (int G = 0; G < NG; ++G) {
-            pv(G);
-            if (G + 1 < NG) vdeq(G + 1);
-            slice_end(integral_constant<int, NT>{}, integral_constant<int, 12>{});
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                O[G >> 1][nt] = mfma32(va[G % NVA].h, pb[nt][G & 1].h, O[G >> 1][nt]);
+                fence();
+                if (FOLD && HAS_B && G == 0 && nt == 0) fold(NU - 1);
+                vhalf(2 * G + NVA + nt);
+                if (NT == 1) vhalf(2 * G + NVA + 1);
+                fence();
+            }
         }
     }
 
     if (HAS_B) {
+        // what the next step starts with
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) Sa[nt] = Sb[nt];
+        for (int x = 0; x < TR::NS; ++x) cur.sc[x] = sc_next[x];
+        if constexpr (VS) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) cur.g[x] = g_next[x];
+        }
+        cur.first_operands();
+        cur.k[0] = tr.kcodes(nextK0, 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (LAST && masked < kTile) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) >= masked) Sb[nt][i] = -INFINITY;
+            }
+            Sa[nt] = Sb[nt];
+        }
     }
 }
 
@@ -507,6 +572,7 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
                                                           float* __restrict__ out, AttendPlan p, int direct) {
     using LY = Layout<D, VC, KC>;
     constexpr int NB = D / 32, MG = D / 32, ROWS = 32 * NT;
+    constexpr bool FOLD = fold_scales(KC, K16);
     constexpr int OSTRIDE = D + 4;
     constexpr int TB = LY::tile_bytes;
     __shared__ float m_s[4][ROWS];
@@ -533,17 +599,18 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     // this wave's tiles: t_begin + wave, +4, +8, ...; local index k <-> tile my_first + 4k
     const int my_first = t_begin + wave;
     const int my_count = my_first < t_end ? (t_end - my_first + 3) / 4 : 0;
-    // pointer to local tile k; k past the end is clamped (the refill loads of the last steps then
-    // fetch the wave's own last tile again, harmlessly, instead of needing a branch per load)
-    // (byte offsets from the KV head's first record; pool_create keeps a KV head's records under 4 GiB)
-    const TileRsrc rs = make_tile_rsrc(unit_base, (uint32_t)p.tiles_cap * (uint32_t)TB);
+    // Byte offset of local tile k; k past the end is clamped (the loads of the last steps then fetch the wave's own last
+    // tile again, harmlessly, instead of needing a branch per load).
+    // (From the KV head's first record; pool_create keeps a KV head's records under 4 GiB.)
     const int last_k = max(my_count - 1, 0);
-    auto tile_ptr = [&](int k) { return (uint32_t)(my_first + 4 * min(k, last_k)) * (uint32_t)TB; };
-    RawK<D> rk;
-    RawV<D, VC> rv;
+    auto tile_off = [&](int k) { return (uint32_t)(my_first + 4 * min(k, last_k)) * (uint32_t)TB; };
+    const TileReader<D, VC, KC, K16> tr(make_tile_rsrc(unit_base, (uint32_t)p.tiles_cap * (uint32_t)TB), lane);
+    StepState<D, NT, VC, KC, K16> cur;
     if (my_count > 0) {
-        load_rawk<D, KC>(rk, rs, tile_ptr(0), lane);
-        load_rawv<D, VC, KC>(rv, rs, tile_ptr(0), lane);
+        const uint32_t t0 = tile_off(0);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) cur.k[j] = tr.kcodes(t0, j);
+        tr.kscales(t0, cur.sc);
     }
 
     // ---- query rows as MFMA B operands: lane (n, h) holds q[row 32nt+n][32j + 16s + 8h .. +7].
@@ -601,10 +668,8 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     __syncthreads();  // every wave has picked up its queries: the merge at the end reuses this memory
     // The queries are only ever MFMA operands: park them in accumulation registers so that the vector
     // registers are left for the scores and the dequantization temporaries (a second loop, so that the LDS
-    // reads above are all in flight before the first one is waited for).  Not at head_dim 256: there the
-    // allocator has to spill, and builds that spilled parked operands to scratch memory computed wrong
-    // results.
-    if constexpr (D != 256) {
+    // reads above are all in flight before the first one is waited for).
+    {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -621,49 +686,57 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         m_ref[32 * nt] = -INFINITY;
-        mneg[nt] = INFINITY;   // no reference yet: the first tile's probabilities come out as +inf and set one
+        mneg[nt] = FOLD ? 0.0f : INFINITY;   // no reference yet: the first tile's maximum sets one
         Lsum[nt] = 0.0f;
     }
     const LoopConsts lc = make_loop_consts();
-    float16v S[NT];  // scores of the tile whose softmax comes next
 
-    // Local tile k is "B" in step k-1 (scores) and "A" in step k (softmax, PV).  Only the pool's very
-    // last tile can be ragged; it stays out of the pipeline and goes last.
-    const bool last_ragged = my_count > 0 && (my_first + 4 * (my_count - 1)) * kTile + kTile > p.T;
-    const int full_count = last_ragged ? my_count - 1 : my_count;
-    if (full_count > 0) {
-        // register sets: (rk, rv) and (rk2, rv2) alternate between "current" and "being loaded"
-        RawK<D> rk2;
-        RawV<D, VC> rv2;
-        // prologue: scores of tile 0 from rk; requests K of tile 1 and (again) V of tile 0 into set 2
-        pipeline_step<D, NT, VC, KC, K16, false, true>(rv, rk, rv2, rk2, rs, tile_ptr(1), tile_ptr(0), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
+    // Local tile k is "B" in step k-1 (scores) and "A" in step k (softmax, PV).
+    if (my_count > 0) {
+        int k = 0;                                            // the step's tile A
+        auto rest = [&](int b) { return p.T - (my_first + 4 * b) * kTile; };   // tokens from tile b's first one on
+        cur.first_operands();
+        cur.k[0] = tr.kcodes(tile_off(1), 0);
+        // prologue: scores of tile 0; requests the values of tile 0 and the keys of tile 1
+#pragma unroll
+        for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
+        pipeline_step<D, NT, VC, KC, K16, false, true, false, true>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), qscale,
+                                                                   lane, qb, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const float m0 = xor32_max(max16(S[nt]));
+            const float m0 = xor32_max(max16(cur.S[nt])) * (FOLD ? 1.0f : qscale);
             m_ref[32 * nt] = m0;
-            mneg[nt] = -m0 * qscale;
+            mneg[nt] = -m0;
+            if constexpr (FOLD) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) cur.S[nt][i] -= m0;
+            }
         }
-        int s = 0;
-        for (; s + 1 < full_count - 1; s += 2) {  // two steps per trip: the sets swap roles without copies
-            pipeline_step<D, NT, VC, KC, K16, true, true>(rv2, rk2, rv, rk, rs, tile_ptr(s + 2), tile_ptr(s + 1), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
-            pipeline_step<D, NT, VC, KC, K16, true, true>(rv, rk, rv2, rk2, rs, tile_ptr(s + 3), tile_ptr(s + 2), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
+        auto main_step = [&]() {
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                       kTile, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+            ++k;
+        };
+        while (k + 3 < my_count) {   // two steps a trip: the two tiles' scores swap registers without copies
+            main_step();
+            main_step();
         }
-        if (s < full_count - 1) {  // one step with a B tile left: current = set 2
-            pipeline_step<D, NT, VC, KC, K16, true, true>(rv2, rk2, rv, rk, rs, tile_ptr(s + 2), tile_ptr(s + 1), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
-            pipeline_step<D, NT, VC, KC, K16, true, false>(rv, rk, rv2, rk2, rs, tile_ptr(s + 2), tile_ptr(s + 2), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
-        } else {
-            pipeline_step<D, NT, VC, KC, K16, true, false>(rv2, rk2, rv, rk, rs, tile_ptr(s + 1), tile_ptr(s + 1), qscale, lane, qb, O, Lsum, m_ref, mneg, S, lc);
-        }
+        for (; k + 1 < my_count; ++k)   // one or two: tile B may be the pool's last
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                      rest(k + 1), qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+        pipeline_step<D, NT, VC, KC, K16, true, false, false, false>(cur, tr, 0, 0, 0, kTile, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
     }
-    if (last_ragged)
-        process_ragged_tile<D, NT, VC, KC, K16>(rs, tile_ptr(my_count - 1), my_first + 4 * (my_count - 1), p.T, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
 
     // ---- merge the four waves through LDS: every wave stores its row maxima, denominators and accumulators
     // as they are into buffers of its own; the final pass rescales them to the common row maximum and adds
     // them in a fixed order, so the result is reproducible.
+    // (the lane number is read again here: across the main loop it would hold registers)
+    int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(elane));
     {
+        const int h = elane >> 5, n = elane & 31;
         float* obuf = o_s + wave * (ROWS * OSTRIDE);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -689,14 +762,14 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     // instruction; the rotation is then log2(D/4) in-register stages and two DPP stages, whichever index bits
     // sit in the lane.
     constexpr int CPL = D / 4, RPW = ROWS / 4;
-    const int ri = lane >> 2, qd = lane & 3;
+    const int ri = elane >> 2, qd = elane & 3;
     if (ri < RPW) {
         const int rr = wave + 4 * ri, r = row0 + rr;
         const float Mr = fmaxf(fmaxf(m_s[0][rr], m_s[1][rr]), fmaxf(m_s[2][rr], m_s[3][rr]));
         float fw[4];  // a wave's weight: 2^(its maximum - the common one); 0 if it saw no tile
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-            fw[w] = m_s[w][rr] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_s[w][rr] - Mr) * qscale);
+            fw[w] = m_s[w][rr] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_s[w][rr] - Mr);
         const float l = (l_s[rr] * fw[0] + l_s[ROWS + rr] * fw[1]) + (l_s[2 * ROWS + rr] * fw[2] + l_s[3 * ROWS + rr] * fw[3]);
         // Direct output with private tails: the row's tail partial (maximum in base-2 units, denominator and
         // unnormalized sum in the original value domain; written by the tail kernel, which ran before this one
@@ -708,8 +781,8 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
             tail_row = (size_t)usel * p.R + min(r, p.R - 1);
             const float tm = ws_ml[tail_row * 2], tl = ws_ml[tail_row * 2 + 1];
             if (tl > 0.0f) {
-                const float Mp = Mr * qscale, M2 = fmaxf(Mp, tm);
-                const float wa = __builtin_amdgcn_exp2f(Mp - M2), wb = __builtin_amdgcn_exp2f(tm - M2);
+                const float M2 = fmaxf(Mr, tm);
+                const float wa = __builtin_amdgcn_exp2f(Mr - M2), wb = __builtin_amdgcn_exp2f(tm - M2);
                 const float inv = 1.0f / (wa * l + wb * tl);
                 inv_l = wa * inv;
                 tail_w = wb * inv;
@@ -719,7 +792,7 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
         // int8 values are accumulated unrotated and unscaled: 1/l is all that is left to do
         constexpr float kCS = inv_centroid_scale<vc_bits(VC)>();
         const float f = VC == 2 ? (direct ? inv_l : 1.0f)
-                        : direct ? quad_entry_sign(lane) * (kCS * (D == 64 ? 0.125f : D == 128 ? 0.08838834764831845f : 0.0625f)) *
+                        : direct ? quad_entry_sign(elane) * (kCS * (D == 64 ? 0.125f : D == 128 ? 0.08838834764831845f : 0.0625f)) *
                                        inv_l
                                  : kCS;
 #pragma unroll
@@ -737,7 +810,7 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
         }
         if (direct) {
             if (VC != 2) {
-                wht_cross_quad<CPL>(x, lane);
+                wht_cross_quad<CPL>(x, elane);
                 wht_inlane<CPL>(x);
                 // rotation variant H.D: piece i holds coordinates 16i + 4qd ..
                 if (p.signs.on) {
@@ -770,45 +843,32 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
 #pragma unroll
             for (int i = 0; i < CPL / 4; ++i) dst[4 * i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
             if (qd == 0) {
-                ws_ml[prow * 2] = Mr * qscale;
+                ws_ml[prow * 2] = Mr;
                 ws_ml[prow * 2 + 1] = l;
             }
         }
     }
 }
 
-// Every shape the pool supports except int8 values at head_dim 256, where two staged tiles of code bytes do not
-// fit the registers next to the accumulators (the vector kernel serves that corner).
-bool matrix_kernel_supports(int head_dim, int rows_per_kv_head, int value_codec) {
-    return (head_dim == 64 || head_dim == 128 || (head_dim == 256 && value_codec != POLYKV_VALUES_INT8)) &&
-           rows_per_kv_head >= 1;
-}
-
-// Query rows per workgroup: 64 where the accumulators, the parked queries, two tiles of scores and two staged
-// tiles fit the 512 registers of a wave; 32 at head_dim 256 and, at head_dim 128, for the two codecs with the
-// most staged value bytes per tile (int8, and 4-bit codes with a scale).
-int matrix_kernel_block_rows(int head_dim, int value_codec) {
-    if (head_dim == 256) return 32;
-    if (head_dim == 128 && (value_codec == POLYKV_VALUES_INT8 || value_codec == POLYKV_VALUES_TQ4_SCALED)) return 32;
-    return 64;
-}
+// Query rows per workgroup: 64 (32 at head_dim 256, where 64 rows' accumulators alone would fill the registers).
+int matrix_kernel_block_rows(int head_dim) { return head_dim == 256 ? 32 : 64; }
 
 bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 
 template <int D, int NT, int VC, int KC, bool K16>
 static hipError_t launch_one(dim3 grid, const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
                              float* ws_o, float* out, int direct, hipStream_t s) {
-    constexpr int kMergeBytes = 4 * 32 * NT * (D + 4) * (int)sizeof(float);
+    constexpr int kShared = 4 * 32 * NT * (D + 4) * (int)sizeof(float);   // the merge buffers
     auto kern = attend_mfma_kernel<D, NT, VC, KC, K16>;
     static std::once_flag configured;  // per instantiation: the limit is a property of the function
     static hipError_t config_result = hipSuccess;
-    if (kMergeBytes > 48 * 1024)
+    if (kShared > 48 * 1024)
         std::call_once(configured, [&]() {
             config_result = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, kMergeBytes);
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
         });
     if (config_result != hipSuccess) return config_result;
-    launch_main_kernel(kern, grid, dim3(256), kMergeBytes, s, storage, (const __half*)Q, ws_ml, ws_o, out, plan, direct);
+    launch_main_kernel(kern, grid, dim3(256), kShared, s, storage, (const __half*)Q, ws_ml, ws_o, out, plan, direct);
     return hipGetLastError();
 }
 
@@ -819,8 +879,7 @@ static hipError_t launch_dv(const polykv_pool* pool, const AttendPlan& plan, con
     const uint8_t* storage = reinterpret_cast<const uint8_t*>(pool->storage);
     const int units = plan.layers * plan.H;
     const int direct = matrix_kernel_direct(plan) ? 1 : 0;
-    constexpr bool two_tiles_fit = D == 64 || (D == 128 && VC != 2 && VC != 6);   // matrix_kernel_block_rows()
-    if constexpr (two_tiles_fit) {
+    if constexpr (D != 256) {
         if (plan.R > 32 && plan.block_rows == 64)
             return launch_one<D, 2, VC, KC, K16>(dim3(plan.nsplit, units, (plan.R + 63) / 64), storage, plan, Q, ws_ml, ws_o,
                                                  out, direct, s);
@@ -834,9 +893,7 @@ static hipError_t launch_dk(const polykv_pool* pool, const AttendPlan& plan, con
                             float* out, hipStream_t s) {
     switch (plan.vcodec) {
         case 1: return launch_dv<D, 1, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 2:
-            if constexpr (D == 256) return hipErrorInvalidValue;   // not built: matrix_kernel_supports() says no
-            else return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
+        case 2: return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
         case 3: return launch_dv<D, 3, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
         case 4: return launch_dv<D, 4, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
         case 5: return launch_dv<D, 5, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);

@@ -85,10 +85,8 @@ inline void launch_main_kernel(void (*kern)(Params...), dim3 grid, dim3 block, s
         kern<<<grid, block, shmem, s>>>(static_cast<Params>(args)...);
 }
 
-// True if the matrix-core attention kernel supports this shape.
-bool matrix_kernel_supports(int head_dim, int rows_per_kv_head, int value_codec);
 // Query rows one workgroup of the matrix-core kernel covers.
-int matrix_kernel_block_rows(int head_dim, int value_codec);
+int matrix_kernel_block_rows(int head_dim);
 // True if the matrix-core kernel writes the final output itself (no merge kernel needed).
 bool matrix_kernel_direct(const AttendPlan& plan);
 hipError_t launch_attend_matrix(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml,

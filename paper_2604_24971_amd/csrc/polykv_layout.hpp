@@ -252,14 +252,22 @@ __device__ __forceinline__ void lookup4_b2(uint32_t sel, uint32_t sign, uint32_t
 }
 // Eight codes of coordinate group G from the lane's dword `w` -> eight fp16 centroids (four dwords, codes e
 // in order).  4 bits: w is the group's dword; 2 bits: w is the dword of the pair G/2 and `odd` = G % 2.
+__device__ __forceinline__ void half4_b4(uint32_t w, int hf, uint32_t& out01, uint32_t& out23) {   // codes 4 hf ..
+    if (hf == 0) lookup4_b4(w & 0x07070707u, (w << 4) & 0x80808080u, out01, out23);
+    else lookup4_b4((w >> 4) & 0x07070707u, w & 0x80808080u, out01, out23);
+}
+__device__ __forceinline__ void half4_b2(uint32_t w, int odd, int hf, uint32_t& out01, uint32_t& out23) {
+    const uint32_t v = odd ? w >> 4 : w;   // slots 2*odd and 2*odd + 1 now sit at bits 0..1 and 2..3 of every byte
+    if (hf == 0) lookup4_b2(v & 0x01010101u, (v << 6) & 0x80808080u, out01, out23);
+    else lookup4_b2((v >> 2) & 0x01010101u, (v << 4) & 0x80808080u, out01, out23);
+}
 __device__ __forceinline__ void group8_b4(uint32_t w, uint32_t (&out)[4]) {
-    lookup4_b4(w & 0x07070707u, (w << 4) & 0x80808080u, out[0], out[1]);
-    lookup4_b4((w >> 4) & 0x07070707u, w & 0x80808080u, out[2], out[3]);
+    half4_b4(w, 0, out[0], out[1]);
+    half4_b4(w, 1, out[2], out[3]);
 }
 __device__ __forceinline__ void group8_b2(uint32_t w, int odd, uint32_t (&out)[4]) {
-    const uint32_t v = odd ? w >> 4 : w;   // slots 2*odd and 2*odd + 1 now sit at bits 0..1 and 2..3 of every byte
-    lookup4_b2(v & 0x01010101u, (v << 6) & 0x80808080u, out[0], out[1]);
-    lookup4_b2((v >> 2) & 0x01010101u, (v << 4) & 0x80808080u, out[2], out[3]);
+    half4_b2(w, odd, 0, out[0], out[1]);
+    half4_b2(w, odd, 1, out[2], out[3]);
 }
 // The sign-magnitude code of (token t of the tile, rotated coordinate dv) from the V-code region (dword view).
 __device__ __forceinline__ int vcode_extract_b4(const uint32_t* v, int D, int t, int dv) {
@@ -275,16 +283,18 @@ __device__ __forceinline__ int vcode_extract_b2(const uint32_t* v, int D, int t,
 // tokens, e = 0..3 in the bytes of sel_a and e = 4..7 in the bytes of sel_b.  m7, m3, m4 are the byte masks
 // 0x07070707, 0x03030303 and 0x04040404: a caller whose loop is bound by instruction fetch keeps them in
 // registers (as literals they would double the size of the instructions that use them).
-__device__ __forceinline__ void vcode_selectors(uint32_t w0, uint32_t w1, uint32_t w2, int gi, uint32_t m7, uint32_t m3,
-                                                uint32_t m4, uint32_t& sel_a, uint32_t& sel_b) {
+__device__ __forceinline__ uint32_t vcode_selector(uint32_t w0, uint32_t w1, uint32_t w2, int gi, int hf, uint32_t m7,
+                                                   uint32_t m3, uint32_t m4) {   // hf: 0 for sel_a, 1 for sel_b
     if (gi < 3) {
         const uint32_t w = gi == 0 ? w0 : gi == 1 ? w1 : w2;
-        sel_a = w & m7;
-        sel_b = (w >> 3) & m7;
-    } else {
-        sel_a = ((w0 >> 6) & m3) | ((w1 >> 4) & m4);
-        sel_b = ((w2 >> 6) & m3) | ((w1 >> 5) & m4);
+        return (hf ? w >> 3 : w) & m7;
     }
+    return hf ? ((w2 >> 6) & m3) | ((w1 >> 5) & m4) : ((w0 >> 6) & m3) | ((w1 >> 4) & m4);
+}
+__device__ __forceinline__ void vcode_selectors(uint32_t w0, uint32_t w1, uint32_t w2, int gi, uint32_t m7, uint32_t m3,
+                                                uint32_t m4, uint32_t& sel_a, uint32_t& sel_b) {
+    sel_a = vcode_selector(w0, w1, w2, gi, 0, m7, m3, m4);
+    sel_b = vcode_selector(w0, w1, w2, gi, 1, m7, m3, m4);
 }
 __device__ __forceinline__ void vcode_selectors(uint32_t w0, uint32_t w1, uint32_t w2, int gi, uint32_t& sel_a,
                                                 uint32_t& sel_b) {
