@@ -26,7 +26,7 @@
 // vector instructions) more than its length.  Scaling the block products instead of the keys (the exact dequantized key
 // has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
 //   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
-//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us
+//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below)
 // and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
 //   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
 //
@@ -582,9 +582,17 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
     const int h = lane >> 5, n = lane & 31;
-    const int usel = blockIdx.y, ls = usel / p.H, kvh = usel - ls * p.H;
-    const int row0 = blockIdx.z * ROWS;
-    const int split = blockIdx.x;
+    // Workgroup -> (token stream = split of a KV head, row block).  Consecutive workgroups go to the eight dies in turn,
+    // each with an L2 of its own: the row blocks of a stream follow each other on one die, so that they read its records
+    // from memory once.  (Row blocks in the outermost grid dimension read every record once per block from memory:
+    // 1,450 us for 16 row blocks over 7,194 tokens, 1,165 us in this order.)
+    const int streams = p.layers * p.H * p.nsplit, row_blocks = (p.R + ROWS - 1) / ROWS;
+    const int slot = (int)(blockIdx.x >> 3);
+    const int stream = slot / row_blocks * 8 + (int)(blockIdx.x & 7);
+    if (stream >= streams) return;
+    const int row0 = slot % row_blocks * ROWS;
+    const int usel = stream / p.nsplit, split = stream - usel * p.nsplit;
+    const int ls = usel / p.H, kvh = usel - ls * p.H;
     const int tps = (p.tiles + p.nsplit - 1) / p.nsplit;
     const int t_begin = split * tps, t_end = min(p.tiles, t_begin + tps);
     const uint8_t* unit_base = pool + (size_t)((p.layer_begin + ls) * p.H + kvh) * p.tiles_cap * TB;
@@ -856,7 +864,7 @@ int matrix_kernel_block_rows(int head_dim) { return head_dim == 256 ? 32 : 64; }
 bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 
 template <int D, int NT, int VC, int KC, bool K16>
-static hipError_t launch_one(dim3 grid, const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
+static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
                              float* ws_o, float* out, int direct, hipStream_t s) {
     constexpr int kShared = 4 * 32 * NT * (D + 4) * (int)sizeof(float);   // the merge buffers
     auto kern = attend_mfma_kernel<D, NT, VC, KC, K16>;
@@ -868,6 +876,8 @@ static hipError_t launch_one(dim3 grid, const uint8_t* storage, const AttendPlan
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
         });
     if (config_result != hipSuccess) return config_result;
+    const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = (plan.R + 32 * NT - 1) / (32 * NT);
+    const dim3 grid((unsigned)((streams + 7) / 8 * 8 * row_blocks));
     launch_main_kernel(kern, grid, dim3(256), kShared, s, storage, (const __half*)Q, ws_ml, ws_o, out, plan, direct);
     return hipGetLastError();
 }
@@ -877,15 +887,12 @@ template <int D, int VC, int KC, bool K16>
 static hipError_t launch_dv(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml, float* ws_o,
                             float* out, hipStream_t s) {
     const uint8_t* storage = reinterpret_cast<const uint8_t*>(pool->storage);
-    const int units = plan.layers * plan.H;
     const int direct = matrix_kernel_direct(plan) ? 1 : 0;
     if constexpr (D != 256) {
         if (plan.R > 32 && plan.block_rows == 64)
-            return launch_one<D, 2, VC, KC, K16>(dim3(plan.nsplit, units, (plan.R + 63) / 64), storage, plan, Q, ws_ml, ws_o,
-                                                 out, direct, s);
+            return launch_one<D, 2, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, s);
     }
-    return launch_one<D, 1, VC, KC, K16>(dim3(plan.nsplit, units, (plan.R + 31) / 32), storage, plan, Q, ws_ml, ws_o, out,
-                                         direct, s);
+    return launch_one<D, 1, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, s);
 }
 
 template <int D, int KC, bool K16>

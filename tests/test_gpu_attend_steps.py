@@ -41,3 +41,14 @@ def test_codecs_over_growing_keys(codec, d):
     case, Q = _case(d, 32 * 21 + 5, growing=True, **codec)
     case.attend_check(Q, splits=1)
     case.attend_check(Q[:, :3], splits=2)
+
+
+@pytest.mark.parametrize("heads,agents,splits", [(1, 33, 1), (3, 33, 1), (3, 17, 2), (9, 33, 3)])
+def test_row_blocks_and_streams_that_do_not_fill_the_dies(heads, agents, splits):
+    """Row blocks times (head, split) streams: the launch rounds the streams up to the eight dies."""
+    rng = np.random.default_rng(heads * 100 + agents)
+    T, d = 32 * 9 + 3, 64
+    cfg = W.PoolConfig(0, "blocks", 1, heads, 4 * heads, d, T, agents, 1)
+    case = Case(cfg, rng.standard_normal((1, heads, T, d)).astype(np.float16),
+                rng.standard_normal((1, heads, T, d)).astype(np.float16))
+    case.attend_check(rng.standard_normal((1, agents, 1, 4 * heads, d)).astype(np.float16), splits=splits)
