@@ -155,22 +155,33 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         if (want < 1) want = 1;
         nsplit = (int)((want + 3) / 4 * 4);
     } else {
-        // One workgroup (4 waves, one per SIMD) per split: fill the 256 CUs once, but keep at least two
-        // tiles per wave -- below that the per-workgroup prologue, epilogue and the partials written for
-        // the merge kernel cost more than the idle CUs (measured on one-layer calls of the Llama shape:
-        // 16 splits of 8 tiles 16.8 us, 32 splits of 4 tiles 19.3 us).
+        // One workgroup (4 waves) per split.  The count is the one with the least estimated time, in steps of a wave
+        // (one tile): rounds of workgroups over the 256 CUs, times the tiles of a wave plus five steps' worth of query
+        // fetch, ramp and final pass (13,000 of 90,000 cycles at 32 tiles a wave); more than one split adds the merge
+        // kernel and the partials it reads.  At least two tiles per wave, or the partials outweigh the idle CUs
+        // (one-layer calls of the Llama shape: 16 splits of 8 tiles 16.8 us, 32 of 4 tiles 19.3 us).
+        // Filling the CUs once by the count of workgroups alone, the rule before, split the 208 KV heads of a 26-layer
+        // pool in two, 416 workgroups in two rounds and a merge: 58.3 us for 2,500 tokens at head_dim 256, 44.9 us
+        // unsplit; and the 4 heads of a 600-token pool: 9.2 us a call, 7.25 us unsplit.
         // Rows per workgroup: 64 where the kernel has such a form, but 32 when 64-row blocks, split as far as
         // the two-tiles-per-wave rule allows, would leave CUs without a workgroup (one-layer calls: 8 KV heads x
         // 16 splits = 128 workgroups of 64 rows, or 256 of 32 rows that each do half the matrix work).
         auto splits_for = [&](int block_rows, long* n_groups) {
             const long groups = (long)units * ((p.R + block_rows - 1) / block_rows);
-            long want = (256 + groups - 1) / groups;
-            if (want > cap_tiles / 8) want = cap_tiles / 8;
-            if (prm->splits > 0) want = prm->splits;
-            if (want > (cap_tiles + 3) / 4) want = (cap_tiles + 3) / 4;
-            if (want < 1) want = 1;
             *n_groups = groups;
-            return want;
+            const long most = (cap_tiles + 3) / 4;
+            if (prm->splits > 0) return prm->splits < most ? (long)prm->splits : most;
+            long best = 1;
+            double least = 0;
+            for (long n = 1; n <= cap_tiles / 8 || n == 1; ++n) {
+                const long per_wave = ((cap_tiles + n - 1) / n + 3) / 4;
+                double cost = (double)((groups * n + 255) / 256) * (per_wave + 5);
+                // the merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us
+                if (n > 1) cost += 3.5 + (double)units * n * p.R * p.D * 8 / 4e12 / 1.2e-6;
+                if (n == 1 || cost < least) least = cost, best = n;
+                if (groups * n >= 1024) break;   // finer splits only add partials
+            }
+            return best;
         };
         int block_rows = matrix_kernel_block_rows(p.D);
         long groups = 0;

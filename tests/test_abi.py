@@ -149,6 +149,22 @@ def test_state_machine_and_argument_errors_without_gpu():
     lib.pool_destroy(h)
 
 
+@pytest.mark.parametrize("layers,heads,d,tokens,agents,group,splits", [
+    (26, 8, 256, 2500, 15, 2, 1),     # 208 KV heads: one round of workgroups, no merge
+    (1, 4, 64, 600, 3, 1, 1),         # four heads of few tokens: the merge would cost more than the idle CUs
+    (1, 8, 128, 4096, 15, 4, 16),     # one layer's call: two tiles a wave on every CU
+    (1, 1, 64, 40, 1, 1, 1),          # fewer tiles than a split may have
+])
+def test_automatic_split_counts(layers, heads, d, tokens, agents, group, splits):
+    rc, h = _create(layers, heads, d, tokens)
+    p = pk.AttendParams()
+    p.agents, p.q_per_agent, p.q_heads, p.layer_begin, p.layer_end = agents, 1, heads * group, 0, layers
+    rows = layers * heads * splits * agents * group
+    up = lambda n: (n + 255) // 256 * 256
+    assert lib.pool_attend_workspace(h, C.byref(p)) == up(rows * 8) + up(rows * d * 4)
+    lib.pool_destroy(h)
+
+
 def test_attend_plan_validation_and_workspace_size():
     rc, h = _create(4, 2, 128, 4000)
     p = pk.AttendParams()
