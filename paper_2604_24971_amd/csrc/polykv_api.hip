@@ -163,6 +163,9 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         // Filling the CUs once by the count of workgroups alone, the rule before, split the 208 KV heads of a 26-layer
         // pool in two, 416 workgroups in two rounds and a merge: 58.3 us for 2,500 tokens at head_dim 256, 44.9 us
         // unsplit; and the 4 heads of a 600-token pool: 9.2 us a call, 7.25 us unsplit.
+        // What the partials of a split call take stays within the built-in scratch of pool_attend_static, so that the
+        // estimate never makes that entry point refuse a call (unsplit, a call needs the least there is; finer splits
+        // than this are about 1,000 workgroups at head_dim 128 and 256, where they gain nothing).
         // Rows per workgroup: 64 where the kernel has such a form, but 32 when 64-row blocks, split as far as
         // the two-tiles-per-wave rule allows, would leave CUs without a workgroup (one-layer calls: 8 KV heads x
         // 16 splits = 128 workgroups of 64 rows, or 256 of 32 rows that each do half the matrix work).
@@ -173,11 +176,13 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             if (prm->splits > 0) return prm->splits < most ? (long)prm->splits : most;
             long best = 1;
             double least = 0;
+            const double rows = (double)units * p.R;
             for (long n = 1; n <= cap_tiles / 8 || n == 1; ++n) {
+                if (n > 1 && rows * (n + (tails ? 1 : 0)) * (p.D + 2) * sizeof(float) + 1024 > POLYKV_STATIC_WORKSPACE_BYTES) break;
                 const long per_wave = ((cap_tiles + n - 1) / n + 3) / 4;
                 double cost = (double)((groups * n + 255) / 256) * (per_wave + 5);
                 // the merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us
-                if (n > 1) cost += 3.5 + (double)units * n * p.R * p.D * 8 / 4e12 / 1.2e-6;
+                if (n > 1) cost += 3.5 + rows * n * p.D * 8 / 4e12 / 1.2e-6;
                 if (n == 1 || cost < least) least = cost, best = n;
                 if (groups * n >= 1024) break;   // finer splits only add partials
             }

@@ -216,6 +216,16 @@ def test_attend_plan_validation_and_workspace_size():
     lib.pool_destroy(h)
 
 
+@pytest.mark.parametrize("layers, kv_heads, head_dim, tokens, group, agents, q", [
+    (17, 5, 128, 72553, 4, 36, 2), (25, 32, 256, 17992, 2, 4, 4), (1, 8, 256, 24622, 8, 67, 2), (8, 3, 128, 10175, 4, 90, 4)])
+def test_the_split_count_does_not_outgrow_the_built_in_scratch(layers, kv_heads, head_dim, tokens, group, agents, q):
+    rc, h = _create(layers, kv_heads, head_dim, tokens)
+    p = pk.AttendParams()
+    p.agents, p.q_per_agent, p.q_heads, p.layer_end = agents, q, kv_heads * group, layers
+    assert 0 < lib.pool_attend_workspace(h, C.byref(p)) <= 32 << 20
+    lib.pool_destroy(h)
+
+
 def test_python_binding_rejects_wrong_tensors_before_any_launch():
     import torch
     pool = pk.Pool(1, 2, 64, 50)
