@@ -12,6 +12,7 @@
 
 #include "polykv_internal.hpp"
 #include "polykv_layout.hpp"
+#include "polykv_tail.hpp"
 
 namespace polykv {
 
@@ -238,186 +239,12 @@ __global__ __launch_bounds__(256) void attend_vector_kernel(const uint8_t* __res
 }
 
 // ------------------------------------------------------------------------------ tail kernel ---
-// Dense 16-bit attention of one agent's rows over its private, uncompressed continuation.
-// One wave per (selected layer, kv head, agent, block of kRB rows); emits (m, l, o) in the original domain.
-// The loops over a block's loads and pieces are unrolled in full: the compiler then keeps a block's key row and
-// the query pieces in registers (all 256 at head_dim 128, one wave per SIMD plus what the 19 KB of LDS allow) and
-// has every load of a block in flight at once.  Held under 128 registers for more waves per SIMD the kernel is
-// 2 % faster on 64-token tails of all layers and 4 % slower on one layer's 32-token tails (measured); the
-// unrolled form stays.  Per block of 64 tokens:
-//   scores  the 64 key rows are fetched with coalesced loads and staged in LDS; lane = token then walks its
-//           row in 16-byte pieces; the products with the raw 16-bit queries (LDS broadcast) are packed dot
-//           products with fp32 accumulation, the softmax scale is applied to the sum;
-//   P.V     lane = (token slot, 8 coordinates): one 16-byte load covers a lane's 8 coordinates of a token,
-//           D/8 lanes a whole value row, so a wave load covers 512/D tokens of consecutive rows; every lane
-//           accumulates its slot's tokens, the slots are added once at the very end.
-typedef _Float16 tail_h2 __attribute__((ext_vector_type(2)));
-typedef short tail_s2 __attribute__((ext_vector_type(2)));
-template <bool BF> __device__ __forceinline__ float tail_dot2(uint32_t a, uint32_t b, float c) {
-    if constexpr (BF) {
-        union { uint32_t u; tail_s2 v; } x, y;
-        x.u = a, y.u = b;
-        return __builtin_amdgcn_fdot2_f32_bf16(x.v, y.v, c, false);
-    } else {
-        union { uint32_t u; tail_h2 v; } x, y;
-        x.u = a, y.u = b;
-        return __builtin_amdgcn_fdot2(x.v, y.v, c, false);
-    }
-}
-
+// One wave per (selected layer, kv head, agent, block of kTailRows rows), see tail_rows().
 template <int D, bool BF>
-__global__ __launch_bounds__(64) void attend_tail_kernel(const __half* __restrict__ Q, TailPtrs tails,
-                                                            float* __restrict__ tail_ml,
-                                                            float* __restrict__ tail_o, AttendPlan p) {
-    constexpr int LPR = D / 8;       // lanes per value row
-    constexpr int TPL = 64 / LPR;    // tokens per wave load (token slots)
-    constexpr int NLD = 64 / TPL;    // wave loads per 64 tokens
-    __shared__ __align__(16) uint16_t q_s[kRB][D];     // the raw 16-bit queries
-    __shared__ __align__(16) float p_s[64][kRB];       // probabilities, [token][row]
-    __shared__ uint4 k_s[64][LPR + 1];                 // 64 key rows (one spare piece per row rotates the banks)
-    const int lane = threadIdx.x;
-    const int usel = blockIdx.y, ls = usel / p.H, kvh = usel - ls * p.H;
-    const int a = blockIdx.x;
-    const int rows_a = p.nq * p.G;  // rows of this agent within the KV head, contiguous
-    const int r0 = a * rows_a + blockIdx.z * kRB;
-    const int r_end = min((a + 1) * rows_a, r0 + kRB);
-    if (r0 >= r_end) return;
-    const int len = tails.len[a];
-    // tokens each of the wave's rows may see: all of them, or, for a causal multi-token step, one less for
-    // every query position before the agent's last (row r0 + r is query (r0 + r - a * rows_a) / G)
-    int len_r[kRB];
-#pragma unroll
-    for (int r = 0; r < kRB; ++r) {
-        const int qi = (r0 + r - a * rows_a) / p.G;
-        len_r[r] = p.tail_causal ? max(0, len - (p.nq - 1 - min(qi, p.nq - 1))) : len;
-    }
-    const size_t head_off = ((size_t)(p.layer_begin + ls) * p.H + kvh) * p.tail_capacity * D;
-    const uint16_t* Kt = reinterpret_cast<const uint16_t*>(tails.K[a]) + head_off;
-    const uint16_t* Vt = reinterpret_cast<const uint16_t*>(tails.V[a]) + head_off;
-
-    // queries: 16-byte loads, D/8 lanes to a row; rows past the agent's last are zero
-    for (int i = lane; i < kRB * LPR; i += 64) {
-        const int r = i / LPR, piece = i - r * LPR;
-        uint4 raw = make_uint4(0, 0, 0, 0);
-        if (r0 + r < r_end) raw = *reinterpret_cast<const uint4*>(Q + q_row_index(p, ls, kvh, r0 + r) * D + 8 * piece);
-        *reinterpret_cast<uint4*>(&q_s[r][8 * piece]) = raw;
-    }
-    __syncthreads();
-
-    const int slot = lane / LPR, piece = lane - slot * LPR;
-    float m_run[kRB], l_run[kRB], acc[kRB][8];
-#pragma unroll
-    for (int r = 0; r < kRB; ++r) {
-        m_run[r] = -INFINITY;
-        l_run[r] = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[r][c] = 0.0f;
-    }
-
-    for (int t0 = 0; t0 < len; t0 += 64) {
-        const int cnt = min(64, len - t0);
-        // ---- the 64 key rows come in with fully coalesced loads (lane = (token slot, piece), as for the
-        // values below) and go through LDS, where every lane then walks the row of its own token
-        // (rows past the end are copies of the last token; their scores become -inf)
-#pragma unroll
-        for (int b0 = 0; b0 < NLD; b0 += 8) {
-            uint4 kin[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                kin[u] = *reinterpret_cast<const uint4*>(Kt + (size_t)(t0 + min((b0 + u) * TPL + slot, cnt - 1)) * D + 8 * piece);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) k_s[(b0 + u) * TPL + slot][piece] = kin[u];
-        }
-        __syncthreads();
-        const uint4* krow = &k_s[lane][0];
-        float sc[kRB];
-#pragma unroll
-        for (int r = 0; r < kRB; ++r) sc[r] = 0.0f;
-#pragma unroll
-        for (int i0 = 0; i0 < LPR; i0 += 4) {   // four 16-byte pieces of the key row at a time
-            uint4 kraw[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) kraw[u] = krow[i0 + u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int r = 0; r < kRB; ++r) {
-                    const uint4 qv = *reinterpret_cast<const uint4*>(&q_s[r][8 * (i0 + u)]);
-                    sc[r] = tail_dot2<BF>(kraw[u].x, qv.x, sc[r]);
-                    sc[r] = tail_dot2<BF>(kraw[u].y, qv.y, sc[r]);
-                    sc[r] = tail_dot2<BF>(kraw[u].z, qv.z, sc[r]);
-                    sc[r] = tail_dot2<BF>(kraw[u].w, qv.w, sc[r]);
-                }
-        }
-        float alpha[kRB];
-#pragma unroll
-        for (int r = 0; r < kRB; ++r) {
-            const float sv = t0 + lane < len_r[r] ? sc[r] * p.qscale : -INFINITY;
-            const float m_new = fmaxf(m_run[r], wave_max(sv));
-            // a row that has seen no token yet keeps m = -inf: nothing to rescale, every weight 0
-            alpha[r] = m_new == -INFINITY ? 1.0f : exp2f(m_run[r] - m_new);
-            const float pr = m_new == -INFINITY ? 0.0f : exp2f(sv - m_new);
-            l_run[r] = l_run[r] * alpha[r] + wave_sum(pr);
-            m_run[r] = m_new;
-            p_s[lane][r] = pr;
-        }
-        __syncthreads();
-        // ---- P.V, lane = (token slot, 8 coordinates)
-#pragma unroll
-        for (int r = 0; r < kRB; ++r)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[r][c] *= alpha[r];
-#pragma unroll
-        for (int b0 = 0; b0 < NLD; b0 += 8) {   // eight wave loads at a time
-            uint4 vraw[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = min((b0 + u) * TPL + slot, cnt - 1);   // past the end: a re-read with weight 0
-                vraw[u] = *reinterpret_cast<const uint4*>(Vt + (size_t)(t0 + t) * D + 8 * piece);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = (b0 + u) * TPL + slot;
-                const float4 pr4 = *reinterpret_cast<const float4*>(&p_s[t][0]);
-                const float pr[4] = {pr4.x, pr4.y, pr4.z, pr4.w};
-                const uint32_t w[4] = {vraw[u].x, vraw[u].y, vraw[u].z, vraw[u].w};
-#pragma unroll
-                for (int c2 = 0; c2 < 4; ++c2) {
-                    const float2 f = pair16_to_float2(w[c2], BF);
-#pragma unroll
-                    for (int r = 0; r < kRB; ++r) {
-                        acc[r][2 * c2] = fmaf(pr[r], f.x, acc[r][2 * c2]);
-                        acc[r][2 * c2 + 1] = fmaf(pr[r], f.y, acc[r][2 * c2 + 1]);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // ---- the token slots' shares are added (lanes piece + LPR * slot), slot 0 stores
-#pragma unroll
-    for (int r = 0; r < kRB; ++r)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            float v = acc[r][c];
-#pragma unroll
-            for (int m = LPR; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
-            acc[r][c] = v;
-        }
-#pragma unroll
-    for (int r = 0; r < kRB; ++r) {
-        if (r0 + r >= r_end) break;
-        const size_t prow = (size_t)usel * p.R + r0 + r;
-        if (slot == 0) {
-            float4* dst = reinterpret_cast<float4*>(tail_o + prow * D + 8 * piece);
-            dst[0] = make_float4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
-            dst[1] = make_float4(acc[r][4], acc[r][5], acc[r][6], acc[r][7]);
-        }
-        if (lane == 0) {
-            tail_ml[prow * 2] = m_run[r];
-            tail_ml[prow * 2 + 1] = l_run[r];
-        }
-    }
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, D == 64 ? 3 : 2))) void attend_tail_kernel(
+    const __half* __restrict__ Q, TailPtrs tails, float* __restrict__ tail_ml, float* __restrict__ tail_o, AttendPlan p) {
+    __shared__ __align__(16) float p_s[tail_block_tokens(D) * kTailRows];
+    tail_rows<D, BF>(Q, tails, tail_ml, tail_o, p, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, p_s);
 }
 
 // ----------------------------------------------------------------------------- merge kernel ---
@@ -539,7 +366,7 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
     // writes the final output itself it takes them in (through its ws_ml / ws_o arguments, which it does not
     // otherwise use then) instead of leaving them to the merge kernel.
     if (plan.has_tails) {
-        dim3 grid(plan.A, units, (plan.nq * plan.G + kRB - 1) / kRB);
+        dim3 grid(plan.A, units, (plan.nq * plan.G + kTailRows - 1) / kTailRows);
         using TailKern = decltype(&attend_tail_kernel<128, false>);
         static const TailKern tail_table[3][2] = {{attend_tail_kernel<64, false>, attend_tail_kernel<64, true>},
                                                   {attend_tail_kernel<128, false>, attend_tail_kernel<128, true>},
