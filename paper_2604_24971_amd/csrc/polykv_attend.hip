@@ -364,8 +364,11 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
 
     // The private tails go first: their partials are independent of the pool's, and where the matrix-core kernel
     // writes the final output itself it takes them in (through its ws_ml / ws_o arguments, which it does not
-    // otherwise use then) instead of leaving them to the merge kernel.
-    if (plan.has_tails) {
+    // otherwise use then) instead of leaving them to the merge kernel.  Where the merge kernel runs, they can go into the
+    // pool's launch.
+    const TailPart tail_part = {tails, tail_ml, tail_o};
+    const bool with_pool = matrix_kernel_takes_tails(plan);
+    if (plan.has_tails && !with_pool) {
         dim3 grid(plan.A, units, (plan.nq * plan.G + kTailRows - 1) / kTailRows);
         using TailKern = decltype(&attend_tail_kernel<128, false>);
         static const TailKern tail_table[3][2] = {{attend_tail_kernel<64, false>, attend_tail_kernel<64, true>},
@@ -378,7 +381,8 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
     if (plan.kernel == POLYKV_KERNEL_MATRIX) {
         const bool direct = matrix_kernel_direct(plan);
         err = launch_attend_matrix(pool, plan, Q, direct && plan.has_tails ? tail_ml : ws_ml,
-                                   direct && plan.has_tails ? tail_o : ws_o, (float*)out, s);
+                                   direct && plan.has_tails ? tail_o : ws_o, (float*)out,
+                                   with_pool ? &tail_part : nullptr, s);
         if (err != hipSuccess) return err;
         if (direct) return hipSuccess;
     } else {

@@ -41,6 +41,7 @@
 
 #include "polykv_internal.hpp"
 #include "polykv_layout.hpp"
+#include "polykv_tail.hpp"
 
 namespace polykv {
 
@@ -565,11 +566,11 @@ constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && 
 
 // ws_ml / ws_o: where the kernel leaves its split's partial (direct == 0); with direct == 1 and private tails,
 // the tail kernel's partials (row maxima and denominators / unnormalized sums), read in the final pass.
+// block: the workgroup's number among those that read the pool.
 template <int D, int NT, int VC, int KC, bool K16>
-__global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(const uint8_t* __restrict__ pool,
-                                                          const __half* __restrict__ Q,
-                                                          float* __restrict__ ws_ml, float* __restrict__ ws_o,
-                                                          float* __restrict__ out, AttendPlan p, int direct) {
+__device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ pool, const __half* __restrict__ Q,
+                                                  float* __restrict__ ws_ml, float* __restrict__ ws_o,
+                                                  float* __restrict__ out, const AttendPlan& p, int direct, uint32_t block) {
     using LY = Layout<D, VC, KC>;
     constexpr int NB = D / 32, MG = D / 32, ROWS = 32 * NT;
     constexpr bool FOLD = fold_scales(KC, K16);
@@ -587,8 +588,8 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     // from memory once.  (Row blocks in the outermost grid dimension read every record once per block from memory:
     // 1,450 us for 16 row blocks over 7,194 tokens, 1,165 us in this order.)
     const int streams = p.layers * p.H * p.nsplit, row_blocks = (p.R + ROWS - 1) / ROWS;
-    const int slot = (int)(blockIdx.x >> 3);
-    const int stream = slot / row_blocks * 8 + (int)(blockIdx.x & 7);
+    const int slot = (int)(block >> 3);
+    const int stream = slot / row_blocks * 8 + (int)(block & 7);
     if (stream >= streams) return;
     const int row0 = slot % row_blocks * ROWS;
     const int usel = stream / p.nsplit, split = stream - usel * p.nsplit;
@@ -858,14 +859,62 @@ __global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_
     }
 }
 
+template <int D, int NT, int VC, int KC, bool K16>
+__global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(
+    const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
+    float* __restrict__ out, AttendPlan p, int direct) {
+    attend_mfma_block<D, NT, VC, KC, K16>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.x);
+}
+
+// Two workgroups a CU wherever the pool's part fits 256 registers (left alone, the tails' part takes 324 at head_dim 128).
+constexpr int tails_waves_per_simd(int D, int VC, int KC) {
+    return D == 128 && vc_has_scale(VC) && KC == 0 ? 1 : kernel_waves_per_simd(D, 1, VC) == 3 ? 3 : 2;
+}
+// The same for a call whose token range is split, with the private tails in the same launch: the workgroups from
+// pool_blocks on do the tails, a wave each.  Neither part needs the other before the merge kernel, and two workgroups of
+// 32 rows fit a CU, so the tails run beside the pool instead of in a launch of their own in front of it: 32 one-layer calls with 32-token
+// tails, 15 agents, 573 us with two launches, 442 us with one.
+template <int D, int VC, int KC, bool K16>
+__global__ __launch_bounds__(256, tails_waves_per_simd(D, VC, KC)) void attend_mfma_tails_kernel(
+    const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
+    AttendPlan p, TailPtrs tails, float* __restrict__ tail_ml, float* __restrict__ tail_o, uint32_t pool_blocks) {
+    if (blockIdx.x < pool_blocks) {
+        attend_mfma_block<D, 1, VC, KC, K16>(pool, Q, ws_ml, ws_o, nullptr, p, 0, blockIdx.x);
+        return;
+    }
+    extern __shared__ __align__(16) float o_s[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int units = p.layers * p.H;
+    const int job = (int)(blockIdx.x - pool_blocks) * 4 + wave;   // agents of a unit follow each other
+    const int a = job % p.A, usel = job / p.A % units, zb = job / p.A / units;
+    float* p_s = o_s + wave * tail_block_tokens(D) * kTailRows;
+    // (a job past the last has no rows)
+    if (p.io_bf16) tail_rows<D, true>(Q, tails, tail_ml, tail_o, p, a, usel, zb, threadIdx.x & 63, p_s);
+    else tail_rows<D, false>(Q, tails, tail_ml, tail_o, p, a, usel, zb, threadIdx.x & 63, p_s);
+}
+
 // Query rows per workgroup: 64 (32 at head_dim 256, where 64 rows' accumulators alone would fill the registers).
 int matrix_kernel_block_rows(int head_dim) { return head_dim == 256 ? 32 : 64; }
 
 bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 
+static int launched_row_tiles(const AttendPlan& plan) { return plan.D != 256 && plan.R > 32 && plan.block_rows == 64 ? 2 : 1; }
+
+static long tail_waves(const AttendPlan& plan) {
+    return (long)plan.A * plan.layers * plan.H * ((plan.nq * plan.G + kTailRows - 1) / kTailRows);
+}
+
+// Tails in the pool's launch: where the merge kernel runs anyway, with 32-row workgroups at head_dim 64 and 128 (of
+// which two fit a CU; the others have a CU to themselves and the tails would follow them), and no more of them than
+// all CUs hold beside one pool workgroup each.
+bool matrix_kernel_takes_tails(const AttendPlan& plan) {
+    return plan.has_tails && plan.kernel == POLYKV_KERNEL_MATRIX && !matrix_kernel_direct(plan) && plan.D != 256 &&
+           launched_row_tiles(plan) == 1 && tail_waves(plan) <= 4 * 256;
+}
+
 template <int D, int NT, int VC, int KC, bool K16>
 static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
-                             float* ws_o, float* out, int direct, hipStream_t s) {
+                             float* ws_o, float* out, int direct, const TailPart* tails, hipStream_t s) {
     constexpr int kShared = 4 * 32 * NT * (D + 4) * (int)sizeof(float);   // the merge buffers
     auto kern = attend_mfma_kernel<D, NT, VC, KC, K16>;
     static std::once_flag configured;  // per instantiation: the limit is a property of the function
@@ -874,10 +923,22 @@ static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, con
         std::call_once(configured, [&]() {
             config_result = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
+            if constexpr (NT == 1 && D != 256)
+                if (config_result == hipSuccess)
+                    config_result = hipFuncSetAttribute(reinterpret_cast<const void*>(attend_mfma_tails_kernel<D, VC, KC, K16>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
         });
     if (config_result != hipSuccess) return config_result;
     const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = (plan.R + 32 * NT - 1) / (32 * NT);
     const dim3 grid((unsigned)((streams + 7) / 8 * 8 * row_blocks));
+    if constexpr (NT == 1 && D != 256) {
+        if (tails != nullptr) {
+            const dim3 all((unsigned)(grid.x + (tail_waves(plan) + 3) / 4));
+            launch_main_kernel(attend_mfma_tails_kernel<D, VC, KC, K16>, all, dim3(256), kShared, s, storage, (const __half*)Q,
+                               ws_ml, ws_o, plan, *tails->ptrs, tails->ml, tails->o, (uint32_t)grid.x);
+            return hipGetLastError();
+        }
+    }
     launch_main_kernel(kern, grid, dim3(256), kShared, s, storage, (const __half*)Q, ws_ml, ws_o, out, plan, direct);
     return hipGetLastError();
 }
@@ -885,49 +946,49 @@ static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, con
 // Row tiles per workgroup: two (64 rows) or one (32 rows), see matrix_kernel_block_rows().
 template <int D, int VC, int KC, bool K16>
 static hipError_t launch_dv(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml, float* ws_o,
-                            float* out, hipStream_t s) {
+                            float* out, const TailPart* tails, hipStream_t s) {
     const uint8_t* storage = reinterpret_cast<const uint8_t*>(pool->storage);
     const int direct = matrix_kernel_direct(plan) ? 1 : 0;
     if constexpr (D != 256) {
-        if (plan.R > 32 && plan.block_rows == 64)
-            return launch_one<D, 2, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, s);
+        if (launched_row_tiles(plan) == 2)
+            return launch_one<D, 2, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
     }
-    return launch_one<D, 1, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, s);
+    return launch_one<D, 1, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
 }
 
 template <int D, int KC, bool K16>
 static hipError_t launch_dk(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml, float* ws_o,
-                            float* out, hipStream_t s) {
+                            float* out, const TailPart* tails, hipStream_t s) {
     switch (plan.vcodec) {
-        case 1: return launch_dv<D, 1, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 2: return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 3: return launch_dv<D, 3, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 4: return launch_dv<D, 4, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 5: return launch_dv<D, 5, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        case 6: return launch_dv<D, 6, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
-        default: return launch_dv<D, 0, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, s);
+        case 1: return launch_dv<D, 1, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 2: return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 3: return launch_dv<D, 3, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 4: return launch_dv<D, 4, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 5: return launch_dv<D, 5, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 6: return launch_dv<D, 6, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        default: return launch_dv<D, 0, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
     }
 }
 
 template <int D>
 static hipError_t launch_d(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml,
-                           float* ws_o, float* out, hipStream_t s) {
-    if (plan.kcodec == POLYKV_KEYS_Q8_TENSOR) return launch_dk<D, 1, false>(pool, plan, Q, ws_ml, ws_o, out, s);
+                           float* ws_o, float* out, const TailPart* tails, hipStream_t s) {
+    if (plan.kcodec == POLYKV_KEYS_Q8_TENSOR) return launch_dk<D, 1, false>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
     // keys rounded to fp16 once dequantized (the precision of the dense cache the paper's read path holds): only
     // for the paper's value codec at head_dim 64 / 128, the shapes this option is meant for
     if (plan.key_fp16) {
         if constexpr (D != 256) {
-            if (plan.vcodec == POLYKV_VALUES_TQ3) return launch_dv<D, 0, 0, true>(pool, plan, Q, ws_ml, ws_o, out, s);
+            if (plan.vcodec == POLYKV_VALUES_TQ3) return launch_dv<D, 0, 0, true>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
         }
     }
-    return launch_dk<D, 0, false>(pool, plan, Q, ws_ml, ws_o, out, s);
+    return launch_dk<D, 0, false>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
 }
 
 hipError_t launch_attend_matrix(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml,
-                                float* ws_o, float* out, hipStream_t s) {
-    if (plan.D == 128) return launch_d<128>(pool, plan, Q, ws_ml, ws_o, out, s);
-    if (plan.D == 256) return launch_d<256>(pool, plan, Q, ws_ml, ws_o, out, s);
-    return launch_d<64>(pool, plan, Q, ws_ml, ws_o, out, s);
+                                float* ws_o, float* out, const TailPart* tails, hipStream_t s) {
+    if (plan.D == 128) return launch_d<128>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+    if (plan.D == 256) return launch_d<256>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+    return launch_d<64>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
 }
 
 }  // namespace polykv

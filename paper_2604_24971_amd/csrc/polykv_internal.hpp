@@ -89,8 +89,15 @@ inline void launch_main_kernel(void (*kern)(Params...), dim3 grid, dim3 block, s
 int matrix_kernel_block_rows(int head_dim);
 // True if the matrix-core kernel writes the final output itself (no merge kernel needed).
 bool matrix_kernel_direct(const AttendPlan& plan);
+// The private tails of a call and where their partials go.
+struct TailPart {
+    const TailPtrs* ptrs;
+    float *ml, *o;
+};
+// True if the private tails are done in the matrix-core kernel's launch; `tails` below is then given, else nullptr.
+bool matrix_kernel_takes_tails(const AttendPlan& plan);
 hipError_t launch_attend_matrix(const polykv_pool* pool, const AttendPlan& plan, const void* Q, float* ws_ml,
-                                float* ws_o, float* out, hipStream_t s);
+                                float* ws_o, float* out, const TailPart* tails, hipStream_t s);
 
 // Query row r of KV head kvh in selected layer ls -> index (in vectors of head_dim) into Q / out.
 // Rows of a KV head are ordered (agent, query, head-in-group): r = (a * nq + i) * G + g.

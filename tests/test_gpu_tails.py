@@ -1,6 +1,6 @@
 """Private tails against the oracle at the edges of the wave's blocks: lengths around its 16-token tiles and 64- (head_dim
 256: 32-) token rounds, agents with more and with fewer rows than the four of a wave, causal steps, with the token range
-whole, split and on the vector kernel; what lies past a
+whole (tails in a launch of their own), split (tails in the pool's launch) and on the vector kernel; what lies past a
 tail's end is NaN and must not be seen."""
 import numpy as np
 import pytest
