@@ -16,15 +16,15 @@
 
 namespace polykv {
 
+// Reductions over the wave by DPP and lane swaps: a step is a vector instruction or two instead of a trip through LDS.
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m, 64));
-    return x;
+    x = fmaxf(x, lane_xor<1>(x));
+    return tail_max64(fmaxf(x, lane_xor<2>(x)));
 }
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-    return x;
+    x += lane_xor<1>(x);
+    x += lane_xor<2>(x);
+    return tail_sum64(x);
 }
 
 constexpr int kRB = 4;  // query rows per pass of the vector kernels
@@ -265,12 +265,24 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const float* __restri
     const int usel = (int)(rg / p.R), r = (int)(rg - (long)usel * p.R);
     const int ls = usel / p.H, kvh = usel - ls * p.H;
 
-    // Every split wrote its partial (zeros with m = -inf, l = 0 where it had no tokens), so nothing here
-    // is conditional: the lanes fetch the (m, l) pairs of 64 splits at a time, the weights
-    // w_s = 2^(m_s - M) are handed out with readlane, and the loads of the partial rows are independent
-    // of each other (eight in flight per lane).
+    // Every split wrote its partial (zeros with m = -inf, l = 0 where it had no tokens).  What bounds the kernel is
+    // latency, a few rows per CU: the (m, l) pairs of up to 64 splits (lane = split), the first 16 partial rows and the
+    // tail partial are all requested before anything is waited for; the weights w_s = 2^(m_s - M) are then handed out
+    // with readlane.  Rows of further splits follow, eight in flight per lane.
     const size_t row0 = (size_t)usel * p.nsplit * p.R + r;     // partial row of split 0; split stride p.R rows
-    // the tail partial is requested now and used last
+    const size_t stride = (size_t)p.R * D;
+    const float* src = ws_o + row0 * D + lane * EPL;
+    constexpr int PRE = 16;
+    const float2 ml0 = *reinterpret_cast<const float2*>(ws_ml + (row0 + (size_t)min(lane, p.nsplit - 1) * p.R) * 2);
+    float v0[PRE][EPL];
+#pragma unroll
+    for (int g = 0; g < PRE; g += 4)
+        if (g < p.nsplit) {
+#pragma unroll
+            for (int u = g; u < g + 4; ++u)   // past the last: a re-read that is not used
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) v0[u][i] = src[(size_t)min(u, p.nsplit - 1) * stride + i];
+        }
     float tail_m = -INFINITY, tail_l = 0.0f, tail_x[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) tail_x[i] = 0.0f;
@@ -281,29 +293,37 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const float* __restri
 #pragma unroll
         for (int i = 0; i < EPL; ++i) tail_x[i] = tail_o[prow * D + lane * EPL + i];
     }
-    float M = -INFINITY;
-    for (int s = lane; s < p.nsplit; s += 64) M = fmaxf(M, ws_ml[(row0 + (size_t)s * p.R) * 2]);
+    float M = ml0.x;
+    for (int s = 64 + lane; s < p.nsplit; s += 64) M = fmaxf(M, ws_ml[(row0 + (size_t)s * p.R) * 2]);
     M = wave_max(M);
-    float Lsum = 0.0f, x[EPL];
+    float w = lane < p.nsplit && ml0.y > 0.0f ? exp2f(ml0.x - M) : 0.0f;
+    float Lsum = lane < p.nsplit ? ml0.y * w : 0.0f, x[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) x[i] = 0.0f;
-    for (int s0 = 0; s0 < p.nsplit; s0 += 64) {
-        const int s_mine = s0 + lane, cnt = min(64, p.nsplit - s0);
-        float w = 0.0f;
-        if (s_mine < p.nsplit) {
-            const float2 ml = *reinterpret_cast<const float2*>(ws_ml + (row0 + (size_t)s_mine * p.R) * 2);
-            w = ml.y > 0.0f ? exp2f(ml.x - M) : 0.0f;
-            Lsum = fmaf(ml.y, w, Lsum);
+#pragma unroll
+    for (int u = 0; u < PRE; ++u)
+        if (u < p.nsplit) {
+            const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), u));
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) x[i] = fmaf(v0[u][i], wu, x[i]);
         }
-        const float* src = ws_o + (row0 + (size_t)s0 * p.R) * D + lane * EPL;
-        const size_t stride = (size_t)p.R * D;
-        int k = 0;
+    for (int s0 = 0, k = PRE; s0 < p.nsplit; s0 += 64, k = 0) {
+        const int s_mine = s0 + lane, cnt = min(64, p.nsplit - s0);
+        if (s0 > 0) {
+            w = 0.0f;
+            if (s_mine < p.nsplit) {
+                const float2 ml = *reinterpret_cast<const float2*>(ws_ml + (row0 + (size_t)s_mine * p.R) * 2);
+                w = ml.y > 0.0f ? exp2f(ml.x - M) : 0.0f;
+                Lsum = fmaf(ml.y, w, Lsum);
+            }
+        }
+        const float* part = src + (size_t)s0 * stride;
         for (; k + 8 <= cnt; k += 8) {
             float v[8][EPL];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int i = 0; i < EPL; ++i) v[u][i] = src[(size_t)(k + u) * stride + i];
+                for (int i = 0; i < EPL; ++i) v[u][i] = part[(size_t)(k + u) * stride + i];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k + u));
@@ -314,7 +334,7 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const float* __restri
         for (; k < cnt; ++k) {
             const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k));
 #pragma unroll
-            for (int i = 0; i < EPL; ++i) x[i] = fmaf(src[(size_t)k * stride + i], wu, x[i]);
+            for (int i = 0; i < EPL; ++i) x[i] = fmaf(part[(size_t)k * stride + i], wu, x[i]);
         }
     }
     Lsum = wave_sum(Lsum);
