@@ -200,6 +200,11 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         nsplit = (int)want;
     }
     p.nsplit = nsplit;
+    p.split_tiles = (p.tiles + nsplit - 1) / nsplit;
+    p.div_G = FastDiv::by(p.G);
+    p.div_H = FastDiv::by(p.H);
+    p.div_nsplit = FastDiv::by(nsplit);
+    p.div_row_blocks = FastDiv::by(matrix_kernel_row_blocks(p));
 
     size_t off = 0;
     p.off_ml = off;

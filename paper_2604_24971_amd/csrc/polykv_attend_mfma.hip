@@ -587,14 +587,12 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     // each with an L2 of its own: the row blocks of a stream follow each other on one die, so that they read its records
     // from memory once.  (Row blocks in the outermost grid dimension read every record once per block from memory:
     // 1,450 us for 16 row blocks over 7,194 tokens, 1,165 us in this order.)
-    const int streams = p.layers * p.H * p.nsplit, row_blocks = (p.R + ROWS - 1) / ROWS;
-    const int slot = (int)(block >> 3);
-    const int stream = slot / row_blocks * 8 + (int)(block & 7);
-    if (stream >= streams) return;
-    const int row0 = slot % row_blocks * ROWS;
-    const int usel = stream / p.nsplit, split = stream - usel * p.nsplit;
-    const int ls = usel / p.H, kvh = usel - ls * p.H;
-    const int tps = (p.tiles + p.nsplit - 1) / p.nsplit;
+    int row_block, split, kvh;
+    const int stream = p.div_row_blocks.divide((int)(block >> 3), &row_block) * 8 + (int)(block & 7);
+    if (stream >= p.layers * p.H * p.nsplit) return;
+    const int row0 = row_block * ROWS;
+    const int usel = p.div_nsplit.divide(stream, &split), ls = p.div_H.divide(usel, &kvh);
+    const int tps = p.split_tiles;
     const int t_begin = split * tps, t_end = min(p.tiles, t_begin + tps);
     const uint8_t* unit_base = pool + (size_t)((p.layer_begin + ls) * p.H + kvh) * p.tiles_cap * TB;
     // One key scale per layer tensor: the keys enter the products as their integer codes and the scale
@@ -900,6 +898,11 @@ bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 
 static int launched_row_tiles(const AttendPlan& plan) { return plan.D != 256 && plan.R > 32 && plan.block_rows == 64 ? 2 : 1; }
 
+int matrix_kernel_row_blocks(const AttendPlan& plan) {
+    const int rows = 32 * launched_row_tiles(plan);
+    return (plan.R + rows - 1) / rows;
+}
+
 static long tail_waves(const AttendPlan& plan) {
     return (long)plan.A * plan.layers * plan.H * ((plan.nq * plan.G + kTailRows - 1) / kTailRows);
 }
@@ -929,7 +932,7 @@ static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, con
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
         });
     if (config_result != hipSuccess) return config_result;
-    const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = (plan.R + 32 * NT - 1) / (32 * NT);
+    const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = plan.div_row_blocks.d;
     const dim3 grid((unsigned)((streams + 7) / 8 * 8 * row_blocks));
     if constexpr (NT == 1 && D != 256) {
         if (tails != nullptr) {

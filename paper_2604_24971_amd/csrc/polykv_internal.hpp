@@ -30,6 +30,20 @@ namespace polykv {
 
 void set_error(const char* fmt, ...);
 
+// Division by a number the host knows, exact for every 32-bit numerator: the quotient by the multiplier is right or one
+// too small.  (The compiler's general division is 25 to 40 instructions, and a workgroup of the attention kernel had eight
+// of them in front of its first loads: 15 agents over 1,837 tokens 26.6 us a call, 26.4 us without.)
+struct FastDiv {
+    uint32_t d, m;
+    static FastDiv by(int divisor) { return FastDiv{(uint32_t)divisor, 0xFFFFFFFFu / (uint32_t)divisor}; }
+    __host__ __device__ inline int divide(int n, int* rem) const {   // n >= 0
+        uint32_t q = (uint32_t)(((uint64_t)(uint32_t)n * m) >> 32), r = (uint32_t)n - q * d;
+        if (r >= d) ++q, r -= d;
+        *rem = (int)r;
+        return (int)q;
+    }
+};
+
 // Everything pool_attend needs after validation; passed by value to the kernels.
 struct AttendPlan {
     int D, T, tiles, H;          // pool shape: T tokens encoded so far, in `tiles` tiles
@@ -42,6 +56,8 @@ struct AttendPlan {
     float qscale;                // softmax scale * log2(e): scores are kept in base-2 units
     int kernel;                  // POLYKV_KERNEL_VECTOR / _MATRIX (resolved)
     int nsplit;                  // token-range splits per KV head
+    int split_tiles;             // tiles of a split of what is filled
+    FastDiv div_G, div_H, div_nsplit, div_row_blocks;   // (matrix-core kernel: row blocks of a token stream)
     int block_rows;              // matrix-core kernel: query rows per workgroup, 64 or 32
     int has_tails, tail_capacity, tail_causal;
     int io_bf16;                 // 1: Q and the tails are bfloat16, 0: fp16
@@ -87,6 +103,8 @@ inline void launch_main_kernel(void (*kern)(Params...), dim3 grid, dim3 block, s
 
 // Query rows one workgroup of the matrix-core kernel covers.
 int matrix_kernel_block_rows(int head_dim);
+// Row blocks the matrix-core kernel is launched with, once R and block_rows of the plan are known.
+int matrix_kernel_row_blocks(const AttendPlan& plan);
 // True if the matrix-core kernel writes the final output itself (no merge kernel needed).
 bool matrix_kernel_direct(const AttendPlan& plan);
 // The private tails of a call and where their partials go.
@@ -102,7 +120,8 @@ hipError_t launch_attend_matrix(const polykv_pool* pool, const AttendPlan& plan,
 // Query row r of KV head kvh in selected layer ls -> index (in vectors of head_dim) into Q / out.
 // Rows of a KV head are ordered (agent, query, head-in-group): r = (a * nq + i) * G + g.
 __host__ __device__ inline size_t q_row_index(const AttendPlan& p, int ls, int kvh, int r) {
-    const int g = r % p.G, ai = r / p.G;
+    int g;
+    const int ai = p.div_G.divide(r, &g);
     return ((size_t)ls * p.A * p.nq + ai) * p.q_heads + kvh * p.G + g;
 }
 

@@ -76,7 +76,8 @@ __device__ __forceinline__ void tail_rows(const __half* __restrict__ Q, const Ta
     constexpr int LPR = D / 8;             // lanes per value row
     constexpr int TPL = 64 / LPR;          // tokens per wave load (token slots)
     constexpr int TB = tail_block_tokens(D), NT = TB / 16, NJ = D / 32, NLD = TB / TPL;
-    const int ls = usel / p.H, kvh = usel - ls * p.H;
+    int kvh, in_group;
+    const int ls = p.div_H.divide(usel, &kvh);
     const int rows_a = p.nq * p.G;         // rows of this agent within the KV head, contiguous
     const int r0 = a * rows_a + zb * kTailRows;
     const int r_end = min((a + 1) * rows_a, r0 + kTailRows);
@@ -85,7 +86,7 @@ __device__ __forceinline__ void tail_rows(const __half* __restrict__ Q, const Ta
     const int g = lane >> 4, col = lane & 15, row = col & 3, copy = col >> 2;
     // tokens the lane's row may see: all of them, or, for a causal multi-token step, one less for every query position
     // before the agent's last (row r0 + row is query (zb * 4 + row) / G)
-    const int qi = (zb * kTailRows + row) / p.G;
+    const int qi = p.div_G.divide(zb * kTailRows + row, &in_group);
     const int row_len = p.tail_causal ? max(0, len - (p.nq - 1 - min(qi, p.nq - 1))) : len;
     const size_t head_off = ((size_t)(p.layer_begin + ls) * p.H + kvh) * p.tail_capacity * D;
     uint16_t* Kt = const_cast<uint16_t*>(reinterpret_cast<const uint16_t*>(tails.K[a])) + head_off;
