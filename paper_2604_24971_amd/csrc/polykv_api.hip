@@ -169,7 +169,11 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         // Rows per workgroup: 64 where the kernel has such a form, but 32 when 64-row blocks, split as far as
         // the two-tiles-per-wave rule allows, would leave CUs without a workgroup (one-layer calls: 8 KV heads x
         // 16 splits = 128 workgroups of 64 rows, or 256 of 32 rows that each do half the matrix work).
-        auto splits_for = [&](int block_rows, long* n_groups) {
+        // With rows to spare, four waves that share 64 rows and take a fourth of the tiles each are slower than four that
+        // have 64 rows each and take all the tiles (own_rows): the same estimate says when.  512 rows over 300 tokens, 256
+        // KV heads: 8 rounds of 3 + 5 steps or 2 of 10 + 5, 66 and 46 us; 1,024 over 7,194: 16 of 57 + 5 or 4 of
+        // 225 + 5, 1,190 and 1,113 us.  With fewer KV heads (one layer, 1,024 rows) sharing fills the CUs and stays.
+        auto splits_for = [&](int block_rows, long* n_groups, int waves = 4, double* estimate = nullptr) {
             const long groups = (long)units * ((p.R + block_rows - 1) / block_rows);
             *n_groups = groups;
             const long most = (cap_tiles + 3) / 4;
@@ -179,22 +183,29 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             const double rows = (double)units * p.R;
             for (long n = 1; n <= cap_tiles / 8 || n == 1; ++n) {
                 if (n > 1 && rows * (n + (tails ? 1 : 0)) * (p.D + 2) * sizeof(float) + 1024 > POLYKV_STATIC_WORKSPACE_BYTES) break;
-                const long per_wave = ((cap_tiles + n - 1) / n + 3) / 4;
+                const long per_wave = ((cap_tiles + n - 1) / n + waves - 1) / waves;
                 double cost = (double)((groups * n + 255) / 256) * (per_wave + 5);
                 // the merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us
                 if (n > 1) cost += 3.5 + rows * n * p.D * 8 / 4e12 / 1.2e-6;
                 if (n == 1 || cost < least) least = cost, best = n;
                 if (groups * n >= 1024) break;   // finer splits only add partials
             }
+            if (estimate != nullptr) *estimate = least;
             return best;
         };
         int block_rows = matrix_kernel_block_rows(p.D);
         long groups = 0;
-        long want = splits_for(block_rows, &groups);
+        double shared = 0, own = 0;
+        long want = splits_for(block_rows, &groups, 4, &shared);
         if (block_rows == 64 && p.R > 32 && groups * want < 256) {
             long g32 = 0;
             const long w32 = splits_for(32, &g32);
             if (g32 * w32 > groups * want) block_rows = 32, want = w32;
+        }
+        if (prm->splits == 0 && p.R > 2 * block_rows && block_rows == matrix_kernel_block_rows(p.D)) {
+            long g_own = 0;
+            const long w_own = splits_for(4 * block_rows, &g_own, 1, &own);
+            if (own < shared) p.own_rows = 1, want = w_own;
         }
         p.block_rows = block_rows;
         nsplit = (int)want;

@@ -26,14 +26,16 @@
 // vector instructions) more than its length.  Scaling the block products instead of the keys (the exact dequantized key
 // has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
 //   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
-//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below)
+//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below;
+//                                                                      1,113 with rows of their own for the waves)
 // and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
 //   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
 //
 // The accumulation stays in the rotated value domain; the inverse Walsh-Hadamard rotation is done
 // once per output row (sections "Compression Scheme" / "TurboQuant", dequantization), in this kernel
 // when one workgroup covers the whole token range and there are no private tails, else in the merge
-// kernel.  The four waves of a workgroup take interleaved tiles and are merged through LDS.
+// kernel.  The four waves of a workgroup take interleaved tiles and are merged through LDS, or, where there
+// are rows for it, have rows of their own (OWN, below).
 #include <hip/hip_fp16.h>
 
 #include <mutex>
@@ -567,12 +569,19 @@ constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && 
 // ws_ml / ws_o: where the kernel leaves its split's partial (direct == 0); with direct == 1 and private tails,
 // the tail kernel's partials (row maxima and denominators / unnormalized sums), read in the final pass.
 // block: the workgroup's number among those that read the pool.
-template <int D, int NT, int VC, int KC, bool K16>
+// OWN: every wave has 32 NT query rows of its own and walks the whole token range of the split, instead of four waves
+// sharing the rows and taking every fourth tile: nothing to merge between the waves, a fourth of the workgroups, whose
+// ramps and final passes (five steps' worth, see make_plan) are then spread over four times the steps, and one record
+// serves the four waves from the L1.  Measured, shared rows and own rows, 32 layers x 8 KV heads x 128:
+//   1,024 rows, 7,194 tokens   1,190 and 1,113 us       256 rows, 4,096 tokens   172 and 160 us
+//   512 rows, 300 tokens          66 and 46 us          (head_dim 256, 128 rows, 2,500 tokens   132 and 113 us)
+template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ pool, const __half* __restrict__ Q,
                                                   float* __restrict__ ws_ml, float* __restrict__ ws_o,
                                                   float* __restrict__ out, const AttendPlan& p, int direct, uint32_t block) {
     using LY = Layout<D, VC, KC>;
     constexpr int NB = D / 32, MG = D / 32, ROWS = 32 * NT;
+    constexpr int WG_ROWS = OWN ? 4 * ROWS : ROWS, STEP = OWN ? 1 : 4;   // rows of the workgroup; tiles from one of a wave's to its next
     constexpr bool FOLD = fold_scales(KC, K16);
     constexpr int OSTRIDE = D + 4;
     constexpr int TB = LY::tile_bytes;
@@ -590,7 +599,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     int row_block, split, kvh;
     const int stream = p.div_row_blocks.divide((int)(block >> 3), &row_block) * 8 + (int)(block & 7);
     if (stream >= p.layers * p.H * p.nsplit) return;
-    const int row0 = row_block * ROWS;
+    const int row0 = row_block * WG_ROWS + (OWN ? wave * ROWS : 0);
     const int usel = p.div_nsplit.divide(stream, &split), ls = p.div_H.divide(usel, &kvh);
     const int tps = p.split_tiles;
     const int t_begin = split * tps, t_end = min(p.tiles, t_begin + tps);
@@ -603,14 +612,14 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         qscale *= s_tensor > 0.0f ? s_tensor : 1.0f;
     }
 
-    // this wave's tiles: t_begin + wave, +4, +8, ...; local index k <-> tile my_first + 4k
-    const int my_first = t_begin + wave;
-    const int my_count = my_first < t_end ? (t_end - my_first + 3) / 4 : 0;
+    // this wave's tiles: t_begin + wave, +4, +8, ... (OWN: all); local index k <-> tile my_first + STEP k
+    const int my_first = t_begin + (OWN ? 0 : wave);
+    const int my_count = my_first < t_end && (!OWN || row0 < p.R) ? (t_end - my_first + STEP - 1) / STEP : 0;
     // Byte offset of local tile k; k past the end is clamped (the loads of the last steps then fetch the wave's own last
     // tile again, harmlessly, instead of needing a branch per load).
     // (From the KV head's first record; pool_create keeps a KV head's records under 4 GiB.)
     const int last_k = max(my_count - 1, 0);
-    auto tile_off = [&](int k) { return (uint32_t)(my_first + 4 * min(k, last_k)) * (uint32_t)TB; };
+    auto tile_off = [&](int k) { return (uint32_t)(my_first + STEP * min(k, last_k)) * (uint32_t)TB; };
     const TileReader<D, VC, KC, K16> tr(make_tile_rsrc(unit_base, (uint32_t)p.tiles_cap * (uint32_t)TB), lane);
     StepState<D, NT, VC, KC, K16> cur;
     if (my_count > 0) {
@@ -624,14 +633,16 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     // The block of rows is fetched with fully coalesced 16-byte loads (16 lanes to a row) into LDS
     // (the merge buffers are idle until the end) and picked up from there in operand order.
     constexpr int QS = D + 8;  // halves per staged row: 16-byte aligned, rotates the banks
-    _Float16* q_s = reinterpret_cast<_Float16*>(o_s);
-    constexpr int QP = ROWS * (D / 8) / 256;  // 16-byte pieces per thread; all requested before any is used
-    static_assert(QP * 256 == ROWS * (D / 8), "");
+    constexpr int QT = OWN ? 64 : 256;        // threads that fetch a block of rows
+    const int qt = OWN ? lane : tid;
+    _Float16* q_s = reinterpret_cast<_Float16*>(o_s) + (OWN ? wave * ROWS * QS : 0);
+    constexpr int QP = ROWS * (D / 8) / QT;   // 16-byte pieces per thread; all requested before any is used
+    static_assert(QP * QT == ROWS * (D / 8), "");
     uint4v qraw[QP];
 #pragma unroll
     for (int u = 0; u < QP; ++u) {
         // rows past the end re-read the last row (no branch between the loads) and are zeroed below
-        const int i = tid + 256 * u, rr = i / (D / 8), piece = i - rr * (D / 8), r = min(row0 + rr, p.R - 1);
+        const int i = qt + QT * u, rr = i / (D / 8), piece = i - rr * (D / 8), r = min(row0 + rr, p.R - 1);
         qraw[u] = *reinterpret_cast<const uint4v*>(Q + q_row_index(p, ls, kvh, r) * D + 8 * piece);
     }
     // the accumulators are cleared while the queries and the first tiles are on their way
@@ -646,7 +657,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         }
 #pragma unroll
     for (int u = 0; u < QP; ++u) {
-        const int i = tid + 256 * u, rr = i / (D / 8), piece = i - rr * (D / 8);
+        const int i = qt + QT * u, rr = i / (D / 8), piece = i - rr * (D / 8);
         uint4v raw = row0 + rr < p.R ? qraw[u] : uint4v{0, 0, 0, 0};
         if (p.io_bf16) {  // bfloat16 queries become fp16 operands (exact for magnitudes fp16 holds)
 #pragma unroll
@@ -701,7 +712,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     // Local tile k is "B" in step k-1 (scores) and "A" in step k (softmax, PV).
     if (my_count > 0) {
         int k = 0;                                            // the step's tile A
-        auto rest = [&](int b) { return p.T - (my_first + 4 * b) * kTile; };   // tokens from tile b's first one on
+        auto rest = [&](int b) { return p.T - (my_first + STEP * b) * kTile; };   // tokens from tile b's first one on
         cur.first_operands();
         cur.k[0] = tr.kcodes(tile_off(1), 0);
         // prologue: scores of tile 0; requests the values of tile 0 and the keys of tile 1
@@ -762,22 +773,36 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                 }
         }
     }
-    __syncthreads();
+    if constexpr (OWN) {   // the wave's own buffer: its LDS accesses complete in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
 
     // ---- final pass: every wave finishes ROWS/4 rows, four lanes to a row.  Lane qd of a row takes every
     // fourth 4-coordinate piece (piece 4i + qd), so that the four lanes read and write 64 contiguous bytes per
     // instruction; the rotation is then log2(D/4) in-register stages and two DPP stages, whichever index bits
     // sit in the lane.
+    // (OWN: a wave finishes its own rows, 16 at a time, from its own buffer.)
     constexpr int CPL = D / 4, RPW = ROWS / 4;
     const int ri = elane >> 2, qd = elane & 3;
-    if (ri < RPW) {
-        const int rr = wave + 4 * ri, r = row0 + rr;
-        const float Mr = fmaxf(fmaxf(m_s[0][rr], m_s[1][rr]), fmaxf(m_s[2][rr], m_s[3][rr]));
-        float fw[4];  // a wave's weight: 2^(its maximum - the common one); 0 if it saw no tile
+#pragma unroll 1
+    for (int pass = 0; pass < (OWN ? ROWS / 16 : 1); ++pass) {
+        if (!OWN && ri >= RPW) break;
+        const int rr = OWN ? 16 * pass + ri : wave + 4 * ri, r = row0 + rr;
+        constexpr int NW = OWN ? 1 : 4;   // the waves that hold a share of the row
+        const int w0 = OWN ? wave : 0;
+        float Mr = m_s[w0][rr];
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-            fw[w] = m_s[w][rr] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_s[w][rr] - Mr);
-        const float l = (l_s[rr] * fw[0] + l_s[ROWS + rr] * fw[1]) + (l_s[2 * ROWS + rr] * fw[2] + l_s[3 * ROWS + rr] * fw[3]);
+        for (int w = 1; w < NW; ++w) Mr = fmaxf(Mr, m_s[w][rr]);
+        float fw[NW];  // a wave's weight: 2^(its maximum - the common one); 0 if it saw no tile
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            fw[w] = m_s[w0 + w][rr] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_s[w0 + w][rr] - Mr);
+        float l;
+        if constexpr (OWN) l = l_s[wave * ROWS + rr] * fw[0];
+        else l = (l_s[rr] * fw[0] + l_s[ROWS + rr] * fw[1]) + (l_s[2 * ROWS + rr] * fw[2] + l_s[3 * ROWS + rr] * fw[3]);
         // Direct output with private tails: the row's tail partial (maximum in base-2 units, denominator and
         // unnormalized sum in the original value domain; written by the tail kernel, which ran before this one
         // and whose buffers arrive in ws_ml / ws_o) joins by log-sum-exp weights: the pool part gets wa / den
@@ -803,17 +828,25 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                                        inv_l
                                  : kCS;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) fw[w] *= f;
+        for (int w = 0; w < NW; ++w) fw[w] *= f;
         float x[CPL];  // x[4i + k] = coordinate 16i + 4qd + k
-        const float4* a4 = reinterpret_cast<const float4*>(&o_s[rr * OSTRIDE]) + qd;
         constexpr int BUF4 = ROWS * OSTRIDE / 4;  // one wave's buffer, in float4 units
+        const float4* a4 = reinterpret_cast<const float4*>(&o_s[rr * OSTRIDE]) + w0 * BUF4 + qd;
 #pragma unroll
         for (int i = 0; i < CPL / 4; ++i) {
-            const float4 a = a4[4 * i], b = a4[BUF4 + 4 * i], c = a4[2 * BUF4 + 4 * i], d = a4[3 * BUF4 + 4 * i];
-            x[4 * i + 0] = (a.x * fw[0] + b.x * fw[1]) + (c.x * fw[2] + d.x * fw[3]);
-            x[4 * i + 1] = (a.y * fw[0] + b.y * fw[1]) + (c.y * fw[2] + d.y * fw[3]);
-            x[4 * i + 2] = (a.z * fw[0] + b.z * fw[1]) + (c.z * fw[2] + d.z * fw[3]);
-            x[4 * i + 3] = (a.w * fw[0] + b.w * fw[1]) + (c.w * fw[2] + d.w * fw[3]);
+            const float4 a = a4[4 * i];
+            if constexpr (OWN) {
+                x[4 * i + 0] = a.x * fw[0];
+                x[4 * i + 1] = a.y * fw[0];
+                x[4 * i + 2] = a.z * fw[0];
+                x[4 * i + 3] = a.w * fw[0];
+            } else {
+                const float4 b = a4[BUF4 + 4 * i], c = a4[2 * BUF4 + 4 * i], d = a4[3 * BUF4 + 4 * i];
+                x[4 * i + 0] = (a.x * fw[0] + b.x * fw[1]) + (c.x * fw[2] + d.x * fw[3]);
+                x[4 * i + 1] = (a.y * fw[0] + b.y * fw[1]) + (c.y * fw[2] + d.y * fw[3]);
+                x[4 * i + 2] = (a.z * fw[0] + b.z * fw[1]) + (c.z * fw[2] + d.z * fw[3]);
+                x[4 * i + 3] = (a.w * fw[0] + b.w * fw[1]) + (c.w * fw[2] + d.w * fw[3]);
+            }
         }
         if (direct) {
             if (VC != 2) {
@@ -857,11 +890,11 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     }
 }
 
-template <int D, int NT, int VC, int KC, bool K16>
-__global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(
+template <int D, int NT, int VC, int KC, bool K16, bool OWN>
+__global__ __launch_bounds__(256, OWN ? 1 : kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(
     const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
     float* __restrict__ out, AttendPlan p, int direct) {
-    attend_mfma_block<D, NT, VC, KC, K16>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.x);
+    attend_mfma_block<D, NT, VC, KC, K16, OWN>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.x);
 }
 
 // Two workgroups a CU wherever the pool's part fits 256 registers (left alone, the tails' part takes 324 at head_dim 128).
@@ -877,7 +910,7 @@ __global__ __launch_bounds__(256, tails_waves_per_simd(D, VC, KC)) void attend_m
     const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
     AttendPlan p, TailPtrs tails, float* __restrict__ tail_ml, float* __restrict__ tail_o, uint32_t pool_blocks) {
     if (blockIdx.x < pool_blocks) {
-        attend_mfma_block<D, 1, VC, KC, K16>(pool, Q, ws_ml, ws_o, nullptr, p, 0, blockIdx.x);
+        attend_mfma_block<D, 1, VC, KC, K16, false>(pool, Q, ws_ml, ws_o, nullptr, p, 0, blockIdx.x);
         return;
     }
     extern __shared__ __align__(16) float o_s[];
@@ -899,7 +932,7 @@ bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 static int launched_row_tiles(const AttendPlan& plan) { return plan.D != 256 && plan.R > 32 && plan.block_rows == 64 ? 2 : 1; }
 
 int matrix_kernel_row_blocks(const AttendPlan& plan) {
-    const int rows = 32 * launched_row_tiles(plan);
+    const int rows = 32 * launched_row_tiles(plan) * (plan.own_rows ? 4 : 1);
     return (plan.R + rows - 1) / rows;
 }
 
@@ -915,18 +948,18 @@ bool matrix_kernel_takes_tails(const AttendPlan& plan) {
            launched_row_tiles(plan) == 1 && tail_waves(plan) <= 4 * 256;
 }
 
-template <int D, int NT, int VC, int KC, bool K16>
+template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
                              float* ws_o, float* out, int direct, const TailPart* tails, hipStream_t s) {
     constexpr int kShared = 4 * 32 * NT * (D + 4) * (int)sizeof(float);   // the merge buffers
-    auto kern = attend_mfma_kernel<D, NT, VC, KC, K16>;
+    auto kern = attend_mfma_kernel<D, NT, VC, KC, K16, OWN>;
     static std::once_flag configured;  // per instantiation: the limit is a property of the function
     static hipError_t config_result = hipSuccess;
     if (kShared > 48 * 1024)
         std::call_once(configured, [&]() {
             config_result = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
-            if constexpr (NT == 1 && D != 256)
+            if constexpr (NT == 1 && D != 256 && !OWN)
                 if (config_result == hipSuccess)
                     config_result = hipFuncSetAttribute(reinterpret_cast<const void*>(attend_mfma_tails_kernel<D, VC, KC, K16>),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
@@ -934,7 +967,7 @@ static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, con
     if (config_result != hipSuccess) return config_result;
     const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = plan.div_row_blocks.d;
     const dim3 grid((unsigned)((streams + 7) / 8 * 8 * row_blocks));
-    if constexpr (NT == 1 && D != 256) {
+    if constexpr (NT == 1 && D != 256 && !OWN) {
         if (tails != nullptr) {
             const dim3 all((unsigned)(grid.x + (tail_waves(plan) + 3) / 4));
             launch_main_kernel(attend_mfma_tails_kernel<D, VC, KC, K16>, all, dim3(256), kShared, s, storage, (const __half*)Q,
@@ -954,9 +987,12 @@ static hipError_t launch_dv(const polykv_pool* pool, const AttendPlan& plan, con
     const int direct = matrix_kernel_direct(plan) ? 1 : 0;
     if constexpr (D != 256) {
         if (launched_row_tiles(plan) == 2)
-            return launch_one<D, 2, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
+            return plan.own_rows ? launch_one<D, 2, VC, KC, K16, true>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s)
+                                 : launch_one<D, 2, VC, KC, K16, false>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
+    } else if (plan.own_rows) {
+        return launch_one<D, 1, VC, KC, K16, true>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
     }
-    return launch_one<D, 1, VC, KC, K16>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
+    return launch_one<D, 1, VC, KC, K16, false>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
 }
 
 template <int D, int KC, bool K16>

@@ -58,7 +58,8 @@ struct AttendPlan {
     int nsplit;                  // token-range splits per KV head
     int split_tiles;             // tiles of a split of what is filled
     FastDiv div_G, div_H, div_nsplit, div_row_blocks;   // (matrix-core kernel: row blocks of a token stream)
-    int block_rows;              // matrix-core kernel: query rows per workgroup, 64 or 32
+    int block_rows;              // matrix-core kernel: query rows per wave, 64 or 32
+    int own_rows;                // 1: the waves of a workgroup have rows of their own, 0: they share them
     int has_tails, tail_capacity, tail_causal;
     int io_bf16;                 // 1: Q and the tails are bfloat16, 0: fp16
     int key_fp16;                // 1: scores over the dequantized keys rounded to fp16 (POLYKV_KEY_PRECISION_FP16)

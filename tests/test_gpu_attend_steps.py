@@ -52,3 +52,22 @@ def test_row_blocks_and_streams_that_do_not_fill_the_dies(heads, agents, splits)
     case = Case(cfg, rng.standard_normal((1, heads, T, d)).astype(np.float16),
                 rng.standard_normal((1, heads, T, d)).astype(np.float16))
     case.attend_check(rng.standard_normal((1, agents, 1, 4 * heads, d)).astype(np.float16), splits=splits)
+
+
+# Many rows over KV heads enough to fill the CUs more than once: the waves have rows of their own.  One tile, a few, a
+# ragged end; a last wave of one row and waves with none; a split token range (65 heads, 256 rows); private tails.
+@pytest.mark.parametrize("d,heads,T,agents,q,group,tails", [
+    (64, 40, 20, 33, 4, 4, False), (64, 40, 300, 57, 3, 3, False), (64, 65, 2300, 64, 1, 4, False), (128, 40, 131, 33, 4, 4, True),
+    (128, 40, 33, 57, 3, 3, False), (256, 40, 129, 43, 2, 3, True), (256, 40, 64, 65, 4, 1, False)])
+@pytest.mark.parametrize("codec", [dict(), dict(scaled_values=True), dict(key_per_tensor=True)])
+def test_waves_with_rows_of_their_own(d, heads, T, agents, q, group, tails, codec):
+    rng = np.random.default_rng(d + heads + T)
+    half = lambda *s: rng.standard_normal(s).astype(np.float16)
+    cfg = W.PoolConfig(0, "rows", 1, heads, heads * group, d, T, agents, q)
+    K = half(1, heads, T, d) * np.linspace(0.2, 4.0, T)[None, None, :, None].astype(np.float16)
+    case = Case(cfg, K, half(1, heads, T, d), **codec)
+    kw = {}
+    if tails:
+        lens = [(7 * a) % 20 for a in range(agents)]
+        kw = dict(tails_np=[(half(1, heads, 20, d), half(1, heads, 20, d)) for _ in lens], tails_len=lens)
+    case.attend_check(half(1, agents, q, heads * group, d), **kw)
