@@ -137,11 +137,11 @@ def other_config(pk, W, n, kprec):
     nbytes = packed + Q.numel() * 2 + out.numel() * 4 + tail_bytes
     R = cfg.rows_per_kv_head
     nt = 1 if R <= 32 else 2
-    t = call if tails is not None else kern                 # with tails a call is three kernels: stream-level time
+    t = call if tails is not None else kern                 # with tails a call is two kernels: stream-level time
     res = {"workload": cfg.name, "rows_per_kv_head": R, "tokens": T, "pool_bytes": packed, "tail_len": tail_len,
            "tail_bytes": tail_bytes, "algorithmic_bytes": nbytes, "pool_copies_rotated": copies,
            "kernel": "attend_mfma_kernel<%d,%d,0,0>" % (d, nt), "kernel_ms": kern * 1e3, "call_ms": call * 1e3,
-           "timed": "pool_attend back to back; " + ("call (tail kernel + pool kernel + merge kernel, stream events)"
+           "timed": "pool_attend back to back; " + ("call (tail kernel + pool kernel, stream events)"
                                                     if tails is not None else "the pool kernel's own events"),
            "GB_per_s": nbytes / t / 1e9, "frac_of_hbm_peak": nbytes / t / 1e9 / HBM_PEAK_GBPS}
     if R >= 256:                                            # matrix-bound shape: useful attention arithmetic
@@ -398,7 +398,7 @@ def main():
            "stream), median over the timed steps; traffic = the stored rocprofv3 FETCH_SIZE + WRITE_SIZE figure of "
            "profiles/ (copy-scaled), not measured in this run")
     vc = codec                                                          # the kernels' value-codec template argument
-    nt = 1 if (cfg.rows_per_kv_head <= 32 or d == 256 or (vc in (2, 6) and d == 128)) else 2
+    nt = 1 if (cfg.rows_per_kv_head <= 32 or d == 256) else 2
     kc = 1 if args.key_codec == "tensor" else 0
     attend_roof = roof(att_gbps, "attend_mfma_kernel<%d,%d,%d,%d,%s> (pool_attend)" % (d, nt, vc, kc, "true" if args.key_precision == "fp16" else "false") + how +
                        "; achieved = algorithmic bytes (packed pool + Q + out) / duration")

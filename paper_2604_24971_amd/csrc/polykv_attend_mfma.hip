@@ -282,8 +282,9 @@ template <typename SV> __device__ __forceinline__ float max16(const SV& a) {
 }
 
 // Four scores of a row -> fp16 probabilities (packed pairs) and their sum into lsum (the tile's sum).  FOLD: S holds
-// the exponents themselves (base-2 units, relative to the row's reference), else raw scores.  With value scales (g != nullptr: the lane's RawV::g) the P.V operand is p * scale of its token (formed in fp32,
-// rounded to fp16 once), at most 2^8 * 2^7; the denominator sums the plain, unrounded p.
+// the exponents themselves (base-2 units, relative to the row's reference), else raw scores.  With value scales (g, the
+// lane's StepState::g) the P.V operand is p * scale of its token (formed in fp32, rounded to fp16 once), at most
+// 2^8 * 2^7; the denominator sums the plain, unrounded p.
 template <bool VS, bool FOLD, typename SV>
 __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mneg, H8 (&pb)[2], float& lsum,
                                      const uint32_t* g, half2v one2, float* gmax = nullptr) {
