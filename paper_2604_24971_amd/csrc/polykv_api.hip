@@ -126,7 +126,12 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
     }
     p.signs = pool->signs;
 
-    p.kernel = prm->kernel == POLYKV_KERNEL_AUTO ? POLYKV_KERNEL_MATRIX : prm->kernel;
+    const bool mat_ok = matrix_kernel_supports(p.D, p.vcodec);
+    if (prm->kernel == POLYKV_KERNEL_MATRIX && !mat_ok) {
+        set_error("pool_attend: the matrix-core kernel does not support int8 values at head_dim=%d", p.D);
+        return POLYKV_ESHAPE;
+    }
+    p.kernel = prm->kernel != POLYKV_KERNEL_AUTO ? prm->kernel : mat_ok ? POLYKV_KERNEL_MATRIX : POLYKV_KERNEL_VECTOR;
     // Launch limits: the vector kernel and the tail kernel put their 4-row blocks on grid.z (at most 65,535).
     if (p.kernel == POLYKV_KERNEL_VECTOR && (p.R + 3) / 4 > 65535) {
         set_error("pool_attend: the vector kernel supports at most 262,140 query rows per KV head (got %d)", p.R);

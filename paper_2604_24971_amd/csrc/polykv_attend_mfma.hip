@@ -925,6 +925,10 @@ __global__ __launch_bounds__(256, tails_waves_per_simd(D, VC, KC)) void attend_m
     else tail_rows<D, false>(Q, tails, tail_ml, tail_o, p, a, usel, zb, threadIdx.x & 63, p_s);
 }
 
+// int8 values at head_dim 256 stay with the vector kernel: it keeps queries and probabilities in 32 bits, and takes bfloat16
+// queries of any magnitude; the matrix kernel would have both in fp16 (its registers hold the pair, it is not a matter of fit).
+bool matrix_kernel_supports(int head_dim, int value_codec) { return head_dim != 256 || value_codec != POLYKV_VALUES_INT8; }
+
 // Query rows per workgroup: 64 (32 at head_dim 256, where 64 rows' accumulators alone would fill the registers).
 int matrix_kernel_block_rows(int head_dim) { return head_dim == 256 ? 32 : 64; }
 
@@ -1001,7 +1005,9 @@ static hipError_t launch_dk(const polykv_pool* pool, const AttendPlan& plan, con
                             float* out, const TailPart* tails, hipStream_t s) {
     switch (plan.vcodec) {
         case 1: return launch_dv<D, 1, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
-        case 2: return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
+        case 2:
+            if constexpr (D == 256) return hipErrorInvalidValue;   // not built: matrix_kernel_supports() says no
+            else return launch_dv<D, 2, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
         case 3: return launch_dv<D, 3, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
         case 4: return launch_dv<D, 4, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);
         case 5: return launch_dv<D, 5, KC, K16>(pool, plan, Q, ws_ml, ws_o, out, tails, s);

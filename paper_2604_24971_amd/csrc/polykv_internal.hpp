@@ -102,6 +102,8 @@ inline void launch_main_kernel(void (*kern)(Params...), dim3 grid, dim3 block, s
         kern<<<grid, block, shmem, s>>>(static_cast<Params>(args)...);
 }
 
+// True if the matrix-core kernel takes pools of this head_dim and value codec.
+bool matrix_kernel_supports(int head_dim, int value_codec);
 // Query rows one workgroup of the matrix-core kernel covers.
 int matrix_kernel_block_rows(int head_dim);
 // Row blocks the matrix-core kernel is launched with, once R and block_rows of the plan are known.

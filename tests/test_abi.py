@@ -226,6 +226,20 @@ def test_the_split_count_does_not_outgrow_the_built_in_scratch(layers, kv_heads,
     lib.pool_destroy(h)
 
 
+@pytest.mark.parametrize("key_codec", [pk.KEYS_Q8_BLOCK32, pk.KEYS_Q8_TENSOR])
+def test_int8_values_at_head_dim_256_are_the_vector_kernels(key_codec):
+    h = C.c_void_p()
+    assert lib.pool_create_codecs(2, 4, 256, 900, key_codec, pk.VALUES_INT8, C.byref(h)) == pk.OK
+    p = pk.AttendParams()
+    p.agents, p.q_per_agent, p.q_heads, p.layer_end = 15, 1, 8, 2
+    auto = lib.pool_attend_workspace(h, C.byref(p))
+    p.kernel = pk.KERNEL_VECTOR
+    assert auto == lib.pool_attend_workspace(h, C.byref(p)) > 0
+    p.kernel = pk.KERNEL_MATRIX
+    assert lib.pool_attend_workspace(h, C.byref(p)) == 0 and b"does not support" in lib.polykv_last_error()
+    lib.pool_destroy(h)
+
+
 def test_python_binding_rejects_wrong_tensors_before_any_launch():
     import torch
     pool = pk.Pool(1, 2, 64, 50)

@@ -145,3 +145,26 @@ def test_int8_append_in_chunks_equals_one_encode(d, chunks):
         out = pool.attend(pu.dev(Q))
         torch.cuda.synchronize()
         pu.compare_attend(out, O.pool_attend(Kh, Vh, Q), H, dirty, 0, atol=pu.attend_row_atol(Kh, Vh, Q))
+
+
+def test_int8_head_dim_256_takes_bfloat16_queries_of_any_magnitude():
+    """Queries beyond the fp16 range over keys small enough to bring the scores back to a few units: what holds the
+    queries in fp16 sees infinities."""
+    pk, pu = _pk(), _pu()
+    rng = np.random.default_rng(256)
+    L, H, G, T, d, A = 1, 2, 2, 130, 256, 3
+    size = np.array([2e-5, 1.0])[None, :, None, None]
+    K = W.bf16_round((rng.standard_normal((L, H, T, d)) * size).astype(np.float32))
+    V = W.bf16_round(rng.standard_normal((L, H, T, d)).astype(np.float32))
+    Q = rng.standard_normal((L, A, 1, H, G, d)) / np.array([1e-5, 1.0])[:, None, None]
+    Q = W.bf16_round(Q.reshape(L, A, 1, H * G, d).astype(np.float32))
+    assert np.abs(Q).max() > 65504
+    ref = O.pool_encode(K, V, int8_values=True)
+    pool = pu.gpu_pool(K, V, int8_values=True, bf16=True)
+    pu.compare_codes(pool, ref)
+    Kh, Vh = O.pool_decode(ref)
+    out = pool.attend(pu.dev(Q, True))
+    pu.compare_attend(out, O.pool_attend(Kh, Vh, Q), H, atol=pu.attend_row_atol(Kh, Vh, Q))
+    assert torch.equal(out, pool.attend(pu.dev(Q, True), kernel=pk.KERNEL_VECTOR))
+    with pytest.raises(pk.PolyKVError):
+        pool.attend(pu.dev(Q, True), kernel=pk.KERNEL_MATRIX)
