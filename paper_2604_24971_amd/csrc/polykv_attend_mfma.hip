@@ -326,17 +326,24 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 //              its key codes and scales; on exit the same for the next step, requested from nextV (tile B), nextK (the
 //              tile after B) and, for block 0, whose operands are formed at the end of the step before, nextK0
 //   masked     (LAST only: tile B may be the pool's last) tokens of tile B from `masked` on lie past the end of the pool
+//   down       (REBASE only) rows whose maximum of tile A lies less than `down` below their reference take it for their reference
 //
 // Softmax bookkeeping: the reference m_ref (base-2 units) of a row only moves when the row's probabilities
 // of a tile, taken against the old reference, sum to more than kRaiseSum = 2^15 in one of the row's two lanes --
 // with value scales: when that sum times the largest scale among the lane's tokens of the tile does.  Every operand
 // that reaches a P.V product (a probability, or a probability times its token's scale) is therefore at most 2^15:
 // fp16 holds it; what matters for the result is the relative precision of a probability, which does not depend on
-// its magnitude, and a probability 2^-29 below the row's largest may flush to zero.  The common case takes no
+// its magnitude, down to fp16's smallest normal number: a probability less than 2^-14 of the row's reference (divided
+// by its token's value scale) loses bits, one less than 2^-25 is flushed to zero.  The common case takes no
 // maximum over the scores, and on keys with outlier channels, where a row's maximum keeps creeping up, the expensive
 // rescale of the accumulators stays rare: with a threshold of 2^8 it was a tenth of the kernel's time on the
 // Llama-shaped workload.
-constexpr float kRaiseSum = 32768.0f;
+//
+// Which tokens set a reference shows in the result.  A probability is rounded to fp16, except where it is a power of two: the
+// token that set the row's reference is exact, and the tokens with the largest probabilities make most of a row's error.
+// Whoever has the pool's last tile therefore takes references from it where it is not full: its few tokens may hold a maximum
+// (with the nine heaviest of 393 tokens there, an error of 2.1e-5 instead of 3.8e-5 at head_dim 128).
+constexpr float kRaiseSum = 32768.0f, kNoRebase = -INFINITY;
 
 template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     using TR = TileReader<D, VC, KC, K16>;
@@ -352,9 +359,9 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     }
 };
 
-template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST>
+template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
 __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
-                                              uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, float qscale,
+                                              uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, float down, float qscale,
                                               int lane, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
                                               float (&Lsum)[NT], float* m_ref, float (&mneg)[NT], const LoopConsts& lc) {
     using TR = TileReader<D, VC, KC, K16>;
@@ -385,6 +392,43 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         tr.kscales(nextK, sc_next);
         if constexpr (VS) tr.vscales(nextV, g_next);
     };
+
+    // the row's maximum of tile A in base-2 units (FOLD: the exponents are relative to the reference)
+    auto row_max = [&](int nt, float m_old) {
+        return FOLD ? m_old + xor32_max(max16(Sa[nt])) : xor32_max(max16(Sa[nt])) * qscale;
+    };
+    auto move_reference = [&](int nt, float m_old, float m_new, bool both) {
+        const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f(m_old - m_new);
+        m_ref[32 * nt] = m_new;
+        mneg[nt] = -m_new;
+        if constexpr (FOLD) {   // the exponents of the tiles in flight move along
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                Sa[nt][i] -= m_new - m_old;
+                if (both) Sb[nt][i] -= m_new - m_old;
+            }
+        }
+        // The accumulators live in accumulation registers that vector instructions cannot read; an MFMA with zero
+        // operands (D = 0*0 + C) carries them to vector registers and back, so the hot path never copies them.
+        Lsum[nt] *= alpha;
+#pragma unroll
+        for (int g = 0; g < MG; ++g) {
+            float16v y = mfma32(zero8, zero8, O[g][nt]);
+            y *= alpha;
+            O[g][nt] = mfma32(zero8, zero8, y);
+        }
+    };
+    // A tile that sets references does so before anything is taken relative to them.
+    static_assert(!REBASE || !HAS_B, "");
+    if constexpr (REBASE) {
+        if (down != kNoRebase) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float m_old = m_ref[32 * nt], m = row_max(nt, m_old), m_new = m >= m_old - down ? m : m_old;
+                if (__any(m_new != m_old)) move_reference(nt, m_old, m_new, false);
+            }
+        }
+    }
 
     // block j's products with row tile nt (FOLD): two of them take turns, one is folded while the other is formed
     float16v P[FOLD ? 2 : 1];
@@ -481,30 +525,9 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             for (int nt = 0; nt < NT; ++nt) {
                 const bool row_raise = !(xor32_max(lt[nt] * gmax) <= kRaiseSum);   // (+inf stays +inf through the max)
                 const float m_old = m_ref[32 * nt];
-                // the row's maximum in base-2 units (FOLD: the exponents are relative to the reference)
-                const float row_max = FOLD ? m_old + xor32_max(max16(Sa[nt])) : xor32_max(max16(Sa[nt])) * qscale;
-                const float m_new = row_raise ? fmaxf(m_old, row_max) : m_old;
+                const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : m_old;
                 if (!__any(m_new != m_old)) continue;   // no row of this row tile moves: it keeps what it has
-                const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f(m_old - m_new);
-                m_ref[32 * nt] = m_new;
-                mneg[nt] = -m_new;
-                if constexpr (FOLD) {   // the exponents of both tiles in flight move along
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        Sa[nt][i] -= m_new - m_old;
-                        if (HAS_B) Sb[nt][i] -= m_new - m_old;
-                    }
-                }
-                // The accumulators live in accumulation registers that vector instructions cannot read; an
-                // MFMA with zero operands (D = 0*0 + C) carries them to vector registers and back, so the
-                // hot path never copies them.
-                Lsum[nt] *= alpha;
-#pragma unroll
-                for (int g = 0; g < MG; ++g) {
-                    float16v y = mfma32(zero8, zero8, O[g][nt]);
-                    y *= alpha;
-                    O[g][nt] = mfma32(zero8, zero8, y);
-                }
+                move_reference(nt, m_old, m_new, HAS_B);
                 lt[nt] = 0.0f;
 #pragma unroll
                 for (int c = 4 * nt; c < 4 * nt + 4; ++c) exp_chunk(c);
@@ -719,8 +742,8 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         // prologue: scores of tile 0; requests the values of tile 0 and the keys of tile 1
 #pragma unroll
         for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
-        pipeline_step<D, NT, VC, KC, K16, false, true, false, true>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), qscale,
-                                                                   lane, qb, O, Lsum, m_ref, mneg, lc);
+        pipeline_step<D, NT, VC, KC, K16, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), 0.0f,
+                                                                   qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
 #pragma unroll
@@ -734,8 +757,8 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             }
         }
         auto main_step = [&]() {
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                       kTile, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                              kTile, 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
         while (k + 3 < my_count) {   // two steps a trip: the two tiles' scores swap registers without copies
@@ -743,9 +766,11 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             main_step();
         }
         for (; k + 1 < my_count; ++k)   // one or two: tile B may be the pool's last
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                      rest(k + 1), qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
-        pipeline_step<D, NT, VC, KC, K16, true, false, false, false>(cur, tr, 0, 0, 0, kTile, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                             rest(k + 1), 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+        const float down = rest(k) < kTile ? 0.0f : kNoRebase;
+        pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, lane, qb, O, Lsum,
+                                                                           m_ref, mneg, lc);
     }
 
     // ---- merge the four waves through LDS: every wave stores its row maxima, denominators and accumulators
