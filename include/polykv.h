@@ -215,6 +215,18 @@ typedef struct {
 /* Scratch bytes pool_attend needs for these parameters (workspace fields are ignored). */
 size_t pool_attend_workspace(const polykv_pool* pool, const polykv_attend_params* params);
 
+/* What pool_attend does with these parameters (workspace fields are ignored), for tests, benchmarks and profilers; host
+ * call, nothing is launched.  The choices are not part of the interface and may differ between versions. */
+typedef struct {
+    int kernel;               /* POLYKV_KERNEL_VECTOR or POLYKV_KERNEL_MATRIX                                  */
+    int splits;               /* token-range splits per KV head                                               */
+    int block_rows;           /* query rows a wave works on at a time                                         */
+    int own_rows;             /* 1: the waves of a workgroup have rows of their own, 0: they share them       */
+    int references;           /* tiles whose maxima a wave takes for softmax references, one after the other  */
+    int tails_in_pool_launch; /* 1: private tails are worked on in the pool kernel's launch                   */
+} polykv_attend_choice;
+int pool_attend_plan(const polykv_pool* pool, const polykv_attend_params* params, polykv_attend_choice* choice);
+
 /* Q_dev: fp16 (or bfloat16, see io_dtype) [layer_end-layer_begin, agents, q_per_agent, q_heads, head_dim];
  * out_dev: fp32, same shape.  Reads the pool only; concurrent calls on different streams are
  * safe if they use different workspaces.  POLYKV_ESHAPE for shapes beyond the launch limits: more than 2^20 query

@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 
@@ -27,6 +28,20 @@ KernelEvents take_kernel_events() {
     const KernelEvents ev = g_kernel_events;
     g_kernel_events = KernelEvents{};
     return ev;
+}
+
+// Splits of the token range with which 64-row workgroups (32-row ones where that gives more of them) fill the 256 CUs once,
+// as far as a wave keeps two tiles.
+static long matrix_kernel_fill_splits(int head_dim, int rows, long units, int cap_tiles) {
+    auto fill = [&](int block_rows, long* groups) {
+        *groups = units * ((rows + block_rows - 1) / block_rows);
+        return std::max(1l, std::min((256 + *groups - 1) / *groups, (long)cap_tiles / 8));
+    };
+    long groups = 0, g32 = 0;
+    const long n = fill(matrix_kernel_block_rows(head_dim), &groups);
+    if (head_dim == 256 || rows <= 32 || groups * n >= 256) return n;
+    const long n32 = fill(32, &g32);
+    return g32 * n32 > groups * n ? n32 : n;
 }
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -176,8 +191,13 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         // 16 splits = 128 workgroups of 64 rows, or 256 of 32 rows that each do half the matrix work).
         // With rows to spare, four waves that share 64 rows and take a fourth of the tiles each are slower than four that
         // have 64 rows each and take all the tiles (own_rows): the same estimate says when.  512 rows over 300 tokens, 256
-        // KV heads: 8 rounds of 3 + 5 steps or 2 of 10 + 5, 66 and 46 us; 1,024 over 7,194: 16 of 57 + 5 or 4 of
-        // 225 + 5, 1,190 and 1,113 us.  With fewer KV heads (one layer, 1,024 rows) sharing fills the CUs and stays.
+        // KV heads: 8 rounds of 3 + 5 steps or 2 of 10 + 5, 75 and 56 us; 1,024 over 7,194: 16 of 57 + 5 or 4 of
+        // 225 + 5, 1,145 and 1,086 us.  With fewer KV heads (one layer, 1,024 rows) sharing fills the CUs and stays.
+        // A row's softmax references (one per split and wave that shares it) are no fewer than filling the CUs once would give:
+        // what a plan lacks, its waves take from further tiles (kRebaseDown).  The estimate leaves that out: 16 layers of
+        // 1,500 tokens 15.1 us unsplit with one reference a wave, 16.2 with two, 20.3 in two splits.
+        const long fill = matrix_kernel_fill_splits(p.D, p.R, units, cap_tiles);
+        auto references_of = [&](long n, int waves) { return (4 / waves * fill + n - 1) / n; };
         auto splits_for = [&](int block_rows, long* n_groups, int waves = 4, double* estimate = nullptr) {
             const long groups = (long)units * ((p.R + block_rows - 1) / block_rows);
             *n_groups = groups;
@@ -212,10 +232,14 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             const long w_own = splits_for(4 * block_rows, &g_own, 1, &own);
             if (own < shared) p.own_rows = 1, want = w_own;
         }
+        // (the most that the accumulators' range allows; nothing automatic comes near)
+        if (prm->splits == 0) p.references = (int)std::min(references_of(want, p.own_rows ? 1 : 4), 16l);
         p.block_rows = block_rows;
         nsplit = (int)want;
     }
     p.nsplit = nsplit;
+    if (p.references == 0) p.references = 1;   // splits asked for by number: a reference each
+    p.raise_sum = p.references > 1 ? 2048.0f : 32768.0f;
     p.split_tiles = (p.tiles + nsplit - 1) / nsplit;
     p.div_G = FastDiv::by(p.G);
     p.div_H = FastDiv::by(p.H);
@@ -479,6 +503,24 @@ size_t pool_attend_workspace(const polykv_pool* pool, const polykv_attend_params
     AttendPlan plan;
     if (make_plan(pool, params, &plan) != POLYKV_OK) return 0;
     return plan.total;
+}
+
+int pool_attend_plan(const polykv_pool* pool, const polykv_attend_params* params, polykv_attend_choice* choice) {
+    AttendPlan plan;
+    const int rc = make_plan(pool, params, &plan);
+    if (rc != POLYKV_OK) return rc;
+    if (choice == nullptr) {
+        set_error("pool_attend_plan: NULL choice");
+        return POLYKV_EINVAL;
+    }
+    const bool matrix = plan.kernel == POLYKV_KERNEL_MATRIX;
+    choice->kernel = plan.kernel;
+    choice->splits = plan.nsplit;
+    choice->block_rows = matrix ? 32 * matrix_kernel_row_tiles(plan) : 4;
+    choice->own_rows = plan.own_rows;
+    choice->references = plan.references;
+    choice->tails_in_pool_launch = matrix_kernel_takes_tails(plan) ? 1 : 0;
+    return POLYKV_OK;
 }
 
 // pool_attend with the workspace already resolved: `workspace` holds at least plan.total bytes.

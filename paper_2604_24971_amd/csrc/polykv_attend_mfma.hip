@@ -27,7 +27,7 @@
 // has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
 //   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
 //   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below;
-//                                                                      1,113 with rows of their own for the waves)
+//                                                                      1,086 with rows of their own for the waves)
 // and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
 //   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
 //
@@ -243,8 +243,9 @@ template <typename SV> __device__ __forceinline__ void fold_block(SV& S, const f
 struct LoopConsts {
     uint32_t m7, m3, m4;   // byte masks 0x07070707, 0x03030303, 0x04040404 (value-code selectors)
     half2v one2;           // (1, 1): the packed dot product that sums a pair of probabilities
+    float raise_sum;       // AttendPlan::raise_sum
 };
-__device__ __forceinline__ LoopConsts make_loop_consts() {
+__device__ __forceinline__ LoopConsts make_loop_consts(float raise_sum) {
     uint32_t m7 = 0x07070707u, m3 = 0x03030303u, m4 = 0x04040404u, one = 0x3c003c00u;
     asm volatile("" : "+s"(m7), "+s"(m3), "+s"(m4), "+s"(one));   // opaque: the compiler would fold them back
     union {
@@ -252,7 +253,7 @@ __device__ __forceinline__ LoopConsts make_loop_consts() {
         half2v h;
     } o;
     o.u = one;
-    return LoopConsts{m7, m3, m4, o.h};
+    return LoopConsts{m7, m3, m4, o.h, raise_sum};
 }
 
 // Half hf (codes 4 hf .. 4 hf + 3) of coordinate group gi = 0..3 of a chunk of value codes -> fp16 centroids: half of
@@ -329,7 +330,7 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 //   down       (REBASE only) rows whose maximum of tile A lies less than `down` below their reference take it for their reference
 //
 // Softmax bookkeeping: the reference m_ref (base-2 units) of a row only moves when the row's probabilities
-// of a tile, taken against the old reference, sum to more than kRaiseSum = 2^15 in one of the row's two lanes --
+// of a tile, taken against the old reference, sum to more than raise_sum = 2^15 in one of the row's two lanes --
 // with value scales: when that sum times the largest scale among the lane's tokens of the tile does.  Every operand
 // that reaches a P.V product (a probability, or a probability times its token's scale) is therefore at most 2^15:
 // fp16 holds it; what matters for the result is the relative precision of a probability, which does not depend on
@@ -339,11 +340,21 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 // rescale of the accumulators stays rare: with a threshold of 2^8 it was a tenth of the kernel's time on the
 // Llama-shaped workload.
 //
-// Which tokens set a reference shows in the result.  A probability is rounded to fp16, except where it is a power of two: the
-// token that set the row's reference is exact, and the tokens with the largest probabilities make most of a row's error.
-// Whoever has the pool's last tile therefore takes references from it where it is not full: its few tokens may hold a maximum
-// (with the nine heaviest of 393 tokens there, an error of 2.1e-5 instead of 3.8e-5 at head_dim 128).
-constexpr float kRaiseSum = 32768.0f, kNoRebase = -INFINITY;
+// Which tokens set a reference shows in the result.  A probability is rounded to fp16, except where it is a power of two:
+// the token that set the row's reference is exact, and the tokens with the largest probabilities make most of a row's
+// error.  Every split and every wave that shares a row brings a reference of its own.  A plan with fewer of them than the one
+// that gives every CU a workgroup makes up for it:
+//   - a wave takes the maxima of its first AttendPlan::references tiles for references, one after the other, which costs a
+//     rescale of the accumulators each, about a step;
+//   - rows move their reference at sums of 2^11 (keys with outlier channels, where each of several waves would have moved
+//     its own).
+// And whoever has the pool's last tile takes references from it where it is not full, as its few tokens may hold a maximum.
+// Error against float64, rms over outputs, 32 layers x 8 KV heads x 128, with shared rows / own rows and one reference /
+// own rows as described: 512 rows over 300 tokens 1.30 / 1.51 / 1.30e-4; 1,024 rows over 7,194 tokens 1.513 / 1.526 / 1.496e-4.
+//
+// A reference moves down by kRebaseDown at most: a token further below the largest so far hardly shows in the result,
+// and the accumulators stay in range (16 references, 2^64).
+constexpr float kRebaseDown = 4.0f, kNoRebase = -INFINITY;
 
 template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     using TR = TileReader<D, VC, KC, K16>;
@@ -418,9 +429,11 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             O[g][nt] = mfma32(zero8, zero8, y);
         }
     };
-    // A tile that sets references does so before anything is taken relative to them.
-    static_assert(!REBASE || !HAS_B, "");
-    if constexpr (REBASE) {
+    // A tile that sets references does so before anything is taken relative to them, so that nothing is done twice (1,024 rows
+    // over 7,194 tokens 1,094 instead of 1,158 us).  Without FOLD and with a tile B the registers do not hold it here, and it is
+    // done with the rows that outgrew their references, further down.
+    constexpr bool EARLY = REBASE && (FOLD || !HAS_B);
+    if constexpr (EARLY) {
         if (down != kNoRebase) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
@@ -515,17 +528,18 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         // rows that outgrew their reference move it: a row's result depends on that row's scores alone, whatever other
         // agents' rows share the wave.
         // gmax: the largest value scale among the lane's 16 tokens of this tile (1 without value scales), collected
-        // by the chunks of row tile 0; the products probability x scale stay below kRaiseSum if the tile's sum of
+        // by the chunks of row tile 0; the products probability x scale stay below raise_sum if the tile's sum of
         // probabilities times gmax does
         bool raise = false;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) raise |= !(lt[nt] * gmax <= kRaiseSum);   // (inf and NaN say yes)
-        if (__builtin_expect(__any(raise), 0)) {
+        for (int nt = 0; nt < NT; ++nt) raise |= !(lt[nt] * gmax <= lc.raise_sum);   // (inf and NaN say yes)
+        const bool set_here = REBASE && !EARLY && down != kNoRebase;
+        if (__builtin_expect(__any(raise) || set_here, 0)) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const bool row_raise = !(xor32_max(lt[nt] * gmax) <= kRaiseSum);   // (+inf stays +inf through the max)
+                const bool row_raise = !(xor32_max(lt[nt] * gmax) <= lc.raise_sum);   // (+inf stays +inf through the max)
                 const float m_old = m_ref[32 * nt];
-                const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : m_old;
+                const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : set_here && m >= m_old - down ? m : m_old;
                 if (!__any(m_new != m_old)) continue;   // no row of this row tile moves: it keeps what it has
                 move_reference(nt, m_old, m_new, HAS_B);
                 lt[nt] = 0.0f;
@@ -597,8 +611,9 @@ constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && 
 // sharing the rows and taking every fourth tile: nothing to merge between the waves, a fourth of the workgroups, whose
 // ramps and final passes (five steps' worth, see make_plan) are then spread over four times the steps, and one record
 // serves the four waves from the L1.  Measured, shared rows and own rows, 32 layers x 8 KV heads x 128:
-//   1,024 rows, 7,194 tokens   1,190 and 1,113 us       256 rows, 4,096 tokens   172 and 160 us
-//   512 rows, 300 tokens          66 and 46 us          (head_dim 256, 128 rows, 2,500 tokens   132 and 113 us)
+//   1,024 rows, 7,194 tokens   1,145 and 1,086 us       256 rows, 4,096 tokens   171 and 161 us
+//   512 rows, 300 tokens          75 and 56 us          (head_dim 256, 128 rows, 2,500 tokens   135 and 121 us)
+// (own rows with as many references as the shared ones have, see kRebaseDown)
 template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ pool, const __half* __restrict__ Q,
                                                   float* __restrict__ ws_ml, float* __restrict__ ws_o,
@@ -731,7 +746,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         mneg[nt] = FOLD ? 0.0f : INFINITY;   // no reference yet: the first tile's maximum sets one
         Lsum[nt] = 0.0f;
     }
-    const LoopConsts lc = make_loop_consts();
+    const LoopConsts lc = make_loop_consts(p.raise_sum);
 
     // Local tile k is "B" in step k-1 (scores) and "A" in step k (softmax, PV).
     if (my_count > 0) {
@@ -756,6 +771,11 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                 for (int i = 0; i < 16; ++i) cur.S[nt][i] -= m0;
             }
         }
+        const int lead = p.references > 1 ? p.references : 0;
+        for (; k < lead && k + 1 < my_count; ++k)
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                            rest(k + 1), k > 0 ? kRebaseDown : kNoRebase, qscale, lane,
+                                                                            qb, O, Lsum, m_ref, mneg, lc);
         auto main_step = [&]() {
             pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                               kTile, 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
@@ -768,7 +788,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         for (; k + 1 < my_count; ++k)   // one or two: tile B may be the pool's last
             pipeline_step<D, NT, VC, KC, K16, true, true, true, true, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                              rest(k + 1), 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
-        const float down = rest(k) < kTile ? 0.0f : kNoRebase;
+        const float down = k > 0 && k < lead ? kRebaseDown : rest(k) < kTile ? 0.0f : kNoRebase;
         pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, lane, qb, O, Lsum,
                                                                            m_ref, mneg, lc);
     }
@@ -959,10 +979,10 @@ int matrix_kernel_block_rows(int head_dim) { return head_dim == 256 ? 32 : 64; }
 
 bool matrix_kernel_direct(const AttendPlan& plan) { return plan.nsplit == 1; }
 
-static int launched_row_tiles(const AttendPlan& plan) { return plan.D != 256 && plan.R > 32 && plan.block_rows == 64 ? 2 : 1; }
+int matrix_kernel_row_tiles(const AttendPlan& plan) { return plan.D != 256 && plan.R > 32 && plan.block_rows == 64 ? 2 : 1; }
 
 int matrix_kernel_row_blocks(const AttendPlan& plan) {
-    const int rows = 32 * launched_row_tiles(plan) * (plan.own_rows ? 4 : 1);
+    const int rows = 32 * matrix_kernel_row_tiles(plan) * (plan.own_rows ? 4 : 1);
     return (plan.R + rows - 1) / rows;
 }
 
@@ -975,7 +995,7 @@ static long tail_waves(const AttendPlan& plan) {
 // all CUs hold beside one pool workgroup each.
 bool matrix_kernel_takes_tails(const AttendPlan& plan) {
     return plan.has_tails && plan.kernel == POLYKV_KERNEL_MATRIX && !matrix_kernel_direct(plan) && plan.D != 256 &&
-           launched_row_tiles(plan) == 1 && tail_waves(plan) <= 4 * 256;
+           matrix_kernel_row_tiles(plan) == 1 && tail_waves(plan) <= 4 * 256;
 }
 
 template <int D, int NT, int VC, int KC, bool K16, bool OWN>
@@ -1016,7 +1036,7 @@ static hipError_t launch_dv(const polykv_pool* pool, const AttendPlan& plan, con
     const uint8_t* storage = reinterpret_cast<const uint8_t*>(pool->storage);
     const int direct = matrix_kernel_direct(plan) ? 1 : 0;
     if constexpr (D != 256) {
-        if (launched_row_tiles(plan) == 2)
+        if (matrix_kernel_row_tiles(plan) == 2)
             return plan.own_rows ? launch_one<D, 2, VC, KC, K16, true>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s)
                                  : launch_one<D, 2, VC, KC, K16, false>(storage, plan, Q, ws_ml, ws_o, out, direct, tails, s);
     } else if (plan.own_rows) {

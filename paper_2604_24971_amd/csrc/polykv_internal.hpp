@@ -59,6 +59,8 @@ struct AttendPlan {
     int split_tiles;             // tiles of a split of what is filled
     FastDiv div_G, div_H, div_nsplit, div_row_blocks;   // (matrix-core kernel: row blocks of a token stream)
     int block_rows;              // matrix-core kernel: query rows per wave, 64 or 32
+    int references;              // matrix-core kernel: tiles from whose maxima a wave takes a reference of its rows (>= 1)
+    float raise_sum;             // ... and the sum of a tile's probabilities beyond which a row moves its reference (<= 2^15)
     int own_rows;                // 1: the waves of a workgroup have rows of their own, 0: they share them
     int has_tails, tail_capacity, tail_causal;
     int io_bf16;                 // 1: Q and the tails are bfloat16, 0: fp16
@@ -106,6 +108,8 @@ inline void launch_main_kernel(void (*kern)(Params...), dim3 grid, dim3 block, s
 bool matrix_kernel_supports(int head_dim, int value_codec);
 // Query rows one workgroup of the matrix-core kernel covers.
 int matrix_kernel_block_rows(int head_dim);
+// Row tiles of 32 query rows that a wave of the matrix-core kernel holds.
+int matrix_kernel_row_tiles(const AttendPlan& plan);
 // Row blocks the matrix-core kernel is launched with, once R and block_rows of the plan are known.
 int matrix_kernel_row_blocks(const AttendPlan& plan);
 // True if the matrix-core kernel writes the final output itself (no merge kernel needed).

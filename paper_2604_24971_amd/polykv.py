@@ -42,6 +42,10 @@ class AttendParams(C.Structure):
     ]
 
 
+class AttendChoice(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("kernel", "splits", "block_rows", "own_rows", "references", "tails_in_pool_launch")]
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError(
@@ -82,6 +86,8 @@ def _load():
     lib.pool_export_value_scales.restype = ip
     lib.pool_attend_workspace.argtypes = [vp, C.POINTER(AttendParams)]
     lib.pool_attend_workspace.restype = sz
+    lib.pool_attend_plan.argtypes = [vp, C.POINTER(AttendParams), C.POINTER(AttendChoice)]
+    lib.pool_attend_plan.restype = ip
     lib.pool_attend.argtypes = [vp, vp, vp, C.POINTER(AttendParams), vp]
     lib.pool_attend.restype = ip
     lib.pool_attend_static.argtypes = [vp, vp, vp, C.POINTER(AttendParams), vp]
@@ -313,6 +319,15 @@ class Pool:
                                 kw.get("scale"), kw.get("tails"), kw.get("kernel", KERNEL_AUTO),
                                 kw.get("splits", 0), kw.get("tail_causal", False))
         return lib.pool_attend_workspace(self._h, C.byref(p))
+
+    def attend_plan(self, Q, **kw) -> AttendChoice:
+        """What attend(Q, **kw) does; for tests and benchmarks."""
+        p, _keep = self._params(Q, kw.get("q_heads"), kw.get("layer_begin", 0), kw.get("layer_end"), kw.get("scale"),
+                                kw.get("tails"), kw.get("kernel", KERNEL_AUTO), kw.get("splits", 0),
+                                kw.get("tail_causal", False), kw.get("key_precision", KEY_PRECISION_EXACT))
+        choice = AttendChoice()
+        _check(lib.pool_attend_plan(self._h, C.byref(p), C.byref(choice)))
+        return choice
 
     # pool_attend(Q[agents], out)
     def attend(self, Q: torch.Tensor, out: torch.Tensor | None = None, *, q_heads=None, layer_begin=0,

@@ -165,6 +165,38 @@ def test_automatic_split_counts(layers, heads, d, tokens, agents, group, splits)
     lib.pool_destroy(h)
 
 
+def _plan(h, **kw):
+    p, c = pk.AttendParams(), pk.AttendChoice()
+    for k, v in kw.items():
+        setattr(p, k, v)
+    assert lib.pool_attend_plan(h, C.byref(p), C.byref(c)) == pk.OK
+    return c
+
+
+def test_a_row_has_as_many_softmax_references_as_when_every_cu_has_a_workgroup():
+    import random
+    rng = random.Random(3)
+    few = 0
+    for _ in range(3000):
+        heads, layers, d = rng.choice([1, 3, 4, 8, 16, 32]), rng.randint(1, 40), rng.choice([64, 128, 256])
+        tokens, group = int(2 ** rng.uniform(3, 15)), rng.choice([1, 2, 4, 8])
+        agents, q = int(2 ** rng.uniform(0, 7)), rng.choice([1, 1, 2, 4])
+        rc, h = _create(layers, heads, d, tokens)
+        kw = dict(agents=agents, q_per_agent=q, q_heads=heads * group, layer_end=layers)
+        c = _plan(h, **kw)
+        rows, tiles = agents * q * group, (tokens + 31) // 32
+        # splits with which workgroups of 64 rows (256: 32), or of 32 if those are more, fill the 256 CUs once
+        fill = lambda block: max(1, min(-(-256 // (layers * heads * -(-rows // block))), tiles // 8))  # noqa: E731
+        groups = lambda block: layers * heads * -(-rows // block) * fill(block)  # noqa: E731
+        block = 32 if d == 256 or rows <= 32 or (groups(64) < 256 and groups(32) > groups(64)) else 64
+        assert c.references * c.splits * (1 if c.own_rows else 4) >= 4 * fill(block)
+        assert 1 <= c.references <= 16
+        few += c.references > 1
+        assert _plan(h, splits=3, **kw).references == 1      # splits by number: as they are
+        lib.pool_destroy(h)
+    assert few > 100
+
+
 def test_attend_plan_validation_and_workspace_size():
     rc, h = _create(4, 2, 128, 4000)
     p = pk.AttendParams()
@@ -235,6 +267,9 @@ def test_int8_values_at_head_dim_256_are_the_vector_kernels(key_codec):
     auto = lib.pool_attend_workspace(h, C.byref(p))
     p.kernel = pk.KERNEL_VECTOR
     assert auto == lib.pool_attend_workspace(h, C.byref(p)) > 0
+    c = pk.AttendChoice()
+    assert lib.pool_attend_plan(h, C.byref(p), C.byref(c)) == pk.OK and c.kernel == pk.KERNEL_VECTOR
+    assert lib.pool_attend_plan(h, C.byref(p), None) == pk.EINVAL
     p.kernel = pk.KERNEL_MATRIX
     assert lib.pool_attend_workspace(h, C.byref(p)) == 0 and b"does not support" in lib.polykv_last_error()
     lib.pool_destroy(h)
