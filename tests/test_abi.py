@@ -197,6 +197,69 @@ def test_a_row_has_as_many_softmax_references_as_when_every_cu_has_a_workgroup()
     assert few > 100
 
 
+def _splits_with_the_least_estimate(units, rows, d, cap_tiles, block, waves, tails):
+    """The rule of the split count, every count looked at."""
+    groups, best, least, n = units * -(-rows // block), 1, 0.0, 1
+    while n <= cap_tiles // 8 or n == 1:
+        if n > 1 and float(units * rows) * (n + tails) * (d + 2) * 4 + 1024 > pk.STATIC_WORKSPACE_BYTES:
+            break
+        cost = float(-(-groups * n // 256)) * (-(-(-(-cap_tiles // n)) // waves) + 5)
+        if n > 1:
+            cost = cost + 3.5 + float(units * rows) * d * (8 / 4e12 / 1.2e-6) * n
+        if n == 1 or cost < least:
+            least, best = cost, n
+        if groups * n >= 1024:
+            break
+        n += 1
+    return best, least, groups
+
+
+def test_the_search_for_the_split_count_finds_the_least_estimate():
+    import random
+    rng = random.Random(11)
+    seen = set()
+    for _ in range(4000):
+        heads, layers, d = rng.choice([1, 1, 2, 3, 4, 8, 16, 32]), rng.choice([1, 1, rng.randint(1, 40)]), rng.choice([64, 128, 256])
+        tokens, group = int(2 ** rng.uniform(3, 20)), rng.choice([1, 2, 4, 8])
+        agents, q, tails = int(2 ** rng.uniform(0, 7)), rng.choice([1, 1, 2, 4]), rng.random() < 0.3
+        agents = min(agents, 64) if tails else agents
+        rc, h = _create(layers, heads, d, tokens)
+        kw = dict(agents=agents, q_per_agent=q, q_heads=heads * group, layer_end=layers)
+        if tails:
+            none = (C.c_void_p * agents)()
+            kw.update(tail_K=none, tail_V=none, tail_len=(C.c_int * agents)())
+        c = _plan(h, **kw)
+        units, rows, tiles, block = layers * heads, agents * q * group, (tokens + 31) // 32, 32 if d == 256 else 64
+        rule = lambda b, w: _splits_with_the_least_estimate(units, rows, d, tiles, b, w, tails)  # noqa: E731
+        want, shared, groups = rule(block, 4)
+        used = block
+        if block == 64 and rows > 32 and groups * want < 256:
+            w32, _, g32 = rule(32, 4)
+            if g32 * w32 > groups * want:
+                want, used = w32, 32
+        own = False
+        if rows > 2 * used and used == block:
+            w_own, cost, _ = rule(4 * block, 1)
+            if cost < shared:
+                want, own = w_own, True
+        assert (c.splits, bool(c.own_rows)) == (want, own), (layers, heads, d, tokens, rows, tails)
+        seen.add((c.splits, own))
+        lib.pool_destroy(h)
+    assert len(seen) > 60
+
+
+def test_the_plan_of_a_long_context_costs_no_more_than_a_plan_without_a_search():
+    import timeit
+    rc, h = _create(1, 1, 128, 1_000_000)
+    p, c = pk.AttendParams(), pk.AttendChoice()
+    p.agents, p.q_per_agent, p.q_heads, p.layer_end = 15, 1, 4, 1
+    def seconds(splits):
+        p.splits = splits
+        return min(timeit.repeat(lambda: lib.pool_attend_plan(h, C.byref(p), C.byref(c)), number=200, repeat=20)) / 200
+    assert seconds(0) < 2 * seconds(64) + 0.2e-6     # (all counts looked at: 5 us more)
+    lib.pool_destroy(h)
+
+
 def test_attend_plan_validation_and_workspace_size():
     rc, h = _create(4, 2, 128, 4000)
     p = pk.AttendParams()
