@@ -224,6 +224,7 @@ typedef struct {
     int own_rows;             /* 1: the waves of a workgroup have rows of their own, 0: they share them       */
     int references;           /* tiles whose maxima a wave takes for softmax references, one after the other  */
     int tails_in_pool_launch; /* 1: private tails are worked on in the pool kernel's launch                   */
+    int grid[3];              /* workgroups of the pool kernel's launch, 256 threads each                     */
 } polykv_attend_choice;
 int pool_attend_plan(const polykv_pool* pool, const polykv_attend_params* params, polykv_attend_choice* choice);
 

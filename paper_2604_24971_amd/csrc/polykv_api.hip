@@ -264,6 +264,7 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
     p.div_H = FastDiv::by(p.H);
     p.div_nsplit = FastDiv::by(nsplit);
     p.div_row_blocks = FastDiv::by(matrix_kernel_row_blocks(p));
+    p.grid_x = matrix_kernel_grid(p).x;
 
     size_t off = 0;
     p.off_ml = off;
@@ -539,6 +540,8 @@ int pool_attend_plan(const polykv_pool* pool, const polykv_attend_params* params
     choice->own_rows = plan.own_rows;
     choice->references = plan.references;
     choice->tails_in_pool_launch = matrix_kernel_takes_tails(plan) ? 1 : 0;
+    const dim3 grid = matrix ? matrix_kernel_grid(plan) : vector_kernel_grid(plan);
+    choice->grid[0] = (int)grid.x, choice->grid[1] = (int)grid.y, choice->grid[2] = (int)grid.z;
     return POLYKV_OK;
 }
 

@@ -371,6 +371,8 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(const float* __restri
 }
 
 // --------------------------------------------------------------------------------- launcher ---
+dim3 vector_kernel_grid(const AttendPlan& plan) { return dim3(plan.nsplit / 4, plan.layers * plan.H, (plan.R + kRB - 1) / kRB); }
+
 hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const void* Q, void* out,
                          const TailPtrs* tails, void* workspace, hipStream_t s) {
     char* ws = reinterpret_cast<char*>(workspace);
@@ -406,7 +408,7 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
         if (err != hipSuccess) return err;
         if (direct) return hipSuccess;
     } else {
-        dim3 grid(plan.nsplit / 4, units, (plan.R + kRB - 1) / kRB);
+        const dim3 grid = vector_kernel_grid(plan);
         using Kern = decltype(&attend_vector_kernel<128, 0, 0>);
 #define POLYKV_VEC_ROW(D, KC)                                                                                   \
     {attend_vector_kernel<D, 0, KC>, attend_vector_kernel<D, 1, KC>, attend_vector_kernel<D, 2, KC>,            \

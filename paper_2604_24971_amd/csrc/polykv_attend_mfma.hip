@@ -637,7 +637,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     // 1,450 us for 16 row blocks over 7,194 tokens, 1,165 us in this order.)
     int row_block, split, kvh;
     const int stream = p.div_row_blocks.divide((int)(block >> 3), &row_block) * 8 + (int)(block & 7);
-    if (stream >= p.layers * p.H * p.nsplit) return;
+    if (stream >= p.layers * p.H * p.nsplit) return;   // (the dies' rounding, or that of a grid of two dimensions)
     const int row0 = row_block * WG_ROWS + (OWN ? wave * ROWS : 0);
     const int usel = p.div_nsplit.divide(stream, &split), ls = p.div_H.divide(usel, &kvh);
     const int tps = p.split_tiles;
@@ -940,7 +940,7 @@ template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 __global__ __launch_bounds__(256, OWN ? 1 : kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(
     const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
     float* __restrict__ out, AttendPlan p, int direct) {
-    attend_mfma_block<D, NT, VC, KC, K16, OWN>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.x);
+    attend_mfma_block<D, NT, VC, KC, K16, OWN>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.y * p.grid_x + blockIdx.x);
 }
 
 // Two workgroups a CU wherever the pool's part fits 256 registers (left alone, the tails' part takes 324 at head_dim 128).
@@ -955,14 +955,15 @@ template <int D, int VC, int KC, bool K16>
 __global__ __launch_bounds__(256, tails_waves_per_simd(D, VC, KC)) void attend_mfma_tails_kernel(
     const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
     AttendPlan p, TailPtrs tails, float* __restrict__ tail_ml, float* __restrict__ tail_o, uint32_t pool_blocks) {
-    if (blockIdx.x < pool_blocks) {
-        attend_mfma_block<D, 1, VC, KC, K16, false>(pool, Q, ws_ml, ws_o, nullptr, p, 0, blockIdx.x);
+    const uint32_t block = blockIdx.y * p.grid_x + blockIdx.x;
+    if (block < pool_blocks) {
+        attend_mfma_block<D, 1, VC, KC, K16, false>(pool, Q, ws_ml, ws_o, nullptr, p, 0, block);
         return;
     }
     extern __shared__ __align__(16) float o_s[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int units = p.layers * p.H;
-    const int job = (int)(blockIdx.x - pool_blocks) * 4 + wave;   // agents of a unit follow each other
+    const int job = (int)(block - pool_blocks) * 4 + wave;   // agents of a unit follow each other
     const int a = job % p.A, usel = job / p.A % units, zb = job / p.A / units;
     float* p_s = o_s + wave * tail_block_tokens(D) * kTailRows;
     // (a job past the last has no rows)
@@ -998,6 +999,18 @@ bool matrix_kernel_takes_tails(const AttendPlan& plan) {
            matrix_kernel_row_tiles(plan) == 1 && tail_waves(plan) <= 4 * 256;
 }
 
+static uint64_t pool_workgroups(const AttendPlan& plan) {
+    const uint64_t streams = (uint64_t)plan.layers * plan.H * plan.nsplit;
+    return (streams + 7) / 8 * 8 * plan.div_row_blocks.d;
+}
+
+// A grid dimension holds less than 2^32 threads, 16.7 million workgroups; beyond 2^23 of them (only splits asked for by number
+// over pools near 100 GB come there) the launch gets a second dimension.  Whole multiples of eight keep the order of the dies.
+dim3 matrix_kernel_grid(const AttendPlan& plan) {
+    const uint64_t all = pool_workgroups(plan) + (matrix_kernel_takes_tails(plan) ? (tail_waves(plan) + 3) / 4 : 0), most = 1u << 23;
+    return all <= most ? dim3((uint32_t)all) : dim3((uint32_t)most, (uint32_t)((all + most - 1) / most));
+}
+
 template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, const void* Q, float* ws_ml,
                              float* ws_o, float* out, int direct, const TailPart* tails, hipStream_t s) {
@@ -1015,13 +1028,12 @@ static hipError_t launch_one(const uint8_t* storage, const AttendPlan& plan, con
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kShared);
         });
     if (config_result != hipSuccess) return config_result;
-    const long streams = (long)plan.layers * plan.H * plan.nsplit, row_blocks = plan.div_row_blocks.d;
-    const dim3 grid((unsigned)((streams + 7) / 8 * 8 * row_blocks));
+    const dim3 grid = matrix_kernel_grid(plan);
+    if (grid.y > 65535) return hipErrorInvalidConfiguration;
     if constexpr (NT == 1 && D != 256 && !OWN) {
         if (tails != nullptr) {
-            const dim3 all((unsigned)(grid.x + (tail_waves(plan) + 3) / 4));
-            launch_main_kernel(attend_mfma_tails_kernel<D, VC, KC, K16>, all, dim3(256), kShared, s, storage, (const __half*)Q,
-                               ws_ml, ws_o, plan, *tails->ptrs, tails->ml, tails->o, (uint32_t)grid.x);
+            launch_main_kernel(attend_mfma_tails_kernel<D, VC, KC, K16>, grid, dim3(256), kShared, s, storage, (const __half*)Q,
+                               ws_ml, ws_o, plan, *tails->ptrs, tails->ml, tails->o, (uint32_t)pool_workgroups(plan));
             return hipGetLastError();
         }
     }

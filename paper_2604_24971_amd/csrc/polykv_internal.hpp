@@ -58,6 +58,7 @@ struct AttendPlan {
     int nsplit;                  // token-range splits per KV head
     int split_tiles;             // tiles of a split of what is filled
     FastDiv div_G, div_H, div_nsplit, div_row_blocks;   // (matrix-core kernel: row blocks of a token stream)
+    uint32_t grid_x;             // matrix-core kernel: workgroups in the grid's first dimension
     int block_rows;              // matrix-core kernel: query rows per wave, 64 or 32
     int references;              // matrix-core kernel: tiles from whose maxima a wave takes a reference of its rows (>= 1)
     float raise_sum;             // ... and the sum of a tile's probabilities beyond which a row moves its reference (<= 2^15)
@@ -112,6 +113,9 @@ int matrix_kernel_block_rows(int head_dim);
 int matrix_kernel_row_tiles(const AttendPlan& plan);
 // Row blocks the matrix-core kernel is launched with, once R and block_rows of the plan are known.
 int matrix_kernel_row_blocks(const AttendPlan& plan);
+dim3 vector_kernel_grid(const AttendPlan& plan);
+// The matrix-core kernel's grid, once all of the plan but grid_x is known.
+dim3 matrix_kernel_grid(const AttendPlan& plan);
 // True if the matrix-core kernel writes the final output itself (no merge kernel needed).
 bool matrix_kernel_direct(const AttendPlan& plan);
 // The private tails of a call and where their partials go.

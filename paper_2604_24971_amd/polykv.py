@@ -43,7 +43,8 @@ class AttendParams(C.Structure):
 
 
 class AttendChoice(C.Structure):
-    _fields_ = [(n, C.c_int) for n in ("kernel", "splits", "block_rows", "own_rows", "references", "tails_in_pool_launch")]
+    _fields_ = [(n, C.c_int) for n in ("kernel", "splits", "block_rows", "own_rows", "references", "tails_in_pool_launch")] + \
+        [("grid", C.c_int * 3)]
 
 
 def _load():

@@ -260,6 +260,23 @@ def test_the_plan_of_a_long_context_costs_no_more_than_a_plan_without_a_search()
     lib.pool_destroy(h)
 
 
+@pytest.mark.parametrize("heads,tokens,splits,tail", [
+    (65535, 40000, 300, 0), (65535, 34000, 257, 0), (65535, 32800, 256, 0), (60000, 40000, 313, 0), (900, 2_400_000, 18700, 1), (8, 4096, 16, 1)])
+def test_no_grid_dimension_outgrows_what_a_launch_may_have(heads, tokens, splits, tail):
+    """Up to the largest pools that fit the memory, in more splits than any automatic plan has: less than 2^32 threads in a
+    dimension, at most 65,535 workgroups in the others."""
+    h = C.c_void_p()
+    assert lib.pool_create_codec(1, heads, 64, tokens, pk.VALUES_TQ2, C.byref(h)) == pk.OK and lib.pool_bytes(h) < 280e9
+    kw = dict(tail_K=(C.c_void_p * 1)(), tail_V=(C.c_void_p * 1)(), tail_len=(C.c_int * 1)()) if tail else {}
+    c = _plan(h, agents=1, q_per_agent=1, q_heads=heads, layer_end=1, splits=splits, **kw)
+    x, y, z = c.grid
+    assert c.splits == splits and c.tails_in_pool_launch == tail
+    assert 256 * x < 2 ** 32 and y <= 65535 and z == 1
+    needed = (heads * splits + 7) // 8 * 8 + (heads + 3) // 4 * tail
+    assert needed <= x * y < needed + x and (y == 1 or x % 8 == 0)
+    lib.pool_destroy(h)
+
+
 def test_attend_plan_validation_and_workspace_size():
     rc, h = _create(4, 2, 128, 4000)
     p = pk.AttendParams()
