@@ -57,39 +57,104 @@ def _registers(text: str):
     return out
 
 
-def _check_mfma_distances(asm_path: str):
-    """Part of the attention kernel's matrix instructions are inline assembly, whose wait states the compiler does not
-    keep: two between a vector write of an operand and the instruction that reads it, twelve between the instruction and
-    a vector (or memory) access to its result.  The source is laid out so that they are kept; what the register
-    allocator inserts in between is not under its control.  Refuse a build in which a distance is too short."""
-    name, writes, results = None, {}, []    # VALU writes: register -> wait states since; MFMA results: (registers, since)
+# Wait states after a vector write before a matrix instruction or a DPP source reads the register, and after a matrix
+# instruction before a vector (or memory) access to its result.
+_OPERAND_WAIT, _RESULT_WAIT = 2, 12
+
+
+class _WaitStates:
+    """What is still under way at a place in the code: the registers that vector instructions and matrix instructions have
+    written, and the wait states since."""
+
+    def __init__(self, name, writes=None, results=None):
+        self.name, self.writes, self.results = name, dict(writes or {}), list(results or [])
+
+    def copy(self):
+        return _WaitStates(self.name, self.writes, self.results)
+
+    def clear(self):
+        self.writes, self.results = {}, []
+
+    def busy(self):
+        return bool(self.writes or self.results)
+
+    def _fresh(self, regs):
+        return any(self.writes.get(r, _OPERAND_WAIT) < _OPERAND_WAIT for r in regs)
+
+    def _unfinished(self, regs):
+        return any(regs & result for result, _ in self.results)
+
+    def step(self, op, rest, text):
+        mfma = "mfma_f32_32x32x16" in op    # (the smaller ones are all the compiler's own)
+        vector = op.startswith("v_")
+        if self.busy() or mfma or vector:
+            operands = [_registers(o) for o in rest.split(",")]
+            if mfma:
+                if any(self._fresh(o) for o in operands[1:]):
+                    raise RuntimeError("%s: operand written too shortly before: %s" % (self.name, text))
+                if self._unfinished(operands[1] | operands[2]):
+                    raise RuntimeError("%s: result of a matrix instruction read too early: %s" % (self.name, text))
+            elif vector or op.startswith(("ds_", "buffer_", "global_", "scratch_", "flat_")):
+                if self.results and self._unfinished(set().union(*operands)):
+                    raise RuntimeError("%s: result of a matrix instruction accessed too early: %s" % (self.name, text))
+                if "_dpp" in op and self._fresh(operands[1]):
+                    raise RuntimeError("%s: DPP source written too shortly before: %s" % (self.name, text))
+        states = int(rest) + 1 if op == "s_nop" else 1
+        if self.writes:
+            self.writes = {r: n + states for r, n in self.writes.items() if n + states < _OPERAND_WAIT}
+        if self.results:
+            self.results = [(regs, n + states) for regs, n in self.results if n + states < _RESULT_WAIT]
+        if mfma:
+            self.results.append((operands[0], 0))
+        elif vector and not op.startswith("v_cmp"):
+            for o in operands[:2] if "swap" in op else operands[:1]:
+                self.writes.update((r, 0) for r in o)
+
+
+def _check_wait_states(asm_path):
+    """Part of the attention kernel's matrix and DPP instructions are inline assembly, whose wait states the compiler does not
+    keep: two between a vector write of an operand (DPP: of the first source) and the instruction that reads it, twelve
+    between a matrix instruction and a vector (or memory) access to its result.  The source is laid out so that they are
+    kept; what the register allocator inserts in between is not under its control.  Refuse a build in which a distance is
+    too short, along the text or across a branch.  Returns the number of matrix instructions that were checked."""
+    name, code, labels, matrix = None, [], {}, 0
+
+    def follow(at, state):      # from a branch's target, as long as something is under way
+        while at < len(code) and state.busy():
+            op, rest, text = code[at]
+            state.step(op, rest, text)
+            if op.startswith(("s_branch", "s_cbranch")) and rest in labels and state.busy():
+                follow(labels[rest], state.copy())
+            if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                return
+            at += 1
+
+    def check_function():
+        state = _WaitStates(name)
+        for op, rest, text in code:
+            state.step(op, rest, text)
+            if op.startswith(("s_branch", "s_cbranch")) and rest in labels and state.busy():
+                follow(labels[rest], state.copy())
+            if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                state.clear()
+
     for line in open(asm_path):
-        m = re.match(r"^(_Z\S+):", line)
-        if m:
-            name, writes, results = m.group(1), {}, []
+        m = re.match(r"^([\w.$]+):", line)
+        if m and m.group(1).startswith("_Z"):
+            check_function()
+            name, code, labels = m.group(1), [], {}
+        elif m:
+            labels[m.group(1)] = len(code)
         text = line.split(";")[0].strip()
         if not text or text.startswith(".") or text.endswith(":"):
             continue
-        op, _, rest = text.partition(" ") if "\t" not in text else text.partition("\t")
-        operands = [_registers(o) for o in rest.split(",")]
-        mfma = "mfma_f32_32x32x16" in op    # (the smaller ones are all the compiler's own)
-        if mfma:
-            if any(writes.get(r, 9) < 2 for o in operands[1:] for r in o):
-                raise RuntimeError("%s: operand written too shortly before: %s" % (name, text))
-            if any((operands[1] | operands[2]) & regs for regs, since in results if since < 12):
-                raise RuntimeError("%s: result of a matrix instruction read too early: %s" % (name, text))
-        elif op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_", "flat_")):
-            touched = set().union(*operands)
-            if any(touched & regs for regs, since in results if since < 12):
-                raise RuntimeError("%s: result of a matrix instruction accessed too early: %s" % (name, text))
-        states = int(rest) + 1 if op == "s_nop" else 1
-        writes = {r: since + states for r, since in writes.items() if since + states < 3}
-        results = [(regs, since + states) for regs, since in results if since + states < 12]
-        if mfma:
-            results.append((operands[0], 0))
-        elif op.startswith("v_") and not op.startswith("v_cmp"):
-            for o in operands[:2] if "swap" in op else operands[:1]:
-                writes.update((r, 0) for r in o)
+        op, _, rest = text.replace("\t", " ").partition(" ")
+        matrix += "mfma_f32_32x32x16" in op
+        code.append((op, rest.strip(), text))
+    check_function()
+    if not matrix:
+        raise RuntimeError("%s holds no matrix instruction: the check reads the wrong file" % asm_path)
+    return matrix
 
 
 def build_library(verbose: bool = True, extra_flags=()) -> str:
@@ -104,7 +169,7 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
         if SOURCES[i] == "polykv_attend_mfma.hip":
             log = _run(cmd + ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics", "-save-temps=obj"])
             _check_no_scratch(log)
-            _check_mfma_distances(os.path.join(objdir, "polykv_attend_mfma-hip-amdgcn-amd-amdhsa-gfx950.s"))
+            _check_wait_states(os.path.join(objdir, "polykv_attend_mfma-hip-amdgcn-amd-amdhsa-gfx950.s"))
             return "\n".join(l for l in log.splitlines() if "kernel-resource-usage" not in l)
         return _run(cmd)
 
