@@ -182,9 +182,6 @@ class Tails:
                 self.len[a] = int(ent[2])
         if lengths is not None:
             self.set_lengths(lengths)
-        # the arrays stay where they are: their pointers are made once
-        self._pointers = (C.cast(self.k, C.POINTER(C.c_void_p)), C.cast(self.v, C.POINTER(C.c_void_p)),
-                          C.cast(self.len, C.POINTER(C.c_int)))
 
     def set_lengths(self, lengths):
         if len(lengths) != self.agents:
@@ -309,7 +306,7 @@ class Pool:
                 raise ValueError("tails must have one entry per agent")
             if tails.dtype is not None and tails.dtype != Q.dtype:
                 raise TypeError("Q and the tails must have the same dtype")
-            p.tail_K, p.tail_V, p.tail_len = tails._pointers
+            p.tail_K, p.tail_V, p.tail_len = tails.k, tails.v, tails.len    # (arrays become pointers without a cast)
             p.tail_capacity = tails.capacity
             p.tail_causal = 1 if tail_causal else 0
             keep.append(tails)

@@ -368,6 +368,19 @@ def test_python_binding_rejects_wrong_tensors_before_any_launch():
         pk.Pool(1, 2, 80, 50)
 
 
+def test_a_call_takes_the_tails_arrays_as_they_are_now():
+    import torch
+    pool = pk.Pool(1, 2, 64, 50)
+    Q = torch.empty((1, 3, 1, 2, 64), dtype=torch.float16)
+    tails = pk.Tails(pool, [None, None, None], [0, 0, 0])
+    tails.len = (C.c_int * 3)(5, 6, 7)                 # exchanged, not written in place
+    tails.k = (C.c_void_p * 3)(0x100, 0x200, 0x300)
+    p, keep = pool._params(Q, None, 0, None, None, tails, pk.KERNEL_AUTO, 0)
+    assert [p.tail_len[a] for a in range(3)] == [5, 6, 7] and p.tail_K[2] == 0x300 and keep[0] is tails
+    assert tails.set_lengths([1, 2, 3]) is tails and [p.tail_len[a] for a in range(3)] == [1, 2, 3]
+    pool.close()
+
+
 def test_header_is_valid_c99(tmp_path):
     # the boundary is a C ABI: the header must compile as plain C, on its own
     import shutil
