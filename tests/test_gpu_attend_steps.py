@@ -4,8 +4,9 @@ keys that grow along the context, so that rows keep moving their softmax referen
 import numpy as np
 import pytest
 
+from oracle import polykv_oracle as O
 from paper_2604_24971_amd import workloads as W
-from test_gpu_parity import Case, _pk
+from test_gpu_parity import Case, _pk, _pu
 
 pytestmark = pytest.mark.gpu
 
@@ -70,4 +71,58 @@ def test_waves_with_rows_of_their_own(d, heads, T, agents, q, group, tails, code
     if tails:
         lens = [(7 * a) % 20 for a in range(agents)]
         kw = dict(tails_np=[(half(1, heads, 20, d), half(1, heads, 20, d)) for _ in lens], tails_len=lens)
-    case.attend_check(half(1, agents, q, heads * group, d), **kw)
+    Q = half(1, agents, q, heads * group, d)
+    assert case.pool.attend_plan(_pu().dev(Q)).own_rows == 1
+    case.attend_check(Q, **kw)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("codec", [dict(int8_values=True), dict(value_bits=2), dict(value_bits=2, scaled_values=True), dict(value_bits=4),
+                                   dict(value_bits=4, scaled_values=True), dict(value_bits=4, key_per_tensor=True)])
+def test_waves_with_rows_of_their_own_and_the_other_codecs(d, codec):
+    if d == 256 and "int8_values" in codec:
+        pytest.skip("the vector kernel's")
+    rng = np.random.default_rng(d + len(codec))
+    heads, T, agents, q, group = 40, 32 * 6 + 9, 33, 4, 4     # 528 rows: a last workgroup of one wave, six tiles and a few tokens
+    half = lambda *s: rng.standard_normal(s).astype(np.float16)
+    cfg = W.PoolConfig(0, "rows", 1, heads, heads * group, d, T, agents, q)
+    K = half(1, heads, T, d) * np.linspace(0.2, 4.0, T)[None, None, :, None].astype(np.float16)
+    case = Case(cfg, K, half(1, heads, T, d), **codec)
+    Q = half(1, agents, q, heads * group, d)
+    assert case.pool.attend_plan(_pu().dev(Q)).own_rows == 1
+    case.attend_check(Q)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bf16,fp16_keys,causal", [(True, False, False), (False, True, False), (True, True, True), (False, False, True)])
+def test_waves_with_rows_of_their_own_and_the_other_options(d, bf16, fp16_keys, causal):
+    pk, pu = _pk(), _pu()
+    rng = np.random.default_rng(d + 2 * bf16 + fp16_keys)
+    heads, T, agents, q, group, cap = 40, 32 * 5 + 30, 40, 4, 3, 35
+    rnd = (lambda x: W.bf16_round(x.astype(np.float32))) if bf16 else (lambda x: x.astype(np.float16))
+    draw = lambda *s: rnd(rng.standard_normal(s))
+    K, V, Q = draw(1, heads, T, d), draw(1, heads, T, d), draw(1, agents, q, heads * group, d)
+    pool = pu.gpu_pool(K, V, bf16=bf16)
+    ref = O.pool_encode(K, V)
+    pu.compare_codes(pool, ref)
+    Kh, Vh = O.pool_decode(ref)
+    if fp16_keys and d != 256:       # (exact keys at head_dim 256 whatever is asked for)
+        Kh = O.keys_as_fp16(Kh)
+    lens = [(11 * a) % (cap + 1) for a in range(agents)]
+    tails = [(draw(1, heads, cap, d), draw(1, heads, cap, d)) for _ in lens] if causal else None
+    gpu = [(pu.dev(k, bf16), pu.dev(v, bf16), n) for (k, v), n in zip(tails, lens)] if causal else None
+    cut = [(k[:, :, :n], v[:, :, :n]) for (k, v), n in zip(tails, lens)] if causal else None
+    kw = dict(key_precision=pk.KEY_PRECISION_FP16 if fp16_keys else pk.KEY_PRECISION_EXACT, tails=gpu, tail_causal=causal)
+    assert pool.attend_plan(pu.dev(Q, bf16), **kw).own_rows == 1
+    out = pool.attend(pu.dev(Q, bf16), **kw)
+    pu.compare_attend(out, O.pool_attend(Kh, Vh, Q, tails=cut, tail_causal=causal), heads)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("codec", [dict(), dict(value_bits=4), dict(value_bits=2, scaled_values=True)])
+def test_splits_that_are_merged(d, codec):
+    """(Small pools are no longer split by themselves.)"""
+    case, Q = _case(d, 32 * 13 + 6, growing=True, **codec)
+    for splits in (2, 3):
+        assert case.pool.attend_plan(_pu().dev(Q), splits=splits).splits == splits
+        case.attend_check(Q, splits=splits)
