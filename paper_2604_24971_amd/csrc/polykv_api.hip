@@ -192,10 +192,10 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
         // With rows to spare, four waves that share 64 rows and take a fourth of the tiles each are slower than four that
         // have 64 rows each and take all the tiles (own_rows): the same estimate says when.  512 rows over 300 tokens, 256
         // KV heads: 8 rounds of 3 + 5 steps or 2 of 10 + 5, 75 and 56 us; 1,024 over 7,194: 16 of 57 + 5 or 4 of
-        // 225 + 5, 1,145 and 1,086 us.  With fewer KV heads (one layer, 1,024 rows) sharing fills the CUs and stays.
+        // 225 + 5, 1,158 and 1,100 us.  With fewer KV heads (one layer, 1,024 rows) sharing fills the CUs and stays.
         // A row's softmax references (one per split and wave that shares it) are no fewer than filling the CUs once would give:
         // what a plan lacks, its waves take from further tiles (kRebaseDown).  The estimate leaves that out: 16 layers of
-        // 1,500 tokens 15.1 us unsplit with one reference a wave, 16.2 with two, 20.3 in two splits.
+        // 1,500 tokens 14.7 us unsplit with one reference a wave, 15.4 with two, 20.2 in two splits.
         const long fill = matrix_kernel_fill_splits(p.D, p.R, units, cap_tiles);
         auto references_of = [&](long n, int waves) { return (4 / waves * fill + n - 1) / n; };
         auto splits_for = [&](int block_rows, long* n_groups, int waves = 4, double* estimate = nullptr) {

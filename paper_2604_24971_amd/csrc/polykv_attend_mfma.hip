@@ -27,7 +27,7 @@
 // has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
 //   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
 //   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below;
-//                                                                      1,086 with rows of their own for the waves)
+//                                                                      1,100 with rows of their own for the waves)
 // and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
 //   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
 //
@@ -344,13 +344,14 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 // the token that set the row's reference is exact, and the tokens with the largest probabilities make most of a row's
 // error.  Every split and every wave that shares a row brings a reference of its own.  A plan with fewer of them than the one
 // that gives every CU a workgroup makes up for it:
-//   - a wave takes the maxima of its first AttendPlan::references tiles for references, one after the other, which costs a
-//     rescale of the accumulators each, about a step;
+//   - besides its first tile's, a wave takes the maxima of its last AttendPlan::references - 1 tiles for references, one after
+//     the other, which costs a rescale of the accumulators each, about a step (the first ones would do as well, but take
+//     steps of their own in front of the loop: 0.5 us of 25 in the SmolLM2-shaped call, which has no use for them);
 //   - rows move their reference at sums of 2^11 (keys with outlier channels, where each of several waves would have moved
 //     its own).
 // And whoever has the pool's last tile takes references from it where it is not full, as its few tokens may hold a maximum.
 // Error against float64, rms over outputs, 32 layers x 8 KV heads x 128, with shared rows / own rows and one reference /
-// own rows as described: 512 rows over 300 tokens 1.30 / 1.51 / 1.30e-4; 1,024 rows over 7,194 tokens 1.513 / 1.526 / 1.496e-4.
+// own rows as described: 512 rows over 300 tokens 1.32 / 1.51 / 1.32e-4; 1,024 rows over 7,194 tokens 1.51 / 1.53 / 1.48e-4.
 //
 // A reference moves down by kRebaseDown at most: a token further below the largest so far hardly shows in the result,
 // and the accumulators stay in range (16 references, 2^64).
@@ -430,7 +431,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         }
     };
     // A tile that sets references does so before anything is taken relative to them, so that nothing is done twice (1,024 rows
-    // over 7,194 tokens 1,094 instead of 1,158 us).  Without FOLD and with a tile B the registers do not hold it here, and it is
+    // over 7,194 tokens 1,094 instead of 1,158 us, 512 over 300 tokens 57 instead of 59).  Without FOLD and with a tile B the registers do not hold it here, and it is
     // done with the rows that outgrew their references, further down.
     constexpr bool EARLY = REBASE && (FOLD || !HAS_B);
     if constexpr (EARLY) {
@@ -611,8 +612,8 @@ constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && 
 // sharing the rows and taking every fourth tile: nothing to merge between the waves, a fourth of the workgroups, whose
 // ramps and final passes (five steps' worth, see make_plan) are then spread over four times the steps, and one record
 // serves the four waves from the L1.  Measured, shared rows and own rows, 32 layers x 8 KV heads x 128:
-//   1,024 rows, 7,194 tokens   1,145 and 1,086 us       256 rows, 4,096 tokens   171 and 161 us
-//   512 rows, 300 tokens          75 and 56 us          (head_dim 256, 128 rows, 2,500 tokens   135 and 121 us)
+//   1,024 rows, 7,194 tokens   1,158 and 1,100 us       256 rows, 4,096 tokens   171 and 163 us
+//   512 rows, 300 tokens          75 and 56 us          (head_dim 256, 128 rows, 2,500 tokens   133 and 118 us)
 // (own rows with as many references as the shared ones have, see kRebaseDown)
 template <int D, int NT, int VC, int KC, bool K16, bool OWN>
 __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ pool, const __half* __restrict__ Q,
@@ -771,24 +772,25 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                 for (int i = 0; i < 16; ++i) cur.S[nt][i] -= m0;
             }
         }
-        const int lead = p.references > 1 ? p.references : 0;
-        for (; k < lead && k + 1 < my_count; ++k)
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                            rest(k + 1), k > 0 ? kRebaseDown : kNoRebase, qscale, lane,
-                                                                            qb, O, Lsum, m_ref, mneg, lc);
+        // The wave's last tiles set references besides the first, as many as the plan says, and one that is not full on top; by
+        // itself the latter only raises them.
+        const bool ragged = rest(my_count - 1) < kTile;
+        const int setting = my_count - (p.references > 1 ? p.references - 1 + (ragged ? 1 : 0) : 0);   // from this tile on
+        const int pairs_end = min(my_count - 3, setting - 1);
         auto main_step = [&]() {
             pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                               kTile, 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
-        while (k + 3 < my_count) {   // two steps a trip: the two tiles' scores swap registers without copies
+        while (k < pairs_end) {   // two steps a trip: the two tiles' scores swap registers without copies
             main_step();
             main_step();
         }
-        for (; k + 1 < my_count; ++k)   // one or two: tile B may be the pool's last
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                             rest(k + 1), 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
-        const float down = k > 0 && k < lead ? kRebaseDown : rest(k) < kTile ? 0.0f : kNoRebase;
+        for (; k + 1 < my_count; ++k)   // tile B may be the pool's last
+            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+                                                                            rest(k + 1), k > 0 && k >= setting ? kRebaseDown : kNoRebase,
+                                                                            qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+        const float down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0.0f : kNoRebase;
         pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, lane, qb, O, Lsum,
                                                                            m_ref, mneg, lc);
     }

@@ -76,6 +76,23 @@ def test_waves_with_rows_of_their_own(d, heads, T, agents, q, group, tails, code
     case.attend_check(Q, **kw)
 
 
+@pytest.mark.parametrize("growing", [True, False])
+@pytest.mark.parametrize("tiles", [2, 3, 4, 5, 6, 7])
+def test_references_from_the_last_tiles(tiles, growing):
+    """A wave's first tile and its last three set references, in waves of up to seven tiles, over keys that grow (references
+    move up) and shrink (they move down, or lie too far below)."""
+    rng = np.random.default_rng(tiles)
+    heads, agents, q, group, d, T = 40, 33, 4, 4, 64, 32 * tiles - (tiles % 3)
+    half = lambda *s: rng.standard_normal(s).astype(np.float16)
+    size = np.linspace(0.1, 6.0, T)
+    K = half(1, heads, T, d) * (size if growing else size[::-1])[None, None, :, None].astype(np.float16)
+    case = Case(W.PoolConfig(0, "references", 1, heads, heads * group, d, T, agents, q), K, half(1, heads, T, d))
+    Q = half(1, agents, q, heads * group, d)
+    choice = case.pool.attend_plan(_pu().dev(Q))
+    assert choice.own_rows == 1 and choice.references == 4
+    case.attend_check(Q)
+
+
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("codec", [dict(int8_values=True), dict(value_bits=2), dict(value_bits=2, scaled_values=True), dict(value_bits=4),
                                    dict(value_bits=4, scaled_values=True), dict(value_bits=4, key_per_tensor=True)])
