@@ -100,6 +100,18 @@ def attend_back_to_back(pk, pools, Q, out, ws, tails, kprec, n=None):
     return call, kern
 
 
+def attend_kernel_name(pk, pool, Q, vc, kc, **kw):
+    """The pool kernel that attend(Q, **kw) launches, with its template arguments."""
+    c = pool.attend_plan(Q, **kw)
+    if c.kernel == pk.KERNEL_VECTOR:
+        return "attend_vector_kernel<%d,%d,%d>" % (pool.head_dim, vc, kc)
+    fp16_keys = "true" if kw.get("key_precision") == pk.KEY_PRECISION_FP16 and vc == kc == 0 and pool.head_dim != 256 else "false"
+    if c.tails_in_pool_launch:
+        return "attend_mfma_tails_kernel<%d,%d,%d,%s>" % (pool.head_dim, vc, kc, fp16_keys)
+    return "attend_mfma_kernel<%d,%d,%d,%d,%s,%s>" % (pool.head_dim, c.block_rows // 32, vc, kc, fp16_keys,
+                                                      "true" if c.own_rows else "false")
+
+
 def other_config(pk, W, n, kprec):
     """Attention on another of the paper-shaped configurations, back to back over two or three rotated pools.
     The tensors are drawn on the GPU (seeded torch generator) with the recipe of workloads.py: throughput does
@@ -136,11 +148,10 @@ def other_config(pk, W, n, kprec):
     tail_bytes = cfg.agents * tail_len * units * 4 * d
     nbytes = packed + Q.numel() * 2 + out.numel() * 4 + tail_bytes
     R = cfg.rows_per_kv_head
-    nt = 1 if R <= 32 else 2
     t = call if tails is not None else kern                 # with tails a call is two kernels: stream-level time
     res = {"workload": cfg.name, "rows_per_kv_head": R, "tokens": T, "pool_bytes": packed, "tail_len": tail_len,
            "tail_bytes": tail_bytes, "algorithmic_bytes": nbytes, "pool_copies_rotated": copies,
-           "kernel": "attend_mfma_kernel<%d,%d,0,0>" % (d, nt), "kernel_ms": kern * 1e3, "call_ms": call * 1e3,
+           "kernel": attend_kernel_name(pk, pools[0], Q, 0, 0, tails=tails, key_precision=kprec), "kernel_ms": kern * 1e3, "call_ms": call * 1e3,
            "timed": "pool_attend back to back; " + ("call (tail kernel + pool kernel, stream events)"
                                                     if tails is not None else "the pool kernel's own events"),
            "GB_per_s": nbytes / t / 1e9, "frac_of_hbm_peak": nbytes / t / 1e9 / HBM_PEAK_GBPS}
@@ -203,7 +214,7 @@ def main():
         ap.error("--phases takes each of e, d, a at most once")
     args.extras = not args.no_extras and len(args.phases) == 3 and not args.per_layer
     if args.gpus != 1:
-        print("bench.py: this build runs on exactly one GPU (--gpus 1); the pool path shards by layer / KV head "
+        print("bench.py: runs on exactly one GPU (--gpus 1); the pool path shards by layer / KV head "
               "with no exchange between GPUs", file=sys.stderr)
         sys.exit(2)
 
@@ -398,9 +409,10 @@ def main():
            "stream), median over the timed steps; traffic = the stored rocprofv3 FETCH_SIZE + WRITE_SIZE figure of "
            "profiles/ (copy-scaled), not measured in this run")
     vc = codec                                                          # the kernels' value-codec template argument
-    nt = 1 if (cfg.rows_per_kv_head <= 32 or d == 256) else 2
     kc = 1 if args.key_codec == "tensor" else 0
-    attend_roof = roof(att_gbps, "attend_mfma_kernel<%d,%d,%d,%d,%s> (pool_attend)" % (d, nt, vc, kc, "true" if args.key_precision == "fp16" else "false") + how +
+    name = attend_kernel_name(pk, pools[0], Ql[0] if args.per_layer else Q, vc, kc, tails=tails, key_precision=kprec,
+                              **(dict(layer_begin=0, layer_end=1) if args.per_layer else {}))
+    attend_roof = roof(att_gbps, name + " (pool_attend)" + how +
                        "; achieved = algorithmic bytes (packed pool + Q + out) / duration")
     traffic_file = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles",
                                 "attend_hbm_traffic_%s.txt" % cfg.name)
@@ -438,9 +450,8 @@ def main():
         "attend_zero_data_back_to_back_ms": k_att_zero and k_att_zero * 1e3,
         "attend_zero_data_frac_of_hbm_peak": k_att_zero and att_bytes / k_att_zero / 1e9 / HBM_PEAK_GBPS,
         "attend_zero_data_note": "the same back-to-back launches with K = V = Q = 0 (same kernel, same bytes): the "
-                                 "duration of the instruction stream at the full shader clock; with random data the "
-                                 "power management lowers the clock (2.4 -> about 1.4 GHz), which is the gap to the "
-                                 "figure above",
+                                 "duration of the instruction stream near the full shader clock; with random data the "
+                                 "power management lowers the clock, which is the gap to the figure above",
         "other_configs": other,
         "device_copy_GB_per_s": t_copy and 2 * K.numel() * 2 / t_copy / 1e9,
         "append_64_tokens_per_s": append_rate,

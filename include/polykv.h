@@ -207,7 +207,8 @@ typedef struct {
     int key_precision; /* POLYKV_KEY_PRECISION_EXACT (0, the default): scores over K = code * s exactly.
                           POLYKV_KEY_PRECISION_FP16: scores over fp16(code * s), the dequantized key rounded once to
                           the 16-bit type of the dense cache -- what the paper's read path attends over after its cast
-                          to the model dtype (section "DynamicCache Injection"); saves a third of the score products.
+                          to the model dtype (section "DynamicCache Injection").  As many score products as exact
+                          keys, and about the same time.
                           Honoured by the matrix-core kernel for pools with q8_0 block keys and the paper's value
                           codec at head_dim 64 / 128; every other case is computed with exact keys. */
 } polykv_attend_params;
@@ -258,7 +259,8 @@ int polykv_codebook_bits(int bits, float* centroids, float* thresholds);
 /* Measurement hook (for benchmarks and profilers; not an operation of the method).  Arms the calling
  * thread: the NEXT pool_encode, pool_decode or pool_attend call of this thread that launches has the HIP runtime
  * record `start_event` when its main kernel (the encode kernel, the decode kernel, the pool attention
- * kernel -- not the small tail / merge kernels) begins to execute and `stop_event` when it has finished,
+ * kernel -- not the tail and merge kernels; where polykv_attend_choice says tails_in_pool_launch, the private tails are
+ * part of the pool kernel's launch and of the time) begins to execute and `stop_event` when it has finished,
  * on the stream the kernel is launched on; the hook then disarms itself.  Both are hipEvent_t handles
  * created (with timing enabled) and owned by the caller; either may be NULL.  hipEventElapsedTime(start,
  * stop), after the stream has been synchronized, is then the kernel's own duration, without the launch

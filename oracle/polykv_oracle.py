@@ -447,7 +447,7 @@ def keys_as_fp16(K_hat):
     """The decoded keys as the paper's read path holds them: section "DynamicCache Injection" casts the
     decompressed tensors to the model's 16-bit dtype before they enter an agent's cache, so attention there runs
     over K rounded once (to nearest, ties to even) to that type.  Reading taken for the optional reduced key
-    precision of the attention call: fp16, the 16-bit type of this build's dense tensors.  Returns float64."""
+    precision of the attention call: fp16, the library's own 16-bit type of dense tensors.  Returns float64."""
     return np.asarray(K_hat, dtype=np.float64).astype(np.float16).astype(np.float64)
 
 

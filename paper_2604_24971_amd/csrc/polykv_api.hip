@@ -206,7 +206,9 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             const double rows = (double)units * p.R;
             const uint32_t tiles = (uint32_t)cap_tiles, ways = (uint32_t)waves;
             auto per_wave = [&](uint32_t n) { return ((tiles + n - 1) / n + ways - 1) / ways; };
-            // the merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us
+            // The merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us.  (Of the 64-row
+            // form, one workgroup to a CU.  At head_dim 64 with up to 32 rows three share a CU and a step is shorter: rounds
+            // are overcounted there and the merge undercounted, which errs towards few splits.)
             const double merge = 3.5, partials = rows * p.D * (8 / 4e12 / 1.2e-6);
             long best = 1;
             double least = (double)((groups + 255) / 256) * (per_wave(1) + 5);

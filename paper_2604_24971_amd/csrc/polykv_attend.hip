@@ -29,8 +29,6 @@ __device__ __forceinline__ float wave_sum(float x) {
 
 constexpr int kRB = 4;  // query rows per pass of the vector kernels
 
-template <int N> struct __attribute__((aligned(2 * N))) HalfVecN { __half h[N]; };
-
 // ---------------------------------------------------------------------------- vector kernel ---
 // One wave = one token-range split of one (layer, kv head, block of kRB rows).  Per 64 tokens:
 //   scores  lane = token: the lane dequantizes its key (code * block scale, exact in fp32) and dots

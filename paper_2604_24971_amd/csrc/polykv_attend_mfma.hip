@@ -21,10 +21,12 @@
 // Why 32x32x16: a wave that interleaves MFMAs with vector work pays 5 to 8 issue cycles per MFMA whatever its shape and
 // 4 to 5 per vector instruction, so the larger tile halves the MFMA share of the issue time for the same arithmetic.
 //
-// What bounds it: power.  With random operands on the matrix cores the chip holds 1.6-1.9 of its 2.4 GHz, and the time
-// follows the energy of the instruction stream (a fit over variants of this kernel: an MFMA costs about as much as eight
-// vector instructions) more than its length.  Scaling the block products instead of the keys (the exact dequantized key
-// has 18 bits and took two fp16 terms, hence two products) removes a third of the MFMAs for as many vector instructions:
+// What bounds it: the issue of vector instructions by a lone wave per SIMD, at a clock that follows the operands.  15 agents
+// over 4,096 tokens take 95,000 cycles a wave (14,800 vector and 1,024 matrix instructions; the matrix pipe is busy for
+// 32,800, 17,700 are waits): 45.8 us at 2.07 GHz on one machine, 50.8 us at 1.87 GHz on another, 41.8 us at 2.27 GHz over
+// zeros.  Scaling the block products instead of the keys (the exact dequantized key has 18 bits and took two fp16 terms,
+// hence two products) removed a third of the MFMAs for as many vector instructions.  The cycles stayed what they were
+// (95,400), the clock rose, and:
 //   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
 //   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below;
 //                                                                      1,100 with rows of their own for the waves)
@@ -93,7 +95,7 @@ __device__ __forceinline__ float xor32_sum(float x) {
 // key scales of one token, its value codes.  Every load is one contiguous run across the wave (the record is stored in
 // exactly this order).  A piece is requested again, for the tile a step later, as soon as it has been used, so that one
 // set of registers is enough and every load has a whole step to arrive.  (Records staged in LDS with direct loads,
-// three tiles ahead, cost 5 % more time on the Llama-shaped pool: the loop is bound by power, not by latency.)
+// three tiles ahead, cost 5 % more time on the Llama-shaped pool: the loop does not wait for its loads.)
 //
 // The records of a KV head are read through a buffer resource: every load is "resource + wave-uniform byte
 // offset of the tile (a scalar register) + the lane's constant offset (a vector register that never changes)
@@ -355,7 +357,7 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 //
 // A reference moves down by kRebaseDown at most: a token further below the largest so far hardly shows in the result,
 // and the accumulators stay in range (16 references, 2^64).
-constexpr float kRebaseDown = 4.0f, kNoRebase = -INFINITY;
+constexpr int kRebaseDown = 4, kNoRebase = -1;
 
 template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     using TR = TileReader<D, VC, KC, K16>;
@@ -373,7 +375,7 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
 
 template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
 __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
-                                              uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, float down, float qscale,
+                                              uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, int down, float qscale,
                                               int lane, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
                                               float (&Lsum)[NT], float* m_ref, float (&mneg)[NT], const LoopConsts& lc) {
     using TR = TileReader<D, VC, KC, K16>;
@@ -435,10 +437,10 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     // done with the rows that outgrew their references, further down.
     constexpr bool EARLY = REBASE && (FOLD || !HAS_B);
     if constexpr (EARLY) {
-        if (down != kNoRebase) {
+        if (__builtin_expect(down != kNoRebase, 0)) {   // (out of the way of the steps without)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const float m_old = m_ref[32 * nt], m = row_max(nt, m_old), m_new = m >= m_old - down ? m : m_old;
+                const float m_old = m_ref[32 * nt], m = row_max(nt, m_old), m_new = m >= m_old - (float)down ? m : m_old;
                 if (__any(m_new != m_old)) move_reference(nt, m_old, m_new, false);
             }
         }
@@ -540,7 +542,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             for (int nt = 0; nt < NT; ++nt) {
                 const bool row_raise = !(xor32_max(lt[nt] * gmax) <= lc.raise_sum);   // (+inf stays +inf through the max)
                 const float m_old = m_ref[32 * nt];
-                const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : set_here && m >= m_old - down ? m : m_old;
+                const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : set_here && m >= m_old - (float)down ? m : m_old;
                 if (!__any(m_new != m_old)) continue;   // no row of this row tile moves: it keeps what it has
                 move_reference(nt, m_old, m_new, HAS_B);
                 lt[nt] = 0.0f;
@@ -552,6 +554,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         for (int nt = 0; nt < NT; ++nt) Lsum[nt] += lt[nt];
 
         // ---- P.V.  Group G's operand is formed a little ahead of its first product; NVA operands take turns.
+        // (Three where the registers hold them: 15 agents with tails over 7,194 tokens 117.2 us with two, 113.2 with three.)
         constexpr int NVA = FOLD && D == 128 && !VS ? 3 : 2;
         H8 va[NVA];
         auto vhalf = [&](int i) {   // the i-th half operand
@@ -758,7 +761,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         // prologue: scores of tile 0; requests the values of tile 0 and the keys of tile 1
 #pragma unroll
         for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
-        pipeline_step<D, NT, VC, KC, K16, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), 0.0f,
+        pipeline_step<D, NT, VC, KC, K16, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), kNoRebase,
                                                                    qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
@@ -779,7 +782,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         const int pairs_end = min(my_count - 3, setting - 1);
         auto main_step = [&]() {
             pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                              kTile, 0.0f, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+                                                                              kTile, kNoRebase, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
         while (k < pairs_end) {   // two steps a trip: the two tiles' scores swap registers without copies
@@ -790,7 +793,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                             rest(k + 1), k > 0 && k >= setting ? kRebaseDown : kNoRebase,
                                                                             qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
-        const float down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0.0f : kNoRebase;
+        const int down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0 : kNoRebase;
         pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, lane, qb, O, Lsum,
                                                                            m_ref, mneg, lc);
     }

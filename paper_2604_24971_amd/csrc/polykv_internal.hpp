@@ -32,7 +32,8 @@ void set_error(const char* fmt, ...);
 
 // Division by a number the host knows, exact for every 32-bit numerator: the quotient by the multiplier is right or one
 // too small.  (The compiler's general division is 25 to 40 instructions, and a workgroup of the attention kernel had eight
-// of them in front of its first loads: 15 agents over 1,837 tokens 26.6 us a call, 26.4 us without.)
+// of them in front of its first loads: 15 agents over 1,837 tokens 26.6 us a call with them and 26.4 without, about as much as
+// two runs differ.)
 struct FastDiv {
     uint32_t d, m;
     static FastDiv by(int divisor) { return FastDiv{(uint32_t)divisor, 0xFFFFFFFFu / (uint32_t)divisor}; }
