@@ -8,8 +8,9 @@
 //   pipeline two tiles are in flight per wave: the scores of the next tile are computed on the matrix
 //            cores while the vector ALUs run the softmax and value dequantization of the current one.
 //   scores   S^T[t, r] = sum_j s[t,j] * (sum_{k in block j} code[t,k] * q[r,k]): the keys enter the matrix cores as
-//            their integer codes, exact in fp16, and the q8_0 block scales are applied in fp32 to the products of a
-//            block (two K=16 MFMAs) as they are summed.
+//            their codes as stored, exact in fp16, and the q8_0 block scales are applied in fp32 to the products of a
+//            block (two K=16 MFMAs) as they are summed, on top of one product that holds the codes' offset and the
+//            rows' softmax references (Corr).
 //   softmax  online, per row, in base-2 units; a row's reference only moves when the row's probabilities
 //            of one tile sum to more than 2^15 in a lane, so the accumulator rescale is rare, p fits
 //            fp16, and the common case takes no maximum over the scores at all.
@@ -21,17 +22,19 @@
 // Why 32x32x16: a wave that interleaves MFMAs with vector work pays 5 to 8 issue cycles per MFMA whatever its shape and
 // 4 to 5 per vector instruction, so the larger tile halves the MFMA share of the issue time for the same arithmetic.
 //
-// What bounds it: the issue of vector instructions by a lone wave per SIMD, at a clock that follows the operands.  15 agents
-// over 4,096 tokens take 95,000 cycles a wave (14,800 vector and 1,024 matrix instructions; the matrix pipe is busy for
-// 32,800, 17,700 are waits): 45.8 us at 2.07 GHz on one machine, 50.8 us at 1.87 GHz on another, 41.8 us at 2.27 GHz over
-// zeros.  Scaling the block products instead of the keys (the exact dequantized key has 18 bits and took two fp16 terms,
-// hence two products) removed a third of the MFMAs for as many vector instructions.  The cycles stayed what they were
-// (95,400), the clock rose, and:
-//   15 agents x 4,096 tokens, 32 layers x 8 KV heads x 128 (R = 60):   61.4 -> 55 us per call
-//   64 agents x 4 queries, 7,194 tokens (R = 1,024):                   1,624 -> 1,470 us (1,165 in die order, below;
-//                                                                      1,100 with rows of their own for the waves)
-// and the registers it frees hold 64 rows per workgroup for every value codec at head_dim 64 and 128:
-//   int8 values, 15 agents x 2,500 tokens:                             64 -> 42.5 us
+// What bounds it: with 64 rows a workgroup, the power that random operands take.  15 agents over 4,096 tokens are 84,000
+// cycles a wave (70,000 of them the loop), 45.8 us at 1.9 GHz where the pool comes out of the last-level cache, 52 us at 1.6
+// to 1.75 GHz where it comes from memory, whatever the loop's number of cycles: deeper requests (two sets of tile data, every
+// piece asked for two steps ahead) and a loop rearranged to 7 % fewer cycles both changed nothing or lost 1 to 2 %.  Leaving
+// out 8 of the 32 matrix instructions of a step is worth 10 % of the time of 1,024 rows, the fold's 128 vector instructions
+// 12 %.  With 32 rows, HBM (5.8 to 6.9 TB/s in the loop) and the fixed parts around it, 8 to 12 us of a call.
+// What the forms of the scores took, us a call (15 agents x 4,096 tokens at R = 60; 64 agents x 4 queries x 7,194 tokens):
+//   the exact dequantized key, 18 bits, as two fp16 terms and two products     61.4    1,624
+//   codes less their offset (2 packed subtractions per 4 codes), fold          55      1,470 (1,165 in die order, 1,097 with own rows)
+//   codes as stored and the correction (Corr), one box                         53.4 -> 52.4    1,088 -> 1,067
+// The last also took SmolLM2-shaped calls of 5 rows from 28.8 to 27.7 us (24.3 instead of 27.2 out of the cache; half of that
+// by keeping accumulators and queries in vector registers, see parks), tails over 7,194 tokens from 113.9 to 112.0, 32 one-layer
+// calls from 442 to 435.  A step's vector instructions: 400 -> 340 (two row tiles, head_dim 128), 298 -> 139 (one, 64).
 //
 // The accumulation stays in the rotated value domain; the inverse Walsh-Hadamard rotation is done
 // once per output row (sections "Compression Scheme" / "TurboQuant", dequantization), in this kernel
@@ -68,16 +71,27 @@ __device__ __forceinline__ float16v mfma32(const half8& a, const half8& b, const
 // this kernel, which vector instructions cannot read): C = 0, and C = D.  The compiler does not know what is inside, so
 // the call sites keep the distances the instruction asks for: two instructions between the vector write of an operand
 // and the product that reads it, and at least twelve between the product and a vector read of its result.
-// WAIT: with two wait states of its own in front, where the query operand may have been moved just before.
-template <bool WAIT> __device__ __forceinline__ void mfma32_v0(float16v& d, const half8& a, const half8& b) {
-    if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
-    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+// WAIT: with two wait states of its own in front, where an operand may have been moved just before.
+// BA: the second operand is in accumulation registers.
+template <bool WAIT, bool BA> __device__ __forceinline__ void mfma32_v0(float16v& d, const half8& a, const half8& b) {
+    if constexpr (WAIT && BA) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+    else if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+    else if constexpr (BA) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
 }
-template <bool WAIT> __device__ __forceinline__ void mfma32_v(float16v& d, const half8& a, const half8& b) {
-    if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
-    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+template <bool WAIT, bool BA> __device__ __forceinline__ void mfma32_v(float16v& d, const half8& a, const half8& b) {
+    if constexpr (WAIT && BA) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+    else if constexpr (WAIT) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+    else if constexpr (BA) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
 
+// The lane's number, read again where it is needed: across the main loop it would hold a register.
+__device__ __forceinline__ int lane_again() {
+    int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 // lane <-> lane ^ 32 combinations
 __device__ __forceinline__ float xor32_max(float x) {
     const uint32_t xi = __float_as_uint(x);
@@ -113,7 +127,7 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
 }
 
 // How the scores over q8_0 block keys are formed.
-//   FOLD (exact keys): the keys enter the matrix cores as their integer codes, every 32-element block has a product
+//   FOLD (exact keys): the keys enter the matrix cores as their codes, every 32-element block has a product
 //     of its own, and the block scale (times softmax scale * log2 e) is applied to the block's products in fp32 as
 //     they are summed.  A score tile has its tokens in the accumulator's registers, the same 16 tokens for every
 //     lane of a half wave, so a scale is handed out by DPP: position i of each 16-lane row holds the scale of the
@@ -128,7 +142,27 @@ struct Scores16 {
     __device__ __forceinline__ float& operator[](int i) { return v[i]; }
     __device__ __forceinline__ float operator[](int i) const { return v[i]; }
 };
-template <bool FOLD> using ScoreTile = std::conditional_t<FOLD, Scores16, float16v>;
+template <bool FOLD> using ScoreTile = float16v;
+
+// FOLD: the codes enter the products as they are stored, offset by 128, as fp16 subnormals: byte b becomes b * 2^-24, one
+// byte permute per two codes and nothing else (the matrix cores take subnormals at full precision).  What that and the
+// rows' softmax references ask for,
+//   C[t, r] = sum_j s[t, j] * W[r, j] + mu[r],   W[r, j] = -128 * qscale * sum of q[r] over block j,   mu = -reference,
+// is a product of its own per score tile, with the scales as they are (fp16) against W and mu in three fp16 terms each
+// (33 bits): it is what the block products are added to, in the place of 16 moves of mu, and the subtraction from every
+// key code (32 packed instructions per tile) is gone.  What is added and taken away again is at most 128 times the sum of a
+// block's query magnitudes, 2^-24 of it the error: errors against float64 are the same as without (1.577 and 1.576e-4 at 15
+// agents, 1.303 and 1.302e-4 at 512 rows over 300 tokens).  K slots of a row: term * NB + j, then the three terms of mu.
+// A W or mu beyond kCorrMax has zeros there and is added by hand (add_wide).
+template <int D> struct Corr {
+    static constexpr int NB = D / 32;
+    static constexpr int ops = NB == 8 ? 2 : 1;                       // products (K = 16 each)
+    static constexpr int mu_slot = NB == 2 ? 8 : NB == 4 ? 12 : 24;   // (in lanes 32..63, a whole dword pair)
+    static constexpr int mu_op = mu_slot / 16, mu_word = mu_slot % 8 / 2;
+    static constexpr int row_halves = 16 * ops;
+    static constexpr int words = NB / 2;                              // dwords of scales per token
+};
+constexpr float kCorrMax = 60000.0f, kCodeScale = 16777216.0f;        // 2^24
 
 // The records of a KV head as a lane reads them; `tile` is a record's byte offset.
 template <int D, int VC, int KC, bool K16> struct TileReader {
@@ -140,7 +174,7 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
     TileRsrc rs;
     // the lane's offsets: key codes, key scales, value codes, value scales (opaque, so that the compiler adds what is
     // constant in the instruction instead of keeping a register per load)
-    uint32_t k, s, v, g;
+    uint32_t k, s, ts, v, g;
 
     __device__ __forceinline__ TileReader(TileRsrc r, int lane) : rs(r) {
         k = (uint32_t)lane * 16;
@@ -148,10 +182,12 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
         // whose key codes the lane holds
         const int t = fold_scales(KC, K16) ? 8 * ((lane >> 2) & 3) + 4 * (lane >> 5) + (lane & 3) : lane & 31;
         s = (uint32_t)t * (D / 32) * 2;
+        ts = (uint32_t)(lane & 31) * (D / 32) * 2;
         v = (uint32_t)lane * (VB == 8 ? 16 : VB == 3 ? 12 : VB == 4 ? D / 4 : D / 8);
         g = (uint32_t)(lane >> 5) * 8;
         asm volatile("" : "+v"(k), "+v"(v));
         if (KC == 0) asm volatile("" : "+v"(s));
+        if (fold_scales(KC, K16)) asm volatile("" : "+v"(ts));
         if (vc_has_scale(VC)) asm volatile("" : "+v"(g));
     }
     // key codes of token lane % 32, block j: elements 8h..8h+7 (x, y) and 16+8h.. (z, w), h = lane / 32
@@ -169,6 +205,18 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
                 const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::kscales_off + s + 4 * x, tile, 0);
                 sc[x] = two[0], sc[x + 1] = two[1];
             }
+        }
+    }
+    // (FOLD) all key scales of token lane % 32, two per dword
+    __device__ __forceinline__ void token_scales(uint32_t tile, uint32_t (&sc)[D / 64]) const {
+        if constexpr (D == 64) {
+            sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, LY::kscales_off + ts, tile, 0);
+        } else if constexpr (D == 128) {
+            const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::kscales_off + ts, tile, 0);
+            sc[0] = two[0], sc[1] = two[1];
+        } else {
+            const uint4v four = __builtin_amdgcn_raw_buffer_load_b128(rs, LY::kscales_off + ts, tile, 0);
+            sc[0] = four.x, sc[1] = four.y, sc[2] = four.z, sc[3] = four.w;
         }
     }
     // value codes of coordinate groups 4q .. 4q + 3
@@ -205,10 +253,19 @@ __device__ __forceinline__ _Float16 half_of(uint32_t w, int odd) {   // the lowe
     return __builtin_bit_cast(_Float16, (uint16_t)(odd ? w >> 16 : w));
 }
 
-// Half block s of a lane's 16 key codes -> the A operand of one score product: the codes as exact fp16 integers or, for
-// keys rounded to fp16 (K16), code * scale; sc2: the dword that holds the block's scale, odd: in its upper half.
-template <bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& raw, int s, uint32_t sc2, int odd) {
+// Half block s of a lane's 16 key codes -> the A operand of one score product: the codes as fp16 subnormals (FOLD), as exact
+// fp16 integers or, for keys rounded to fp16 (K16), code * scale; sc2: the dword that holds the block's scale, odd: in its
+// upper half.
+template <bool FOLD, bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& raw, int s, uint32_t sc2, int odd) {
     H8 a;
+    if constexpr (FOLD) {
+        const uint32_t lo = s == 0 ? raw.x : raw.z, hi = s == 0 ? raw.y : raw.w;
+        a.u[0] = __builtin_amdgcn_perm(0u, lo, 0x0c010c00u);
+        a.u[1] = __builtin_amdgcn_perm(0u, lo, 0x0c030c02u);
+        a.u[2] = __builtin_amdgcn_perm(0u, hi, 0x0c010c00u);
+        a.u[3] = __builtin_amdgcn_perm(0u, hi, 0x0c030c02u);
+        return a.h;
+    }
     codes4_to_half(s == 0 ? raw.x : raw.z, a.u[0], a.u[1]);
     codes4_to_half(s == 0 ? raw.y : raw.w, a.u[2], a.u[3]);
     a.h = a.h - (_Float16)1152.0f;
@@ -216,28 +273,17 @@ template <bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& r
     return a.h * (half8)half_of(sc2, odd);
 }
 
-// S[i] += scale of register i's token * P[i], i = 8 X .. 8 X + 7 (see fold_scales)
-#define POLYKV_FOLD8(X, R0, R1, R2, R3, R4, R5, R6, R7)                                                              \
-    asm volatile("v_fmac_f32_dpp %0, %16, %8 row_newbcast:" R0 " row_mask:0xf bank_mask:0xf\n\t"                    \
-                 "v_fmac_f32_dpp %1, %16, %9 row_newbcast:" R1 " row_mask:0xf bank_mask:0xf\n\t"                    \
-                 "v_fmac_f32_dpp %2, %16, %10 row_newbcast:" R2 " row_mask:0xf bank_mask:0xf\n\t"                   \
-                 "v_fmac_f32_dpp %3, %16, %11 row_newbcast:" R3 " row_mask:0xf bank_mask:0xf\n\t"                   \
-                 "v_fmac_f32_dpp %4, %16, %12 row_newbcast:" R4 " row_mask:0xf bank_mask:0xf\n\t"                   \
-                 "v_fmac_f32_dpp %5, %16, %13 row_newbcast:" R5 " row_mask:0xf bank_mask:0xf\n\t"                   \
-                 "v_fmac_f32_dpp %6, %16, %14 row_newbcast:" R6 " row_mask:0xf bank_mask:0xf\n\t"                   \
-                 "v_fmac_f32_dpp %7, %16, %15 row_newbcast:" R7 " row_mask:0xf bank_mask:0xf"                       \
-                 : "+v"(S[X]), "+v"(S[X + 1]), "+v"(S[X + 2]), "+v"(S[X + 3]), "+v"(S[X + 4]), "+v"(S[X + 5]),        \
-                   "+v"(S[X + 6]), "+v"(S[X + 7])                                                                    \
-                 : "v"(P[X]), "v"(P[X + 1]), "v"(P[X + 2]), "v"(P[X + 3]), "v"(P[X + 4]), "v"(P[X + 5]),              \
-                   "v"(P[X + 6]), "v"(P[X + 7]), "v"(scale))
-template <typename SV> __device__ __forceinline__ void fold16(SV& S, const float16v& P, float scale) {
-    asm volatile("s_nop 1" : : "v"(scale));   // a DPP source must not have been written by the two instructions before
-    POLYKV_FOLD8(0, "0", "1", "2", "3", "4", "5", "6", "7");
-    POLYKV_FOLD8(8, "8", "9", "10", "11", "12", "13", "14", "15");
+// S[i] += scale of register i's token * P[i] (see fold_scales).  (A statement per element: with several in one the register
+// allocator copies the tile, a matrix instruction's result, out of its 16 consecutive registers.)
+template <int I> __device__ __forceinline__ float fold1(float s, float product, float scale) {
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(s) : "v"(scale), "v"(product), "n"(I));
+    return s;
 }
-#undef POLYKV_FOLD8
-template <typename SV> __device__ __forceinline__ void fold_block(SV& S, const float16v& P, uint32_t sc2, int odd, float qscale) {
-    fold16(S, P, (float)half_of(sc2, odd) * qscale);
+template <typename PV> __device__ __forceinline__ void fold16(float16v& S, const PV& P, float scale) {
+    static_for<16>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        S[i] = fold1<i>(S[i], P[i], scale);
+    });
 }
 
 // Constants the main loop keeps in scalar registers.  As 32-bit literals they would double the size of every
@@ -328,6 +374,7 @@ __device__ __forceinline__ void exp4(const SV& S, int c, float qscale, float mne
 //   cur        what a step is handed by the one before: the scores of tile A and its values, tile B's first key operands,
 //              its key codes and scales; on exit the same for the next step, requested from nextV (tile B), nextK (the
 //              tile after B) and, for block 0, whose operands are formed at the end of the step before, nextK0
+//   upper      the lane is one of 32 .. 63
 //   masked     (LAST only: tile B may be the pool's last) tokens of tile B from `masked` on lie past the end of the pool
 //   down       (REBASE only) rows whose maximum of tile A lies less than `down` below their reference take it for their reference
 //
@@ -365,22 +412,65 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     half8 kop[2];                                  // tile B: key operands of block 0, both halves,
     uint4v k[D / 32];                              //   key codes (block 0: of the tile after B),
     uint32_t sc[TR::NS];                           //   key scales
+    uint32_t tsc[fold_scales(KC, K16) ? D / 64 : 1];   //   and the same in the order of the correction's operand
     uint32_t v[TR::NQ][TR::CW];                    // tile A: value codes
     uint32_t g[vc_has_scale(VC) ? 8 : 1];          //   and value scales
     __device__ __forceinline__ void first_operands() {
-        kop[0] = key_operand<K16>(k[0], 0, sc[0], 0);
-        kop[1] = key_operand<K16>(k[0], 1, sc[0], 0);
+        kop[0] = key_operand<fold_scales(KC, K16), K16>(k[0], 0, sc[0], 0);
+        kop[1] = key_operand<fold_scales(KC, K16), K16>(k[0], 1, sc[0], 0);
     }
+};
+
+// Waves per SIMD the kernel is compiled for: one where it needs all 512 registers; three for 32-row blocks at
+// head_dim 64 (the small-row shape of the SmolLM2-sized pool: 768 workgroups, all resident at once on 256 CUs,
+// so that one workgroup's query fetch, pipeline ramp and merge overlap the others' main loops).
+constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && NT == 1 && vc_bits(VC) == 3 && !vc_has_scale(VC)) ? 3 : 1; }
+// Where three waves share a SIMD, queries and accumulators are in vector registers like everything else: with any
+// accumulation registers in use the compiler has half of a wave's 168 for either kind, and moved 80 values a step between them.
+constexpr bool parks(int D, int NT, int VC) { return kernel_waves_per_simd(D, NT, VC) != 3; }
+
+// The correction's query operands (FOLD) and where the rows' W beyond kCorrMax are; else empty.
+template <int D, int NT> struct CorrState {
+    half8 b[NT][Corr<D>::ops];
+    uint64_t wide;          // the lanes of rows with a W or a reference beyond kCorrMax: add_wide has to be called if there are any
+    const float* w_s;       // the wave's rows' W where beyond kCorrMax, else 0: [row][block]
+    // the reference of the lane's row in row tile nt
+    __device__ __forceinline__ void set_reference(int nt, float m, bool upper) {
+        float mu = -m;
+        const bool beyond = !(fabsf(mu) <= kCorrMax);
+        wide |= __ballot(beyond);
+        if (beyond) mu = 0.0f;
+        union {
+            _Float16 h[4];
+            uint32_t u[2];
+        } t;
+        t.h[0] = (_Float16)mu;
+        mu -= (float)t.h[0];
+        t.h[1] = (_Float16)mu;
+        mu -= (float)t.h[1];
+        t.h[2] = (_Float16)mu;
+        t.h[3] = (_Float16)0.0f;
+        H8 x;
+        x.h = b[nt][Corr<D>::mu_op];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x.u[Corr<D>::mu_word + i] = upper ? t.u[i] : x.u[Corr<D>::mu_word + i];
+        b[nt][Corr<D>::mu_op] = x.h;
+    }
+};
+struct OneValue {   // (in the place of a tile of products)
+    float v;
+    __device__ __forceinline__ float operator[](int) const { return v; }
 };
 
 template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
 __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
                                               uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, int down, float qscale,
-                                              int lane, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
-                                              float (&Lsum)[NT], float* m_ref, float (&mneg)[NT], const LoopConsts& lc) {
+                                              bool upper, const half8 (&qb)[NT][D / 32][2], CorrState<D, NT>& corr,
+                                              float16v (&O)[D / 32][NT], float (&Lsum)[NT], float* m_ref, float (&mneg)[NT],
+                                              const LoopConsts& lc) {
     using TR = TileReader<D, VC, KC, K16>;
     constexpr int NB = D / 32, NG = D / 16, MG = D / 32;
-    constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC);
+    constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC), PARK = parks(D, NT, VC);
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
     auto& Sa = cur.S;
     ScoreTile<FOLD> Sb[NT];
@@ -400,7 +490,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     };
     uint32_t sc_next[TR::NS], g_next[VS ? 8 : 1];   // scales of the tiles a step later
     auto kdeq = [&](int k, half8& dst) {   // half block k's operand; after a block's second half its codes are reloaded
-        dst = key_operand<K16>(cur.k[k >> 1], k & 1, cur.sc[k >> 2], (k >> 1) & 1);
+        dst = key_operand<FOLD, K16>(cur.k[k >> 1], k & 1, cur.sc[k >> 2], (k >> 1) & 1);
     };
     auto scales_next = [&]() {
         tr.kscales(nextK, sc_next);
@@ -413,9 +503,10 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     };
     auto move_reference = [&](int nt, float m_old, float m_new, bool both) {
         const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f(m_old - m_new);
-        m_ref[32 * nt] = m_new;
-        mneg[nt] = -m_new;
+        m_ref[32 * nt + (lane_again() & 31)] = m_new;
+        if constexpr (!FOLD) mneg[nt] = -m_new;
         if constexpr (FOLD) {   // the exponents of the tiles in flight move along
+            corr.set_reference(nt, m_new, upper);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 Sa[nt][i] -= m_new - m_old;
@@ -425,8 +516,16 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         // The accumulators live in accumulation registers that vector instructions cannot read; an MFMA with zero
         // operands (D = 0*0 + C) carries them to vector registers and back, so the hot path never copies them.
         Lsum[nt] *= alpha;
+        if constexpr (!PARK) {
+            asm volatile("s_nop 15" : "+v"(O[0][nt]));   // the last products
+            fence();
+        }
 #pragma unroll
         for (int g = 0; g < MG; ++g) {
+            if constexpr (!PARK) {
+                O[g][nt] *= alpha;
+                continue;
+            }
             float16v y = mfma32(zero8, zero8, O[g][nt]);
             y *= alpha;
             O[g][nt] = mfma32(zero8, zero8, y);
@@ -440,16 +539,37 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         if (__builtin_expect(down != kNoRebase, 0)) {   // (out of the way of the steps without)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const float m_old = m_ref[32 * nt], m = row_max(nt, m_old), m_new = m >= m_old - (float)down ? m : m_old;
+                const float m_old = m_ref[32 * nt + (lane_again() & 31)], m = row_max(nt, m_old), m_new = m >= m_old - (float)down ? m : m_old;
                 if (__any(m_new != m_old)) move_reference(nt, m_old, m_new, false);
             }
         }
     }
 
+    using CR = Corr<D>;
+    H8 acorr[CR::ops];   // the correction's scale operands
+
     // block j's products with row tile nt (FOLD): two of them take turns, one is folded while the other is formed
     float16v P[FOLD ? 2 : 1];
     constexpr int NU = NB * NT;
-    auto fold = [&](int u) { fold_block(Sb[u % NT], P[u & (FOLD ? 1 : 0)], cur.sc[u / NT >> 1], u / NT & 1, qscale); };
+    // (A DPP source must not have been written by the two instructions before: a block's scale is formed a unit ahead.)
+    float fscale[2];
+    auto fold_scale = [&](int j) { fscale[j & 1] = (float)half_of(cur.sc[j >> 1], j & 1) * (qscale * kCodeScale); };
+    auto fold = [&](int u) { fold16(Sb[u % NT], P[u & (FOLD ? 1 : 0)], fscale[u / NT & 1]); };
+    auto add_wide = [&]() {   // (rare) of the rows that have them, what is too large for the correction's operands
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int n = lane_again() & 31, r = 32 * nt + n;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const float scale = (float)half_of(cur.sc[j >> 1], j & 1);
+                asm volatile("s_nop 1" : : "v"(scale));
+                fold16(Sb[nt], OneValue{corr.w_s[r * NB + j]}, scale);
+            }
+            const float m = m_ref[r], mu = fabsf(m) <= kCorrMax || m == -INFINITY ? 0.0f : -m;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) Sb[nt][i] += mu;
+        }
+    };
 
     if (HAS_B) {
         if constexpr (FOLD) {
@@ -460,22 +580,39 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 constexpr int j = u / NT, nt = u % NT;
                 const bool last_nt = nt == NT - 1 && j + 1 < NB;
                 fence();
-                if (u == 0) mfma32_v0<true>(P[u & 1], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
-                else mfma32_v0<!LOOP>(P[u & 1], cur.kop[0], qb[nt][j][0]);
+                if (j == 0) {   // what the block products are added to
+                    float16v& C = Sb[nt];
+                    if (nt == 0) {
+                        // A: the token's scales in every slot of W, ones in those of mu
+#pragma unroll
+                        for (int op = 0; op < CR::ops; ++op)
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) {
+                                const uint32_t w = cur.tsc[x % CR::words];
+                                acorr[op].u[x] = op == CR::mu_op && x >= CR::mu_word && x < CR::mu_word + 2 && upper ? 0x3c003c00u : w;
+                            }
+                        fence();
+                    }
+                    mfma32_v0<true, false>(C, acorr[0].h, corr.b[nt][0]);
+                    if constexpr (CR::ops == 2) mfma32_v<true, false>(C, acorr[CR::ops - 1].h, corr.b[nt][CR::ops - 1]);
+                    fence();
+                    if (nt == NT - 1) tr.token_scales(nextK, cur.tsc);
+                    if (HAS_A) exp_chunk(u);
+                    fence();
+                }
+                if (u == 0) mfma32_v0<true, PARK>(P[u & 1], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
+                else mfma32_v0<!LOOP, PARK>(P[u & 1], cur.kop[0], qb[nt][j][0]);
                 fence();
                 if (u == 0) scales_next();
-                if (j == 0) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) Sb[nt][i] = mneg[nt];
-                }
+                if (nt == 0) fold_scale(j);
                 if (last_nt) kdeq(2 * (j + 1), cur.kop[0]);
-                if (HAS_A) {
+                if (HAS_A) {   // (the first ones have had a chunk each with their tiles' corrections)
 #pragma unroll
-                    for (int c = u * NCH / NU; c < (u + 1) * NCH / NU; ++c) exp_chunk(c);
+                    for (int c = max(NT, u * NCH / NU); c < (u + 1) * NCH / NU; ++c) exp_chunk(c);
                 }
                 fence();
-                if (u == 0) mfma32_v<true>(P[u & 1], cur.kop[1], qb[nt][j][1]);
-                else mfma32_v<!LOOP>(P[u & 1], cur.kop[1], qb[nt][j][1]);
+                if (u == 0) mfma32_v<true, PARK>(P[u & 1], cur.kop[1], qb[nt][j][1]);
+                else mfma32_v<!LOOP, PARK>(P[u & 1], cur.kop[1], qb[nt][j][1]);
                 fence();
                 if (u > 0) {
                     if (!HAS_A) asm volatile("s_nop 15");   // (no probabilities in between)
@@ -501,9 +638,9 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     fence();
-                    if (k == 0) mfma32_v0<true>(Sb[nt], kop2[0], qb[nt][0][0]);
-                    else if (k == 1) mfma32_v<true>(Sb[nt], kop2[1], qb[nt][0][1]);
-                    else mfma32_v<!LOOP || NT == 1>(Sb[nt], kop2[k & 1], qb[nt][k >> 1][k & 1]);
+                    if (k == 0) mfma32_v0<true, PARK>(Sb[nt], kop2[0], qb[nt][0][0]);
+                    else if (k == 1) mfma32_v<true, PARK>(Sb[nt], kop2[1], qb[nt][0][1]);
+                    else mfma32_v<!LOOP || NT == 1, PARK>(Sb[nt], kop2[k & 1], qb[nt][k >> 1][k & 1]);
                     fence();
                     if (k == 0 && nt == 0) scales_next();
                     // the operand two half blocks on, once this one's last product has been issued
@@ -521,6 +658,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             });
             if (!HAS_A) asm volatile("s_nop 15");
         }
+        if (FOLD && !HAS_A && __builtin_expect(corr.wide != 0, 0)) add_wide();   // (else with the rows that move their reference)
     } else if (HAS_A) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) exp_chunk(c);
@@ -537,11 +675,12 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) raise |= !(lt[nt] * gmax <= lc.raise_sum);   // (inf and NaN say yes)
         const bool set_here = REBASE && !EARLY && down != kNoRebase;
-        if (__builtin_expect(__any(raise) || set_here, 0)) {
+        if (__builtin_expect((__ballot(raise) | (FOLD && HAS_B ? corr.wide : 0)) != 0 || set_here, 0)) {
+            if (FOLD && HAS_B && corr.wide != 0) add_wide();
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const bool row_raise = !(xor32_max(lt[nt] * gmax) <= lc.raise_sum);   // (+inf stays +inf through the max)
-                const float m_old = m_ref[32 * nt];
+                const float m_old = m_ref[32 * nt + (lane_again() & 31)];
                 const float m = row_max(nt, m_old), m_new = row_raise ? fmaxf(m_old, m) : set_here && m >= m_old - (float)down ? m : m_old;
                 if (!__any(m_new != m_old)) continue;   // no row of this row tile moves: it keeps what it has
                 move_reference(nt, m_old, m_new, HAS_B);
@@ -571,7 +710,8 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         for (int G = 0; G < NG; ++G) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                O[G >> 1][nt] = mfma32(va[G % NVA].h, pb[nt][G & 1].h, O[G >> 1][nt]);
+                if constexpr (PARK) O[G >> 1][nt] = mfma32(va[G % NVA].h, pb[nt][G & 1].h, O[G >> 1][nt]);
+                else mfma32_v<true, false>(O[G >> 1][nt], va[G % NVA].h, pb[nt][G & 1].h);
                 fence();
                 if (FOLD && HAS_B && G == 0 && nt == 0) fold(NU - 1);
                 vhalf(2 * G + NVA + nt);
@@ -596,17 +736,12 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             if (LAST && masked < kTile) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    if (8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) >= masked) Sb[nt][i] = -INFINITY;
+                    if (8 * (i >> 2) + (upper ? 4 : 0) + (i & 3) >= masked) Sb[nt][i] = -INFINITY;
             }
             Sa[nt] = Sb[nt];
         }
     }
 }
-
-// Waves per SIMD the kernel is compiled for: one where it needs all 512 registers; three for 32-row blocks at
-// head_dim 64 (the small-row shape of the SmolLM2-sized pool: 768 workgroups, all resident at once on 256 CUs,
-// so that one workgroup's query fetch, pipeline ramp and merge overlap the others' main loops).
-constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && NT == 1 && vc_bits(VC) == 3 && !vc_has_scale(VC)) ? 3 : 1; }
 
 // ws_ml / ws_o: where the kernel leaves its split's partial (direct == 0); with direct == 1 and private tails,
 // the tail kernel's partials (row maxima and denominators / unnormalized sums), read in the final pass.
@@ -625,7 +760,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     using LY = Layout<D, VC, KC>;
     constexpr int NB = D / 32, MG = D / 32, ROWS = 32 * NT;
     constexpr int WG_ROWS = OWN ? 4 * ROWS : ROWS, STEP = OWN ? 1 : 4;   // rows of the workgroup; tiles from one of a wave's to its next
-    constexpr bool FOLD = fold_scales(KC, K16);
+    constexpr bool FOLD = fold_scales(KC, K16), PARK = parks(D, NT, VC);
     constexpr int OSTRIDE = D + 4;
     constexpr int TB = LY::tile_bytes;
     __shared__ float m_s[4][ROWS];
@@ -670,6 +805,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
         for (int j = 0; j < NB; ++j) cur.k[j] = tr.kcodes(t0, j);
         tr.kscales(t0, cur.sc);
+        if constexpr (FOLD) tr.token_scales(t0, cur.tsc);
     }
 
     // ---- query rows as MFMA B operands: lane (n, h) holds q[row 32nt+n][32j + 16s + 8h .. +7].
@@ -678,7 +814,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     constexpr int QS = D + 8;  // halves per staged row: 16-byte aligned, rotates the banks
     constexpr int QT = OWN ? 64 : 256;        // threads that fetch a block of rows
     const int qt = OWN ? lane : tid;
-    _Float16* q_s = reinterpret_cast<_Float16*>(o_s) + (OWN ? wave * ROWS * QS : 0);
+    _Float16* q_s = reinterpret_cast<_Float16*>(o_s + (OWN ? wave * ROWS * OSTRIDE : 0));   // (OWN: in the wave's own buffer)
     constexpr int QP = ROWS * (D / 8) / QT;   // 16-byte pieces per thread; all requested before any is used
     static_assert(QP * QT == ROWS * (D / 8), "");
     uint4v qraw[QP];
@@ -696,7 +832,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         for (int g = 0; g < MG; ++g) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) O[g][nt][i] = 0.0f;
-            asm volatile("" : "+a"(O[g][nt]));  // now, not where the first product needs them
+            if constexpr (PARK) asm volatile("" : "+a"(O[g][nt]));  // now, not where the first product needs them
         }
 #pragma unroll
     for (int u = 0; u < QP; ++u) {
@@ -716,6 +852,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             }
         }
         *reinterpret_cast<uint4v*>(q_s + rr * QS + 8 * piece) = raw;
+        qraw[u] = raw;
     }
     __syncthreads();
     half8 qb[NT][NB][2];
@@ -726,11 +863,79 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
             for (int s = 0; s < 2; ++s)
                 qb[nt][j][s] = *reinterpret_cast<const half8*>(q_s + (32 * nt + n) * QS + 32 * j + 16 * s + 8 * h);
+    // FOLD: the rows' W (Corr), while the queries come back from LDS.  Four threads have fetched a block of a row; each stores
+    // one term (the fourth one nothing that is used), in operand order.
+    using CR = Corr<D>;
+    // (OWN: also in the wave's buffer; else in memory of its own, as it is read after the last barrier before the merge)
+    __shared__ __align__(16) _Float16 bshared_s[FOLD && !OWN ? ROWS * CR::row_halves : 8];
+    _Float16* const b_s = OWN ? q_s + ROWS * QS : bshared_s;
+    static_assert(ROWS * (QS + CR::row_halves) * sizeof(_Float16) <= ROWS * OSTRIDE * sizeof(float), "");
+    __shared__ float w_s[FOLD ? WG_ROWS * NB : 1];
+    __shared__ int wide_s[4];
+    CorrState<D, NT> corr;
+    corr.wide = 0;
+    corr.w_s = w_s + (OWN ? wave * ROWS * NB : 0);
+    float w_beyond[QP];
+    if constexpr (FOLD) {
+        const int term = qt & 3;
+#pragma unroll
+        for (int u = 0; u < QP; ++u) {
+            const int i = qt + QT * u, rr = i / (D / 8), j = (i - rr * (D / 8)) >> 2;
+            float w = 0.0f;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t two = qraw[u][b];
+                w = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, two), half2v{1, 1}, w, false);
+            }
+            w += lane_xor<1>(w);
+            w += lane_xor<2>(w);
+            w *= -128.0f * p.qscale;
+            const bool beyond = !(fabsf(w) <= kCorrMax);
+            corr.wide |= __ballot(beyond);
+            w_beyond[u] = beyond ? w : 0.0f;
+            if (beyond) w = 0.0f;
+            const _Float16 t0 = (_Float16)w;
+            w -= (float)t0;
+            const _Float16 t1 = (_Float16)w;
+            w -= (float)t1;
+            b_s[rr * CR::row_halves + term * NB + j] = term == 0 ? t0 : term == 1 ? t1 : (_Float16)w;
+        }
+        if (!OWN && lane == 0) wide_s[wave] = corr.wide != 0;
+    }
     __syncthreads();  // every wave has picked up its queries: the merge at the end reuses this memory
+    if constexpr (FOLD) {
+        if (!OWN) corr.wide = __builtin_amdgcn_readfirstlane(wide_s[0] | wide_s[1] | wide_s[2] | wide_s[3]);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int op = 0; op < CR::ops; ++op) {
+                H8 x;
+                x.h = *reinterpret_cast<const half8*>(b_s + (32 * nt + n) * CR::row_halves + 16 * op + 8 * h);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)   // (slots that no term was stored in; no reference yet)
+                    if (16 * op + 8 * h + 2 * i >= 3 * NB) x.u[i] = 0;
+                corr.b[nt][op] = x.h;
+            }
+        if (__builtin_expect(corr.wide != 0, 0)) {
+            if ((qt & 3) == 0) {
+#pragma unroll
+                for (int u = 0; u < QP; ++u) {
+                    const int i = qt + QT * u, rr = i / (D / 8);
+                    w_s[(OWN ? wave * ROWS * NB : 0) + rr * NB + ((i - rr * (D / 8)) >> 2)] = w_beyond[u];
+                }
+            }
+            if constexpr (OWN) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            } else {
+                __syncthreads();   // (all waves come here or none)
+            }
+        }
+    }
     // The queries are only ever MFMA operands: park them in accumulation registers so that the vector
     // registers are left for the scores and the dequantization temporaries (a second loop, so that the LDS
     // reads above are all in flight before the first one is waited for).
-    {
+    if constexpr (PARK) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -742,11 +947,11 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     // The references themselves are only read where a row moves its reference and at the merge: they live in the
     // wave's row of m_s (LDS), not in registers.  Both lanes of a row hold the same value and write the same value;
     // a wave's LDS accesses complete in order, so a wave reading back what it wrote needs no barrier.
-    float* const m_ref = &m_s[wave][n];   // row 32 nt + n at m_ref[32 * nt]
+    float* const m_ref = m_s[wave];
     float Lsum[NT], mneg[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        m_ref[32 * nt] = -INFINITY;
+        m_ref[32 * nt + n] = -INFINITY;
         mneg[nt] = FOLD ? 0.0f : INFINITY;   // no reference yet: the first tile's maximum sets one
         Lsum[nt] = 0.0f;
     }
@@ -762,15 +967,16 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
         for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
         pipeline_step<D, NT, VC, KC, K16, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), kNoRebase,
-                                                                   qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+                                                                   qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const float m0 = xor32_max(max16(cur.S[nt])) * (FOLD ? 1.0f : qscale);
-            m_ref[32 * nt] = m0;
-            mneg[nt] = -m0;
+            m_ref[32 * nt + n] = m0;
+            if constexpr (!FOLD) mneg[nt] = -m0;
             if constexpr (FOLD) {
+                corr.set_reference(nt, m0, h == 1);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) cur.S[nt][i] -= m0;
             }
@@ -782,7 +988,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         const int pairs_end = min(my_count - 3, setting - 1);
         auto main_step = [&]() {
             pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                              kTile, kNoRebase, qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+                                                                              kTile, kNoRebase, qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
         while (k < pairs_end) {   // two steps a trip: the two tiles' scores swap registers without copies
@@ -792,19 +998,21 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         for (; k + 1 < my_count; ++k)   // tile B may be the pool's last
             pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                             rest(k + 1), k > 0 && k >= setting ? kRebaseDown : kNoRebase,
-                                                                            qscale, lane, qb, O, Lsum, m_ref, mneg, lc);
+                                                                            qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
         const int down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0 : kNoRebase;
-        pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, lane, qb, O, Lsum,
+        pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, h == 1, qb, corr, O, Lsum,
                                                                            m_ref, mneg, lc);
     }
 
     // ---- merge the four waves through LDS: every wave stores its row maxima, denominators and accumulators
     // as they are into buffers of its own; the final pass rescales them to the common row maximum and adds
     // them in a fixed order, so the result is reproducible.
-    // (the lane number is read again here: across the main loop it would hold registers)
-    int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    asm volatile("" : "+v"(elane));
+    const int elane = lane_again();
     {
+        if constexpr (!PARK) {   // the last products
+            asm volatile("s_nop 15" : "+v"(O[0][0]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const int h = elane >> 5, n = elane & 31;
         float* obuf = o_s + wave * (ROWS * OSTRIDE);
 #pragma unroll

@@ -144,3 +144,34 @@ def test_splits_that_are_merged(d, codec):
     for splits in (2, 3):
         assert case.pool.attend_plan(_pu().dev(Q), splits=splits).splits == splits
         case.attend_check(Q, splits=splits)
+
+
+# Queries whose sum over a key block, and references, beyond what the correction's fp16 operands hold (60,000): such a row takes
+# a way of its own, its neighbours in the wave do not.
+@pytest.mark.parametrize("d,heads,agents,q,own", [(64, 2, 5, 1, 0), (64, 2, 12, 1, 0), (128, 2, 5, 1, 0), (128, 2, 12, 1, 0),
+                                                  (256, 2, 5, 1, 0), (64, 40, 33, 4, 1), (128, 40, 33, 4, 1), (256, 40, 33, 4, 1)])
+@pytest.mark.parametrize("what", ["sums", "references"])
+def test_rows_beyond_the_corrections_range(d, heads, agents, q, own, what):
+    rng = np.random.default_rng(d + agents)
+    T, group = 32 * 9 + 5, 4
+    cfg = W.PoolConfig(0, "range", 1, heads, heads * group, d, T, agents, q)
+    K, V = rng.standard_normal((1, heads, T, d)), rng.standard_normal((1, heads, T, d)).astype(np.float16)
+    Q = rng.standard_normal((1, agents, q, heads * group, d))
+    far = np.zeros(agents, bool)
+    far[1::3] = True
+    if what == "sums":             # 300 in every coordinate: |W| = 128 * qscale * 9,600, scores of ordinary size over small keys
+        K *= 0.01
+        Q[:, far] += 300.0
+    else:                          # scores of 10^5 and more; the six largest 10^4 apart (an ulp of them in fp32 is 0.016)
+        K[:, :, 7::50] += 20.0 + 3.0 * np.arange(6)[:, None]
+        Q[:, far] = 200.0 * np.abs(Q[:, far]) + 500.0
+    case = Case(cfg, K.astype(np.float16), V)
+    Q = Q.astype(np.float16)
+    assert case.pool.attend_plan(_pu().dev(Q)).own_rows == own
+    case.attend_check(Q)
+    out = case.pool.attend(_pu().dev(Q))
+    # the other agents' rows do not notice
+    Q2 = Q.copy()
+    Q2[:, far] = 0.0
+    near = np.flatnonzero(~far)
+    assert bool((case.pool.attend(_pu().dev(Q2))[:, near] == out[:, near]).all())
