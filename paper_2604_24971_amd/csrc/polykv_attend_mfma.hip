@@ -615,7 +615,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 else mfma32_v<!LOOP, PARK>(P[u & 1], cur.kop[1], qb[nt][j][1]);
                 fence();
                 if (u > 0) {
-                    if (!HAS_A) asm volatile("s_nop 15");   // (no probabilities in between)
+                    if (!HAS_A) asm volatile("s_nop 7");   // (no probabilities in between)
                     fence();
                     fold(u - 1);
                 }
@@ -1039,16 +1039,20 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         __syncthreads();
     }
 
-    // ---- final pass: every wave finishes ROWS/4 rows, four lanes to a row.  Lane qd of a row takes every
-    // fourth 4-coordinate piece (piece 4i + qd), so that the four lanes read and write 64 contiguous bytes per
-    // instruction; the rotation is then log2(D/4) in-register stages and two DPP stages, whichever index bits
-    // sit in the lane.
+    // ---- final pass: every wave finishes ROWS/4 rows, LR lanes to a row.  Lane qd of a row takes every
+    // LR-th 4-coordinate piece (piece LR i + qd), so that the lanes of a row read and write LR * 16 contiguous bytes per
+    // instruction; the rotation is then log2(D/LR) in-register stages and log2(LR) DPP stages, whichever index bits
+    // sit in the lane.  Four lanes for 16 rows; eight for the 8 rows of a 32-row workgroup's wave, of which each sixteen
+    // lanes take two that lie 8 rows apart, in different halves of the LDS banks.  (With four lanes there, half of a wave idle:
+    // 7,000 of 92,000 cycles of a wave at head_dim 256, 4,000 with eight; 26 layers x 8 heads x 2,500 tokens 46.1 -> 44.7 us,
+    // 32 one-layer calls 435 -> 412, one layer of 600 tokens 7.5 -> 7.3, SmolLM2 shape with 5 rows 28.4 -> 27.8.)
     // (OWN: a wave finishes its own rows, 16 at a time, from its own buffer.)
-    constexpr int CPL = D / 4, RPW = ROWS / 4;
-    const int ri = elane >> 2, qd = elane & 3;
+    constexpr int LR = OWN || NT == 2 ? 4 : 8, CPL = D / LR;
+    const int qd = LR == 8 ? codec_chunk(elane) : elane & 3;
+    const int ri = LR == 8 ? ((elane >> 1) & 2) | ((elane >> 4) & 1) | ((elane >> 3) & 4) : elane >> 2;
+    const float entry_sign = LR == 8 ? codec_entry_sign(elane) : quad_entry_sign(elane);
 #pragma unroll 1
     for (int pass = 0; pass < (OWN ? ROWS / 16 : 1); ++pass) {
-        if (!OWN && ri >= RPW) break;
         const int rr = OWN ? 16 * pass + ri : wave + 4 * ri, r = row0 + rr;
         constexpr int NW = OWN ? 1 : 4;   // the waves that hold a share of the row
         const int w0 = OWN ? wave : 0;
@@ -1083,24 +1087,24 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         // int8 values are accumulated unrotated and unscaled: 1/l is all that is left to do
         constexpr float kCS = inv_centroid_scale<vc_bits(VC)>();
         const float f = VC == 2 ? (direct ? inv_l : 1.0f)
-                        : direct ? quad_entry_sign(elane) * (kCS * (D == 64 ? 0.125f : D == 128 ? 0.08838834764831845f : 0.0625f)) *
+                        : direct ? entry_sign * (kCS * (D == 64 ? 0.125f : D == 128 ? 0.08838834764831845f : 0.0625f)) *
                                        inv_l
                                  : kCS;
 #pragma unroll
         for (int w = 0; w < NW; ++w) fw[w] *= f;
-        float x[CPL];  // x[4i + k] = coordinate 16i + 4qd + k
+        float x[CPL];  // x[4i + k] = coordinate 4 (LR i + qd) + k
         constexpr int BUF4 = ROWS * OSTRIDE / 4;  // one wave's buffer, in float4 units
         const float4* a4 = reinterpret_cast<const float4*>(&o_s[rr * OSTRIDE]) + w0 * BUF4 + qd;
 #pragma unroll
         for (int i = 0; i < CPL / 4; ++i) {
-            const float4 a = a4[4 * i];
+            const float4 a = a4[LR * i];
             if constexpr (OWN) {
                 x[4 * i + 0] = a.x * fw[0];
                 x[4 * i + 1] = a.y * fw[0];
                 x[4 * i + 2] = a.z * fw[0];
                 x[4 * i + 3] = a.w * fw[0];
             } else {
-                const float4 b = a4[BUF4 + 4 * i], c = a4[2 * BUF4 + 4 * i], d = a4[3 * BUF4 + 4 * i];
+                const float4 b = a4[BUF4 + LR * i], c = a4[2 * BUF4 + LR * i], d = a4[3 * BUF4 + LR * i];
                 x[4 * i + 0] = (a.x * fw[0] + b.x * fw[1]) + (c.x * fw[2] + d.x * fw[3]);
                 x[4 * i + 1] = (a.y * fw[0] + b.y * fw[1]) + (c.y * fw[2] + d.y * fw[3]);
                 x[4 * i + 2] = (a.z * fw[0] + b.z * fw[1]) + (c.z * fw[2] + d.z * fw[3]);
@@ -1109,14 +1113,16 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         }
         if (direct) {
             if (VC != 2) {
-                wht_cross_quad<CPL>(x, elane);
+                if constexpr (LR == 8) wht_cross_chunks<CPL>(x, elane);
+                else wht_cross_quad<CPL>(x, elane);
                 wht_inlane<CPL>(x);
-                // rotation variant H.D: piece i holds coordinates 16i + 4qd ..
+                // rotation variant H.D
                 if (p.signs.on) {
 #pragma unroll
                     for (int i = 0; i < CPL / 4; ++i) {
                         float(&x4)[4] = *reinterpret_cast<float(*)[4]>(&x[4 * i]);
-                        flip_signs<4>(x4, sign_word(p.signs, i >> 1) >> (16 * (i & 1) + 4 * qd));
+                        const int at = LR == 8 ? 4 * qd : 16 * (i & 1) + 4 * qd;
+                        flip_signs<4>(x4, sign_word(p.signs, LR == 8 ? i : i >> 1) >> at);
                     }
                 }
             }
@@ -1124,7 +1130,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                 const float4* t4 = reinterpret_cast<const float4*>(ws_o + tail_row * D) + qd;
 #pragma unroll
                 for (int i = 0; i < CPL / 4; ++i) {
-                    const float4 t = t4[4 * i];
+                    const float4 t = t4[LR * i];
                     x[4 * i] = fmaf(tail_w, t.x, x[4 * i]);
                     x[4 * i + 1] = fmaf(tail_w, t.y, x[4 * i + 1]);
                     x[4 * i + 2] = fmaf(tail_w, t.z, x[4 * i + 2]);
@@ -1134,13 +1140,13 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             if (r < p.R) {
                 float4* dst = reinterpret_cast<float4*>(out + q_row_index(p, ls, kvh, r) * D) + qd;
 #pragma unroll
-                for (int i = 0; i < CPL / 4; ++i) dst[4 * i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+                for (int i = 0; i < CPL / 4; ++i) dst[LR * i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
             }
         } else if (r < p.R) {
             const size_t prow = ((size_t)usel * p.nsplit + split) * p.R + r;
             float4* dst = reinterpret_cast<float4*>(ws_o + prow * D) + qd;
 #pragma unroll
-            for (int i = 0; i < CPL / 4; ++i) dst[4 * i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+            for (int i = 0; i < CPL / 4; ++i) dst[LR * i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
             if (qd == 0) {
                 ws_ml[prow * 2] = Mr;
                 ws_ml[prow * 2 + 1] = l;
