@@ -394,8 +394,8 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
         static const TailKern tail_table[3][2] = {{attend_tail_kernel<64, false>, attend_tail_kernel<64, true>},
                                                   {attend_tail_kernel<128, false>, attend_tail_kernel<128, true>},
                                                   {attend_tail_kernel<256, false>, attend_tail_kernel<256, true>}};
-        tail_table[plan.D == 64 ? 0 : plan.D == 128 ? 1 : 2][plan.io_bf16 ? 1 : 0]<<<grid, 64, 0, s>>>(
-            (const __half*)Q, *tails, tail_ml, tail_o, plan);
+        launch_kernel(tail_table[plan.D == 64 ? 0 : plan.D == 128 ? 1 : 2][plan.io_bf16 ? 1 : 0], grid, dim3(64), 0, s, {},
+                      (const __half*)Q, *tails, tail_ml, tail_o, plan);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (plan.kernel == POLYKV_KERNEL_MATRIX) {
@@ -422,12 +422,8 @@ hipError_t launch_attend(const polykv_pool* pool, const AttendPlan& plan, const 
     }
     const long nrows = (long)units * plan.R;
     dim3 mgrid((unsigned)((nrows + 3) / 4));
-    if (plan.D == 128)
-        attend_merge_kernel<128><<<mgrid, 256, 0, s>>>(ws_ml, ws_o, tail_ml, tail_o, (float*)out, plan);
-    else if (plan.D == 64)
-        attend_merge_kernel<64><<<mgrid, 256, 0, s>>>(ws_ml, ws_o, tail_ml, tail_o, (float*)out, plan);
-    else
-        attend_merge_kernel<256><<<mgrid, 256, 0, s>>>(ws_ml, ws_o, tail_ml, tail_o, (float*)out, plan);
+    launch_kernel(plan.D == 128 ? attend_merge_kernel<128> : plan.D == 64 ? attend_merge_kernel<64> : attend_merge_kernel<256>, mgrid,
+                  dim3(256), 0, s, {}, ws_ml, ws_o, tail_ml, tail_o, (float*)out, plan);
     return hipGetLastError();
 }
 
