@@ -423,11 +423,17 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
 
 // Waves per SIMD the kernel is compiled for: one where it needs all 512 registers; three for 32-row blocks at
 // head_dim 64 (the small-row shape of the SmolLM2-sized pool: 768 workgroups, all resident at once on 256 CUs,
-// so that one workgroup's query fetch, pipeline ramp and merge overlap the others' main loops).
-constexpr int kernel_waves_per_simd(int D, int NT, int VC) { return (D == 64 && NT == 1 && vc_bits(VC) == 3 && !vc_has_scale(VC)) ? 3 : 1; }
-// Where three waves share a SIMD, queries and accumulators are in vector registers like everything else: with any
-// accumulation registers in use the compiler has half of a wave's 168 for either kind, and moved 80 values a step between them.
-constexpr bool parks(int D, int NT, int VC) { return kernel_waves_per_simd(D, NT, VC) != 3; }
+// so that one workgroup's query fetch, pipeline ramp and merge overlap the others' main loops); two for 64-row blocks there
+// (24 layers x 32 heads x 1,851 tokens: 40 rows 54.6 us with one, 42.3 with two, 100 rows 97.8 and 72.4).  Value scales, 4-bit
+// values and waves with rows of their own take up to five registers more than that leaves.
+constexpr int kernel_waves_per_simd(int D, int NT, int VC, bool OWN) {
+    if (D != 64 || vc_has_scale(VC) || OWN) return 1;
+    return NT == 2 ? (vc_bits(VC) == 4 ? 1 : 2) : vc_bits(VC) == 3 ? 3 : 1;
+}
+// Where several waves share a SIMD, queries and accumulators are in vector registers like everything else: with any
+// accumulation registers in use the compiler has half of a wave's registers for either kind, and at three waves moved 80 values
+// a step between them.
+constexpr bool parks(int waves_per_simd) { return waves_per_simd == 1; }
 
 // The correction's query operands (FOLD) and where the rows' W beyond kCorrMax are; else empty.
 template <int D, int NT> struct CorrState {
@@ -462,7 +468,7 @@ struct OneValue {   // (in the place of a tile of products)
     __device__ __forceinline__ float operator[](int) const { return v; }
 };
 
-template <int D, int NT, int VC, int KC, bool K16, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
+template <int D, int NT, int VC, int KC, bool K16, int WPS, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
 __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
                                               uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, int down, float qscale,
                                               bool upper, const half8 (&qb)[NT][D / 32][2], CorrState<D, NT>& corr,
@@ -470,7 +476,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                                               const LoopConsts& lc) {
     using TR = TileReader<D, VC, KC, K16>;
     constexpr int NB = D / 32, NG = D / 16, MG = D / 32;
-    constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC), PARK = parks(D, NT, VC);
+    constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC), PARK = parks(WPS);
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
     auto& Sa = cur.S;
     ScoreTile<FOLD> Sb[NT];
@@ -549,12 +555,14 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     H8 acorr[CR::ops];   // the correction's scale operands
 
     // block j's products with row tile nt (FOLD): two of them take turns, one is folded while the other is formed
-    float16v P[FOLD ? 2 : 1];
+    // (with two waves a SIMD one: a unit is folded before the next is formed)
+    constexpr int NP = FOLD && WPS != 2 ? 2 : 1;
+    float16v P[NP];
     constexpr int NU = NB * NT;
     // (A DPP source must not have been written by the two instructions before: a block's scale is formed a unit ahead.)
     float fscale[2];
     auto fold_scale = [&](int j) { fscale[j & 1] = (float)half_of(cur.sc[j >> 1], j & 1) * (qscale * kCodeScale); };
-    auto fold = [&](int u) { fold16(Sb[u % NT], P[u & (FOLD ? 1 : 0)], fscale[u / NT & 1]); };
+    auto fold = [&](int u) { fold16(Sb[u % NT], P[u % NP], fscale[u / NT & 1]); };
     auto add_wide = [&]() {   // (rare) of the rows that have them, what is too large for the correction's operands
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -600,24 +608,36 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                     if (HAS_A) exp_chunk(u);
                     fence();
                 }
-                if (u == 0) mfma32_v0<true, PARK>(P[u & 1], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
-                else mfma32_v0<!LOOP, PARK>(P[u & 1], cur.kop[0], qb[nt][j][0]);
+                if (u == 0) mfma32_v0<true, PARK>(P[u % NP], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
+                else mfma32_v0<!LOOP, PARK>(P[u % NP], cur.kop[0], qb[nt][j][0]);
                 fence();
                 if (u == 0) scales_next();
                 if (nt == 0) fold_scale(j);
                 if (last_nt) kdeq(2 * (j + 1), cur.kop[0]);
-                if (HAS_A) {   // (the first ones have had a chunk each with their tiles' corrections)
+                // The unit's chunks (the first ones have had a chunk each with their tiles' corrections); NP == 1: behind the second
+                // product, which is folded after them.
+                constexpr bool behind = NP == 1 && u + 1 < NU;
+                constexpr int c0 = NP == 2 ? (NT > u * NCH / NU ? NT : u * NCH / NU) : behind ? NT + u * (NCH - NT) / (NU - 1) : NCH;
+                constexpr int c1 = NP == 2 ? (u + 1) * NCH / NU : behind ? NT + (u + 1) * (NCH - NT) / (NU - 1) : NCH;
+                auto chunks = [&]() {
+                    if (HAS_A) {
 #pragma unroll
-                    for (int c = max(NT, u * NCH / NU); c < (u + 1) * NCH / NU; ++c) exp_chunk(c);
-                }
+                        for (int c = c0; c < c1; ++c) exp_chunk(c);
+                    }
+                };
+                if (!behind) chunks();
                 fence();
-                if (u == 0) mfma32_v<true, PARK>(P[u & 1], cur.kop[1], qb[nt][j][1]);
-                else mfma32_v<!LOOP, PARK>(P[u & 1], cur.kop[1], qb[nt][j][1]);
+                if (u == 0) mfma32_v<true, PARK>(P[u % NP], cur.kop[1], qb[nt][j][1]);
+                else mfma32_v<!LOOP, PARK>(P[u % NP], cur.kop[1], qb[nt][j][1]);
                 fence();
-                if (u > 0) {
-                    if (!HAS_A) asm volatile("s_nop 7");   // (no probabilities in between)
+                if (behind) chunks();
+                if (NP == 2 ? u > 0 : behind) {
+                    if (!HAS_A) {   // (no probabilities in between)
+                        if (NP == 2) asm volatile("s_nop 7");
+                        else asm volatile("s_nop 15");
+                    }
                     fence();
-                    fold(u - 1);
+                    fold(NP == 2 ? u - 1 : u);
                 }
                 if (last_nt) {
                     kdeq(2 * (j + 1) + 1, cur.kop[1]);
@@ -760,7 +780,8 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
     using LY = Layout<D, VC, KC>;
     constexpr int NB = D / 32, MG = D / 32, ROWS = 32 * NT;
     constexpr int WG_ROWS = OWN ? 4 * ROWS : ROWS, STEP = OWN ? 1 : 4;   // rows of the workgroup; tiles from one of a wave's to its next
-    constexpr bool FOLD = fold_scales(KC, K16), PARK = parks(D, NT, VC);
+    constexpr int WPS = kernel_waves_per_simd(D, NT, VC, OWN);
+    constexpr bool FOLD = fold_scales(KC, K16), PARK = parks(WPS);
     constexpr int OSTRIDE = D + 4;
     constexpr int TB = LY::tile_bytes;
     __shared__ float m_s[4][ROWS];
@@ -966,7 +987,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         // prologue: scores of tile 0; requests the values of tile 0 and the keys of tile 1
 #pragma unroll
         for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
-        pipeline_step<D, NT, VC, KC, K16, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), kNoRebase,
+        pipeline_step<D, NT, VC, KC, K16, WPS, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), kNoRebase,
                                                                    qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
@@ -987,7 +1008,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         const int setting = my_count - (p.references > 1 ? p.references - 1 + (ragged ? 1 : 0) : 0);   // from this tile on
         const int pairs_end = min(my_count - 3, setting - 1);
         auto main_step = [&]() {
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+            pipeline_step<D, NT, VC, KC, K16, WPS, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                               kTile, kNoRebase, qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
@@ -996,11 +1017,11 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             main_step();
         }
         for (; k + 1 < my_count; ++k)   // tile B may be the pool's last
-            pipeline_step<D, NT, VC, KC, K16, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
+            pipeline_step<D, NT, VC, KC, K16, WPS, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                             rest(k + 1), k > 0 && k >= setting ? kRebaseDown : kNoRebase,
                                                                             qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
         const int down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0 : kNoRebase;
-        pipeline_step<D, NT, VC, KC, K16, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, h == 1, qb, corr, O, Lsum,
+        pipeline_step<D, NT, VC, KC, K16, WPS, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, h == 1, qb, corr, O, Lsum,
                                                                            m_ref, mneg, lc);
     }
 
@@ -1156,7 +1177,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 }
 
 template <int D, int NT, int VC, int KC, bool K16, bool OWN>
-__global__ __launch_bounds__(256, OWN ? 1 : kernel_waves_per_simd(D, NT, VC)) void attend_mfma_kernel(
+__global__ __launch_bounds__(256, kernel_waves_per_simd(D, NT, VC, OWN)) void attend_mfma_kernel(
     const uint8_t* __restrict__ pool, const __half* __restrict__ Q, float* __restrict__ ws_ml, float* __restrict__ ws_o,
     float* __restrict__ out, AttendPlan p, int direct) {
     attend_mfma_block<D, NT, VC, KC, K16, OWN>(pool, Q, ws_ml, ws_o, out, p, direct, blockIdx.y * p.grid_x + blockIdx.x);
@@ -1164,7 +1185,7 @@ __global__ __launch_bounds__(256, OWN ? 1 : kernel_waves_per_simd(D, NT, VC)) vo
 
 // Two workgroups a CU wherever the pool's part fits 256 registers (left alone, the tails' part takes 324 at head_dim 128).
 constexpr int tails_waves_per_simd(int D, int VC, int KC) {
-    return D == 128 && vc_has_scale(VC) && KC == 0 ? 1 : kernel_waves_per_simd(D, 1, VC) == 3 ? 3 : 2;
+    return D == 128 && vc_has_scale(VC) && KC == 0 ? 1 : kernel_waves_per_simd(D, 1, VC, false) == 3 ? 3 : 2;
 }
 // The same for a call whose token range is split, with the private tails in the same launch: the workgroups from
 // pool_blocks on do the tails, a wave each.  Neither part needs the other before the merge kernel, and two workgroups of
