@@ -135,15 +135,6 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
 //   otherwise (one scale per layer tensor, whose scale rides on the softmax scale; keys rounded to fp16): one product
 //     over all blocks.
 __host__ __device__ constexpr bool fold_scales(int KC, bool K16) { return KC == 0 && !K16; }
-// A tile of scores, 16 per lane: the result of a product itself, or 16 separate numbers where the products are folded
-// (as one vector value they would have to sit in 16 consecutive registers, and the register allocator then copies).
-struct Scores16 {
-    float v[16];
-    __device__ __forceinline__ float& operator[](int i) { return v[i]; }
-    __device__ __forceinline__ float operator[](int i) const { return v[i]; }
-};
-template <bool FOLD> using ScoreTile = float16v;
-
 // FOLD: the codes enter the products as they are stored, offset by 128, as fp16 subnormals: byte b becomes b * 2^-24, one
 // byte permute per two codes and nothing else (the matrix cores take subnormals at full precision).  What that and the
 // rows' softmax references ask for,
@@ -408,7 +399,7 @@ constexpr int kRebaseDown = 4, kNoRebase = -1;
 
 template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     using TR = TileReader<D, VC, KC, K16>;
-    ScoreTile<fold_scales(KC, K16)> S[NT];         // scores of tile A
+    float16v S[NT];                                // scores of tile A
     half8 kop[2];                                  // tile B: key operands of block 0, both halves,
     uint4v k[D / 32];                              //   key codes (block 0: of the tile after B),
     uint32_t sc[TR::NS];                           //   key scales
@@ -479,7 +470,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC), PARK = parks(WPS);
     const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
     auto& Sa = cur.S;
-    ScoreTile<FOLD> Sb[NT];
+    float16v Sb[NT];
     float lt[NT];   // this tile's probability sums, per lane
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) lt[nt] = 0.0f;
@@ -884,75 +875,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
             for (int s = 0; s < 2; ++s)
                 qb[nt][j][s] = *reinterpret_cast<const half8*>(q_s + (32 * nt + n) * QS + 32 * j + 16 * s + 8 * h);
-    // FOLD: the rows' W (Corr), while the queries come back from LDS.  Four threads have fetched a block of a row; each stores
-    // one term (the fourth one nothing that is used), in operand order.
-    using CR = Corr<D>;
-    // (OWN: also in the wave's buffer; else in memory of its own, as it is read after the last barrier before the merge)
-    __shared__ __align__(16) _Float16 bshared_s[FOLD && !OWN ? ROWS * CR::row_halves : 8];
-    _Float16* const b_s = OWN ? q_s + ROWS * QS : bshared_s;
-    static_assert(ROWS * (QS + CR::row_halves) * sizeof(_Float16) <= ROWS * OSTRIDE * sizeof(float), "");
-    __shared__ float w_s[FOLD ? WG_ROWS * NB : 1];
-    __shared__ int wide_s[4];
-    CorrState<D, NT> corr;
-    corr.wide = 0;
-    corr.w_s = w_s + (OWN ? wave * ROWS * NB : 0);
-    float w_beyond[QP];
-    if constexpr (FOLD) {
-        const int term = qt & 3;
-#pragma unroll
-        for (int u = 0; u < QP; ++u) {
-            const int i = qt + QT * u, rr = i / (D / 8), j = (i - rr * (D / 8)) >> 2;
-            float w = 0.0f;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const uint32_t two = qraw[u][b];
-                w = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, two), half2v{1, 1}, w, false);
-            }
-            w += lane_xor<1>(w);
-            w += lane_xor<2>(w);
-            w *= -128.0f * p.qscale;
-            const bool beyond = !(fabsf(w) <= kCorrMax);
-            corr.wide |= __ballot(beyond);
-            w_beyond[u] = beyond ? w : 0.0f;
-            if (beyond) w = 0.0f;
-            const _Float16 t0 = (_Float16)w;
-            w -= (float)t0;
-            const _Float16 t1 = (_Float16)w;
-            w -= (float)t1;
-            b_s[rr * CR::row_halves + term * NB + j] = term == 0 ? t0 : term == 1 ? t1 : (_Float16)w;
-        }
-        if (!OWN && lane == 0) wide_s[wave] = corr.wide != 0;
-    }
     __syncthreads();  // every wave has picked up its queries: the merge at the end reuses this memory
-    if constexpr (FOLD) {
-        if (!OWN) corr.wide = __builtin_amdgcn_readfirstlane(wide_s[0] | wide_s[1] | wide_s[2] | wide_s[3]);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int op = 0; op < CR::ops; ++op) {
-                H8 x;
-                x.h = *reinterpret_cast<const half8*>(b_s + (32 * nt + n) * CR::row_halves + 16 * op + 8 * h);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)   // (slots that no term was stored in; no reference yet)
-                    if (16 * op + 8 * h + 2 * i >= 3 * NB) x.u[i] = 0;
-                corr.b[nt][op] = x.h;
-            }
-        if (__builtin_expect(corr.wide != 0, 0)) {
-            if ((qt & 3) == 0) {
-#pragma unroll
-                for (int u = 0; u < QP; ++u) {
-                    const int i = qt + QT * u, rr = i / (D / 8);
-                    w_s[(OWN ? wave * ROWS * NB : 0) + rr * NB + ((i - rr * (D / 8)) >> 2)] = w_beyond[u];
-                }
-            }
-            if constexpr (OWN) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            } else {
-                __syncthreads();   // (all waves come here or none)
-            }
-        }
-    }
     // The queries are only ever MFMA operands: park them in accumulation registers so that the vector
     // registers are left for the scores and the dequantization temporaries (a second loop, so that the LDS
     // reads above are all in flight before the first one is waited for).
@@ -963,6 +886,76 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int s = 0; s < 2; ++s) asm volatile("" : "+a"(qb[nt][j][s]));
+    }
+
+    // FOLD: the rows' W (Corr).  A row's sum over a block is a product of the queries with ones, which leaves it in all registers of
+    // the row's lanes: 16 matrix instructions for 64 rows, and every lane has what it needs for its own operands.  (Summed by the
+    // threads that fetch the queries, and handed over through LDS, it made 512 rows over 100 tokens, with rows of their own for the
+    // waves, 46.1 instead of 44.0 us.)
+    __shared__ float w_s[FOLD ? WG_ROWS * NB : 1];   // (waves that share rows write the same numbers)
+    CorrState<D, NT> corr;
+    corr.wide = 0;
+    float* const w_mine = w_s + (OWN ? wave * ROWS * NB : 0);
+    corr.w_s = w_mine;
+    if constexpr (FOLD) {
+        using CR = Corr<D>;
+        H8 ones;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ones.u[i] = 0x3c003c00u;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            float16v sum[NB];   // (the blocks' products in turn: a block's second waits for its first)
+            static_for<NB>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                mfma32_v0<j == 0, PARK>(sum[j], ones.h, qb[nt][j][0]);
+            });
+            static_for<NB>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                mfma32_v<false, PARK>(sum[j], ones.h, qb[nt][j][1]);
+            });
+            asm volatile("s_nop 11");
+            __builtin_amdgcn_sched_barrier(0);
+            float beyond[NB];
+            bool any = false;
+            _Float16 term[3][NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                float w = sum[j][0] * (-128.0f * p.qscale);
+                const bool far = !(fabsf(w) <= kCorrMax);
+                beyond[j] = far ? w : 0.0f;
+                w = far ? 0.0f : w;
+                any |= far;
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    term[x][j] = (_Float16)w;
+                    w -= (float)term[x][j];
+                }
+            }
+            auto word = [&](int d) -> uint32_t {   // slots 2 d and 2 d + 1; zero beyond the terms (no reference yet)
+                if (2 * d >= 3 * NB) return 0u;
+                return __builtin_bit_cast(uint32_t, half2v{term[2 * d / NB][2 * d % NB], term[2 * d / NB][2 * d % NB + 1]});
+            };
+#pragma unroll
+            for (int op = 0; op < CR::ops; ++op) {
+                H8 x;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x.u[i] = h ? word(8 * op + 4 + i) : word(8 * op + i);
+                corr.b[nt][op] = x.h;
+            }
+            const uint64_t wide = __ballot(any);
+            corr.wide |= wide;
+            if (__builtin_expect(wide != 0, 0)) {
+                if (h == 0) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = beyond[j];
+                }
+            } else if (NT == 2 && h == 0) {   // (the other row tile may have such rows)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = 0.0f;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (a wave's LDS accesses complete in order)
+        __builtin_amdgcn_wave_barrier();
     }
 
     // The references themselves are only read where a row moves its reference and at the merge: they live in the
