@@ -31,7 +31,8 @@
 // What the forms of the scores took, us a call (15 agents x 4,096 tokens at R = 60; 64 agents x 4 queries x 7,194 tokens):
 //   the exact dequantized key, 18 bits, as two fp16 terms and two products     61.4    1,624
 //   codes less their offset (2 packed subtractions per 4 codes), fold          55      1,470 (1,165 in die order, 1,097 with own rows)
-//   codes as stored and the correction (Corr), one box                         53.4 -> 52.4    1,088 -> 1,067
+//   codes as stored and the correction (Corr), one box                         53.4 -> 52.4    1,088 -> 1,067 (1,040 to 1,065
+//                                                                              with the rows' sums by products with ones)
 // The last also took SmolLM2-shaped calls of 5 rows from 28.8 to 27.7 us (24.3 instead of 27.2 out of the cache; half of that
 // by keeping accumulators and queries in vector registers, see parks), tails over 7,194 tokens from 113.9 to 112.0, 32 one-layer
 // calls from 442 to 435.  A step's vector instructions: 400 -> 340 (two row tiles, head_dim 128), 298 -> 139 (one, 64).
