@@ -943,16 +943,10 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
                 for (int i = 0; i < 4; ++i) x.u[i] = h ? word(8 * op + 4 + i) : word(8 * op + i);
                 corr.b[nt][op] = x.h;
             }
-            const uint64_t wide = __ballot(any);
-            corr.wide |= wide;
-            if (__builtin_expect(wide != 0, 0)) {
-                if (h == 0) {
+            corr.wide |= __ballot(any);
+            if (h == 0) {   // (for every row: a reference beyond the range reads them too)
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = beyond[j];
-                }
-            } else if (NT == 2 && h == 0) {   // (the other row tile may have such rows)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = 0.0f;
+                for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = beyond[j];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (a wave's LDS accesses complete in order)

@@ -175,3 +175,44 @@ def test_rows_beyond_the_corrections_range(d, heads, agents, q, own, what):
     Q2[:, far] = 0.0
     near = np.flatnonzero(~far)
     assert bool((case.pool.attend(_pu().dev(Q2))[:, near] == out[:, near]).all())
+
+
+# References beyond 60,000 of rows whose block sums are zero: queries of one size and alternating sign, over keys of which a few
+# lie along them.  In the 32-row form, the one with 64 shared rows and the one with rows of their own, and with the tails in the
+# pool's launch.
+@pytest.mark.parametrize("d,heads,agents,q,block_rows,own,tails", [
+    (64, 2, 5, 1, 32, 0, False), (128, 2, 5, 1, 32, 0, False), (256, 2, 5, 1, 32, 0, False), (64, 2, 5, 1, 32, 0, True),
+    (128, 2, 5, 1, 32, 0, True), (128, 256, 12, 1, 64, 0, False), (64, 40, 33, 4, 64, 1, False),
+    (128, 40, 33, 4, 64, 1, False), (256, 40, 33, 4, 32, 1, False)])
+def test_large_references_alone(d, heads, agents, q, block_rows, own, tails):
+    rng = np.random.default_rng(3 * d + agents)
+    T, group = 32 * 9 + 5, 4
+    half = lambda *s: rng.standard_normal(s).astype(np.float16)
+    sign = np.where(np.arange(d) % 2 == 0, 1.0, -1.0)
+    K = rng.standard_normal((1, heads, T, d))
+    K[:, :, 7::50] += (20.0 + 3.0 * np.arange(6))[:, None] * sign
+    Q = rng.standard_normal((1, agents, q, heads * group, d))
+    far = np.zeros(agents, bool)
+    far[1::3] = True
+    Q[:, far] = 200.0 * sign
+    K, Q = K.astype(np.float16), Q.astype(np.float16)
+    base2 = d ** -0.5 / np.log(2.0)
+    assert np.abs(128.0 * base2 * Q[:, far].astype(np.float64).reshape(-1, d // 32, 32).sum(-1)).max() == 0.0
+    assert (200.0 * sign * K[0, 0, 257].astype(np.float64)).sum() * base2 > 60000.0     # (the largest of the six)
+    case = Case(W.PoolConfig(0, "references", 1, heads, heads * group, d, T, agents, q), K, half(1, heads, T, d))
+    kw, gpu_kw = {}, {}
+    if tails:
+        lens = [3 + 2 * a for a in range(agents)]
+        pairs = [(half(1, heads, 20, d), half(1, heads, 20, d)) for _ in lens]
+        kw = dict(tails_np=pairs, tails_len=lens, splits=2)
+        gpu_kw = dict(tails=[(_pu().dev(k), _pu().dev(v), n) for (k, v), n in zip(pairs, lens)], splits=2)
+    choice = case.pool.attend_plan(_pu().dev(Q), **gpu_kw)
+    assert (choice.block_rows, choice.own_rows, choice.tails_in_pool_launch) == (block_rows, own, int(tails))
+    case.pool.attend(_pu().dev(Q + np.float16(300.0)), **gpu_kw)    # sums beyond the range leave other numbers in the LDS
+    case.attend_check(Q, **kw)
+    out = case.pool.attend(_pu().dev(Q), **gpu_kw)
+    # the other agents' rows do not notice
+    Q2 = Q.copy()
+    Q2[:, far] = 0.0
+    near = np.flatnonzero(~far)
+    assert bool((case.pool.attend(_pu().dev(Q2), **gpu_kw)[:, near] == out[:, near]).all())
