@@ -579,6 +579,15 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 constexpr int u = decltype(uc)::value;
                 constexpr int j = u / NT, nt = u % NT;
                 const bool last_nt = nt == NT - 1 && j + 1 < NB;
+                // The unit's chunks of probabilities, in order, so that a tile's sum is the same where it is formed anew (the rows
+                // that move their reference).  The first units have one each with their tiles' corrections; NP == 1: the others
+                // behind the second product, which is folded after them.
+                constexpr bool behind = NP == 1 && u + 1 < NU;
+                auto chunks_before = [](int x) {
+                    const int first = x < NT ? x : NT, even = x * NCH / NU;
+                    return NP == 2 ? (even > first ? even : first) : x < NU ? first + x * (NCH - NT) / (NU - 1) : NCH;
+                };
+                constexpr int c0 = chunks_before(u), c1 = chunks_before(u + 1);
                 fence();
                 if (j == 0) {   // what the block products are added to
                     float16v& C = Sb[nt];
@@ -597,7 +606,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                     if constexpr (CR::ops == 2) mfma32_v<true, false>(C, acorr[CR::ops - 1].h, corr.b[nt][CR::ops - 1]);
                     fence();
                     if (nt == NT - 1) tr.token_scales(nextK, cur.tsc);
-                    if (HAS_A) exp_chunk(u);
+                    if (HAS_A) exp_chunk(c0);
                     fence();
                 }
                 if (u == 0) mfma32_v0<true, PARK>(P[u % NP], cur.kop[0], qb[nt][j][0]);   // (operands handed over by the last step)
@@ -606,15 +615,10 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 if (u == 0) scales_next();
                 if (nt == 0) fold_scale(j);
                 if (last_nt) kdeq(2 * (j + 1), cur.kop[0]);
-                // The unit's chunks (the first ones have had a chunk each with their tiles' corrections); NP == 1: behind the second
-                // product, which is folded after them.
-                constexpr bool behind = NP == 1 && u + 1 < NU;
-                constexpr int c0 = NP == 2 ? (NT > u * NCH / NU ? NT : u * NCH / NU) : behind ? NT + u * (NCH - NT) / (NU - 1) : NCH;
-                constexpr int c1 = NP == 2 ? (u + 1) * NCH / NU : behind ? NT + (u + 1) * (NCH - NT) / (NU - 1) : NCH;
                 auto chunks = [&]() {
                     if (HAS_A) {
 #pragma unroll
-                        for (int c = c0; c < c1; ++c) exp_chunk(c);
+                        for (int c = c0 + (j == 0 ? 1 : 0); c < c1; ++c) exp_chunk(c);
                     }
                 };
                 if (!behind) chunks();

@@ -182,7 +182,7 @@ def test_rows_beyond_the_corrections_range(d, heads, agents, q, own, what):
 # pool's launch.
 @pytest.mark.parametrize("d,heads,agents,q,block_rows,own,tails", [
     (64, 2, 5, 1, 32, 0, False), (128, 2, 5, 1, 32, 0, False), (256, 2, 5, 1, 32, 0, False), (64, 2, 5, 1, 32, 0, True),
-    (128, 2, 5, 1, 32, 0, True), (128, 256, 12, 1, 64, 0, False), (64, 40, 33, 4, 64, 1, False),
+    (128, 2, 5, 1, 32, 0, True), (64, 256, 12, 1, 64, 0, False), (128, 256, 12, 1, 64, 0, False), (64, 40, 33, 4, 64, 1, False),
     (128, 40, 33, 4, 64, 1, False), (256, 40, 33, 4, 32, 1, False)])
 def test_large_references_alone(d, heads, agents, q, block_rows, own, tails):
     rng = np.random.default_rng(3 * d + agents)
@@ -216,3 +216,28 @@ def test_large_references_alone(d, heads, agents, q, block_rows, own, tails):
     Q2[:, far] = 0.0
     near = np.flatnonzero(~far)
     assert bool((case.pool.attend(_pu().dev(Q2), **gpu_kw)[:, near] == out[:, near]).all())
+
+
+@pytest.mark.parametrize("codec", [dict(), dict(value_bits=2), dict(key_per_tensor=True)])
+@pytest.mark.parametrize("d,heads,agents,q,block_rows,own", [
+    (64, 2, 5, 1, 32, 0), (64, 256, 12, 1, 64, 0), (128, 256, 12, 1, 64, 0), (256, 256, 5, 1, 32, 0), (64, 40, 33, 4, 64, 1)])
+def test_other_agents_references_do_not_show(d, heads, agents, q, block_rows, own, codec):
+    """Some agents' rows outgrow their reference in every tile, and the wave forms the tile's probabilities and sums anew; the
+    others' rows come out bit for bit as they do beside rows that never move theirs."""
+    rng = np.random.default_rng(d + agents)
+    T, group = 32 * (9 if own else 25) + 7, 4
+    K = rng.standard_normal((1, heads, T, d))
+    K[..., 0] = 0.05 * np.arange(T)
+    Q = 3.0 * rng.standard_normal((1, agents, q, heads * group, d))     # sums of large and small terms, whose order shows
+    Q[..., 0] = 0.17 * d ** 0.5
+    far = np.zeros(agents, bool)
+    far[1::3] = True
+    Q[:, far, ..., 0] = 20.0 * d ** 0.5         # by 46 in 32 tokens
+    half = lambda x: _pu().dev(x.astype(np.float16))
+    pool = _pu().gpu_pool(K.astype(np.float16), rng.standard_normal(K.shape).astype(np.float16), **codec)
+    choice = pool.attend_plan(half(Q), splits=1 if own == 0 else 0)
+    assert (choice.block_rows, choice.own_rows) == (block_rows, own)
+    out = pool.attend(half(Q), splits=1 if own == 0 else 0)
+    Q[:, far] = 0.0
+    near = np.flatnonzero(~far)
+    assert bool((pool.attend(half(Q), splits=1 if own == 0 else 0)[:, near] == out[:, near]).all())
