@@ -8,9 +8,8 @@
 //   pipeline two tiles are in flight per wave: the scores of the next tile are computed on the matrix
 //            cores while the vector ALUs run the softmax and value dequantization of the current one.
 //   scores   S^T[t, r] = sum_j s[t,j] * (sum_{k in block j} code[t,k] * q[r,k]): the keys enter the matrix cores as
-//            their codes as stored, exact in fp16, and the q8_0 block scales are applied in fp32 to the products of a
-//            block (two K=16 MFMAs) as they are summed, on top of one product that holds the codes' offset and the
-//            rows' softmax references (Corr).
+//            their integer codes, exact in fp16, and the q8_0 block scales are applied in fp32 to the products of a
+//            block (two K=16 MFMAs) as they are summed.
 //   softmax  online, per row, in base-2 units; a row's reference only moves when the row's probabilities
 //            of one tile sum to more than 2^15 in a lane, so the accumulator rescale is rare, p fits
 //            fp16, and the common case takes no maximum over the scores at all.
@@ -31,11 +30,12 @@
 // What the forms of the scores took, us a call (15 agents x 4,096 tokens at R = 60; 64 agents x 4 queries x 7,194 tokens):
 //   the exact dequantized key, 18 bits, as two fp16 terms and two products     61.4    1,624
 //   codes less their offset (2 packed subtractions per 4 codes), fold          55      1,470 (1,165 in die order, 1,097 with own rows)
-//   codes as stored and the correction (Corr), one box                         53.4 -> 52.4    1,088 -> 1,067 (1,040 to 1,065
-//                                                                              with the rows' sums by products with ones)
-// The last also took SmolLM2-shaped calls of 5 rows from 28.8 to 27.7 us (24.3 instead of 27.2 out of the cache; half of that
-// by keeping accumulators and queries in vector registers, see parks), tails over 7,194 tokens from 113.9 to 112.0, 32 one-layer
-// calls from 442 to 435.  A step's vector instructions: 400 -> 340 (two row tiles, head_dim 128), 298 -> 139 (one, 64).
+// Codes as stored, offset by 128 (fp16 subnormals, no subtraction), with 128 times the queries' sums taken away by a product of
+// their own per score tile, ran 1,024 rows in 1,069 instead of 1,089 us, calls of 5 rows in 27.3 instead of 27.7 and 15 agents in
+// the same time, but the fp32 sums lose up to log2(128 / |code|) bits, most where a block has one massive channel and small codes
+// otherwise: with queries near 1,000 errors of 4.4e-4 to 1.8e-3, where the rounding of the probabilities makes 0.3e-4 or less.
+// With accumulators and queries in vector registers where waves share a SIMD (see parks) and the codes' products folded in
+// place, one statement an element, calls of 5 rows take 27.7 instead of 28.7 us and int8 values 42.2 instead of 42.7.
 //
 // The accumulation stays in the rotated value domain; the inverse Walsh-Hadamard rotation is done
 // once per output row (sections "Compression Scheme" / "TurboQuant", dequantization), in this kernel
@@ -86,7 +86,6 @@ template <bool WAIT, bool BA> __device__ __forceinline__ void mfma32_v(float16v&
     else if constexpr (BA) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
     else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
-
 // The lane's number, read again where it is needed: across the main loop it would hold a register.
 __device__ __forceinline__ int lane_again() {
     int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -136,26 +135,6 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
 //   otherwise (one scale per layer tensor, whose scale rides on the softmax scale; keys rounded to fp16): one product
 //     over all blocks.
 __host__ __device__ constexpr bool fold_scales(int KC, bool K16) { return KC == 0 && !K16; }
-// FOLD: the codes enter the products as they are stored, offset by 128, as fp16 subnormals: byte b becomes b * 2^-24, one
-// byte permute per two codes and nothing else (the matrix cores take subnormals at full precision).  What that and the
-// rows' softmax references ask for,
-//   C[t, r] = sum_j s[t, j] * W[r, j] + mu[r],   W[r, j] = -128 * qscale * sum of q[r] over block j,   mu = -reference,
-// is a product of its own per score tile, with the scales as they are (fp16) against W and mu in three fp16 terms each
-// (33 bits): it is what the block products are added to, in the place of 16 moves of mu, and the subtraction from every
-// key code (32 packed instructions per tile) is gone.  What is added and taken away again is at most 128 times the sum of a
-// block's query magnitudes, 2^-24 of it the error: errors against float64 are the same as without (1.577 and 1.576e-4 at 15
-// agents, 1.303 and 1.302e-4 at 512 rows over 300 tokens).  K slots of a row: term * NB + j, then the three terms of mu.
-// A W or mu beyond kCorrMax has zeros there and is added by hand (add_wide).
-template <int D> struct Corr {
-    static constexpr int NB = D / 32;
-    static constexpr int ops = NB == 8 ? 2 : 1;                       // products (K = 16 each)
-    static constexpr int mu_slot = NB == 2 ? 8 : NB == 4 ? 12 : 24;   // (in lanes 32..63, a whole dword pair)
-    static constexpr int mu_op = mu_slot / 16, mu_word = mu_slot % 8 / 2;
-    static constexpr int row_halves = 16 * ops;
-    static constexpr int words = NB / 2;                              // dwords of scales per token
-};
-constexpr float kCorrMax = 60000.0f, kCodeScale = 16777216.0f;        // 2^24
-
 // The records of a KV head as a lane reads them; `tile` is a record's byte offset.
 template <int D, int VC, int KC, bool K16> struct TileReader {
     using LY = Layout<D, VC, KC>;
@@ -166,7 +145,7 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
     TileRsrc rs;
     // the lane's offsets: key codes, key scales, value codes, value scales (opaque, so that the compiler adds what is
     // constant in the instruction instead of keeping a register per load)
-    uint32_t k, s, ts, v, g;
+    uint32_t k, s, v, g;
 
     __device__ __forceinline__ TileReader(TileRsrc r, int lane) : rs(r) {
         k = (uint32_t)lane * 16;
@@ -174,12 +153,10 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
         // whose key codes the lane holds
         const int t = fold_scales(KC, K16) ? 8 * ((lane >> 2) & 3) + 4 * (lane >> 5) + (lane & 3) : lane & 31;
         s = (uint32_t)t * (D / 32) * 2;
-        ts = (uint32_t)(lane & 31) * (D / 32) * 2;
         v = (uint32_t)lane * (VB == 8 ? 16 : VB == 3 ? 12 : VB == 4 ? D / 4 : D / 8);
         g = (uint32_t)(lane >> 5) * 8;
         asm volatile("" : "+v"(k), "+v"(v));
         if (KC == 0) asm volatile("" : "+v"(s));
-        if (fold_scales(KC, K16)) asm volatile("" : "+v"(ts));
         if (vc_has_scale(VC)) asm volatile("" : "+v"(g));
     }
     // key codes of token lane % 32, block j: elements 8h..8h+7 (x, y) and 16+8h.. (z, w), h = lane / 32
@@ -197,18 +174,6 @@ template <int D, int VC, int KC, bool K16> struct TileReader {
                 const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::kscales_off + s + 4 * x, tile, 0);
                 sc[x] = two[0], sc[x + 1] = two[1];
             }
-        }
-    }
-    // (FOLD) all key scales of token lane % 32, two per dword
-    __device__ __forceinline__ void token_scales(uint32_t tile, uint32_t (&sc)[D / 64]) const {
-        if constexpr (D == 64) {
-            sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, LY::kscales_off + ts, tile, 0);
-        } else if constexpr (D == 128) {
-            const auto two = __builtin_amdgcn_raw_buffer_load_b64(rs, LY::kscales_off + ts, tile, 0);
-            sc[0] = two[0], sc[1] = two[1];
-        } else {
-            const uint4v four = __builtin_amdgcn_raw_buffer_load_b128(rs, LY::kscales_off + ts, tile, 0);
-            sc[0] = four.x, sc[1] = four.y, sc[2] = four.z, sc[3] = four.w;
         }
     }
     // value codes of coordinate groups 4q .. 4q + 3
@@ -245,19 +210,10 @@ __device__ __forceinline__ _Float16 half_of(uint32_t w, int odd) {   // the lowe
     return __builtin_bit_cast(_Float16, (uint16_t)(odd ? w >> 16 : w));
 }
 
-// Half block s of a lane's 16 key codes -> the A operand of one score product: the codes as fp16 subnormals (FOLD), as exact
-// fp16 integers or, for keys rounded to fp16 (K16), code * scale; sc2: the dword that holds the block's scale, odd: in its
-// upper half.
-template <bool FOLD, bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& raw, int s, uint32_t sc2, int odd) {
+// Half block s of a lane's 16 key codes -> the A operand of one score product: the codes as exact fp16 integers or, for
+// keys rounded to fp16 (K16), code * scale; sc2: the dword that holds the block's scale, odd: in its upper half.
+template <bool K16> __device__ __forceinline__ half8 key_operand(const uint4v& raw, int s, uint32_t sc2, int odd) {
     H8 a;
-    if constexpr (FOLD) {
-        const uint32_t lo = s == 0 ? raw.x : raw.z, hi = s == 0 ? raw.y : raw.w;
-        a.u[0] = __builtin_amdgcn_perm(0u, lo, 0x0c010c00u);
-        a.u[1] = __builtin_amdgcn_perm(0u, lo, 0x0c030c02u);
-        a.u[2] = __builtin_amdgcn_perm(0u, hi, 0x0c010c00u);
-        a.u[3] = __builtin_amdgcn_perm(0u, hi, 0x0c030c02u);
-        return a.h;
-    }
     codes4_to_half(s == 0 ? raw.x : raw.z, a.u[0], a.u[1]);
     codes4_to_half(s == 0 ? raw.y : raw.w, a.u[2], a.u[3]);
     a.h = a.h - (_Float16)1152.0f;
@@ -271,7 +227,7 @@ template <int I> __device__ __forceinline__ float fold1(float s, float product, 
     asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(s) : "v"(scale), "v"(product), "n"(I));
     return s;
 }
-template <typename PV> __device__ __forceinline__ void fold16(float16v& S, const PV& P, float scale) {
+__device__ __forceinline__ void fold16(float16v& S, const float16v& P, float scale) {
     static_for<16>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         S[i] = fold1<i>(S[i], P[i], scale);
@@ -404,12 +360,11 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
     half8 kop[2];                                  // tile B: key operands of block 0, both halves,
     uint4v k[D / 32];                              //   key codes (block 0: of the tile after B),
     uint32_t sc[TR::NS];                           //   key scales
-    uint32_t tsc[fold_scales(KC, K16) ? D / 64 : 1];   //   and the same in the order of the correction's operand
     uint32_t v[TR::NQ][TR::CW];                    // tile A: value codes
     uint32_t g[vc_has_scale(VC) ? 8 : 1];          //   and value scales
     __device__ __forceinline__ void first_operands() {
-        kop[0] = key_operand<fold_scales(KC, K16), K16>(k[0], 0, sc[0], 0);
-        kop[1] = key_operand<fold_scales(KC, K16), K16>(k[0], 1, sc[0], 0);
+        kop[0] = key_operand<K16>(k[0], 0, sc[0], 0);
+        kop[1] = key_operand<K16>(k[0], 1, sc[0], 0);
     }
 };
 
@@ -427,45 +382,11 @@ constexpr int kernel_waves_per_simd(int D, int NT, int VC, bool OWN) {
 // a step between them.
 constexpr bool parks(int waves_per_simd) { return waves_per_simd == 1; }
 
-// The correction's query operands (FOLD) and where the rows' W beyond kCorrMax are; else empty.
-template <int D, int NT> struct CorrState {
-    half8 b[NT][Corr<D>::ops];
-    uint64_t wide;          // the lanes of rows with a W or a reference beyond kCorrMax: add_wide has to be called if there are any
-    const float* w_s;       // the wave's rows' W where beyond kCorrMax, else 0: [row][block]
-    // the reference of the lane's row in row tile nt
-    __device__ __forceinline__ void set_reference(int nt, float m, bool upper) {
-        float mu = -m;
-        const bool beyond = !(fabsf(mu) <= kCorrMax);
-        wide |= __ballot(beyond);
-        if (beyond) mu = 0.0f;
-        union {
-            _Float16 h[4];
-            uint32_t u[2];
-        } t;
-        t.h[0] = (_Float16)mu;
-        mu -= (float)t.h[0];
-        t.h[1] = (_Float16)mu;
-        mu -= (float)t.h[1];
-        t.h[2] = (_Float16)mu;
-        t.h[3] = (_Float16)0.0f;
-        H8 x;
-        x.h = b[nt][Corr<D>::mu_op];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) x.u[Corr<D>::mu_word + i] = upper ? t.u[i] : x.u[Corr<D>::mu_word + i];
-        b[nt][Corr<D>::mu_op] = x.h;
-    }
-};
-struct OneValue {   // (in the place of a tile of products)
-    float v;
-    __device__ __forceinline__ float operator[](int) const { return v; }
-};
-
 template <int D, int NT, int VC, int KC, bool K16, int WPS, bool HAS_A, bool HAS_B, bool LOOP, bool LAST, bool REBASE>
 __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur, const TileReader<D, VC, KC, K16>& tr,
                                               uint32_t nextV, uint32_t nextK, uint32_t nextK0, int masked, int down, float qscale,
-                                              bool upper, const half8 (&qb)[NT][D / 32][2], CorrState<D, NT>& corr,
-                                              float16v (&O)[D / 32][NT], float (&Lsum)[NT], float* m_ref, float (&mneg)[NT],
-                                              const LoopConsts& lc) {
+                                              bool upper, const half8 (&qb)[NT][D / 32][2], float16v (&O)[D / 32][NT],
+                                              float (&Lsum)[NT], float* m_ref, float (&mneg)[NT], const LoopConsts& lc) {
     using TR = TileReader<D, VC, KC, K16>;
     constexpr int NB = D / 32, NG = D / 16, MG = D / 32;
     constexpr bool FOLD = fold_scales(KC, K16), VS = vc_has_scale(VC), PARK = parks(WPS);
@@ -488,7 +409,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     };
     uint32_t sc_next[TR::NS], g_next[VS ? 8 : 1];   // scales of the tiles a step later
     auto kdeq = [&](int k, half8& dst) {   // half block k's operand; after a block's second half its codes are reloaded
-        dst = key_operand<FOLD, K16>(cur.k[k >> 1], k & 1, cur.sc[k >> 2], (k >> 1) & 1);
+        dst = key_operand<K16>(cur.k[k >> 1], k & 1, cur.sc[k >> 2], (k >> 1) & 1);
     };
     auto scales_next = [&]() {
         tr.kscales(nextK, sc_next);
@@ -502,9 +423,8 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     auto move_reference = [&](int nt, float m_old, float m_new, bool both) {
         const float alpha = m_new == m_old ? 1.0f : __builtin_amdgcn_exp2f(m_old - m_new);
         m_ref[32 * nt + (lane_again() & 31)] = m_new;
-        if constexpr (!FOLD) mneg[nt] = -m_new;
+        mneg[nt] = -m_new;
         if constexpr (FOLD) {   // the exponents of the tiles in flight move along
-            corr.set_reference(nt, m_new, upper);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 Sa[nt][i] -= m_new - m_old;
@@ -543,9 +463,6 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         }
     }
 
-    using CR = Corr<D>;
-    H8 acorr[CR::ops];   // the correction's scale operands
-
     // block j's products with row tile nt (FOLD): two of them take turns, one is folded while the other is formed
     // (with two waves a SIMD one: a unit is folded before the next is formed)
     constexpr int NP = FOLD && WPS != 2 ? 2 : 1;
@@ -553,24 +470,8 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
     constexpr int NU = NB * NT;
     // (A DPP source must not have been written by the two instructions before: a block's scale is formed a unit ahead.)
     float fscale[2];
-    auto fold_scale = [&](int j) { fscale[j & 1] = (float)half_of(cur.sc[j >> 1], j & 1) * (qscale * kCodeScale); };
+    auto fold_scale = [&](int j) { fscale[j & 1] = (float)half_of(cur.sc[j >> 1], j & 1) * qscale; };
     auto fold = [&](int u) { fold16(Sb[u % NT], P[u % NP], fscale[u / NT & 1]); };
-    auto add_wide = [&]() {   // (rare) of the rows that have them, what is too large for the correction's operands
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int n = lane_again() & 31, r = 32 * nt + n;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const float scale = (float)half_of(cur.sc[j >> 1], j & 1);
-                asm volatile("s_nop 1" : : "v"(scale));
-                fold16(Sb[nt], OneValue{corr.w_s[r * NB + j]}, scale);
-            }
-            const float m = m_ref[r], mu = fabsf(m) <= kCorrMax || m == -INFINITY ? 0.0f : -m;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Sb[nt][i] += mu;
-        }
-    };
-
     if (HAS_B) {
         if constexpr (FOLD) {
             // Unit u: block u / NT with row tile u % NT, two products.  The operand of a half block is formed as soon as
@@ -580,8 +481,8 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 constexpr int j = u / NT, nt = u % NT;
                 const bool last_nt = nt == NT - 1 && j + 1 < NB;
                 // The unit's chunks of probabilities, in order, so that a tile's sum is the same where it is formed anew (the rows
-                // that move their reference).  The first units have one each with their tiles' corrections; NP == 1: the others
-                // behind the second product, which is folded after them.
+                // that move their reference).  The first units have one each in front; NP == 1: the others behind the second
+                // product, which is folded after them.
                 constexpr bool behind = NP == 1 && u + 1 < NU;
                 auto chunks_before = [](int x) {
                     const int first = x < NT ? x : NT, even = x * NCH / NU;
@@ -589,23 +490,12 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
                 };
                 constexpr int c0 = chunks_before(u), c1 = chunks_before(u + 1);
                 fence();
-                if (j == 0) {   // what the block products are added to
-                    float16v& C = Sb[nt];
-                    if (nt == 0) {
-                        // A: the token's scales in every slot of W, ones in those of mu
+                // What the block products are added to.  (In front: 15 agents 53.6 us; behind the first product 54.5.  As a product
+                // of the references with constants, one fp32 matrix instruction for 16 moves, 1,024 rows 1,108 instead of 1,097.)
+                if (j == 0) {
 #pragma unroll
-                        for (int op = 0; op < CR::ops; ++op)
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) {
-                                const uint32_t w = cur.tsc[x % CR::words];
-                                acorr[op].u[x] = op == CR::mu_op && x >= CR::mu_word && x < CR::mu_word + 2 && upper ? 0x3c003c00u : w;
-                            }
-                        fence();
-                    }
-                    mfma32_v0<true, false>(C, acorr[0].h, corr.b[nt][0]);
-                    if constexpr (CR::ops == 2) mfma32_v<true, false>(C, acorr[CR::ops - 1].h, corr.b[nt][CR::ops - 1]);
+                    for (int i = 0; i < 16; ++i) Sb[nt][i] = mneg[nt];
                     fence();
-                    if (nt == NT - 1) tr.token_scales(nextK, cur.tsc);
                     if (HAS_A) exp_chunk(c0);
                     fence();
                 }
@@ -674,7 +564,6 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
             });
             if (!HAS_A) asm volatile("s_nop 15");
         }
-        if (FOLD && !HAS_A && __builtin_expect(corr.wide != 0, 0)) add_wide();   // (else with the rows that move their reference)
     } else if (HAS_A) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) exp_chunk(c);
@@ -691,8 +580,7 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) raise |= !(lt[nt] * gmax <= lc.raise_sum);   // (inf and NaN say yes)
         const bool set_here = REBASE && !EARLY && down != kNoRebase;
-        if (__builtin_expect((__ballot(raise) | (FOLD && HAS_B ? corr.wide : 0)) != 0 || set_here, 0)) {
-            if (FOLD && HAS_B && corr.wide != 0) add_wide();
+        if (__builtin_expect(__any(raise) || set_here, 0)) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const bool row_raise = !(xor32_max(lt[nt] * gmax) <= lc.raise_sum);   // (+inf stays +inf through the max)
@@ -822,7 +710,6 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
         for (int j = 0; j < NB; ++j) cur.k[j] = tr.kcodes(t0, j);
         tr.kscales(t0, cur.sc);
-        if constexpr (FOLD) tr.token_scales(t0, cur.tsc);
     }
 
     // ---- query rows as MFMA B operands: lane (n, h) holds q[row 32nt+n][32j + 16s + 8h .. +7].
@@ -869,7 +756,6 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             }
         }
         *reinterpret_cast<uint4v*>(q_s + rr * QS + 8 * piece) = raw;
-        qraw[u] = raw;
     }
     __syncthreads();
     half8 qb[NT][NB][2];
@@ -891,70 +777,6 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
             for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int s = 0; s < 2; ++s) asm volatile("" : "+a"(qb[nt][j][s]));
-    }
-
-    // FOLD: the rows' W (Corr).  A row's sum over a block is a product of the queries with ones, which leaves it in all registers of
-    // the row's lanes: 16 matrix instructions for 64 rows, and every lane has what it needs for its own operands.  (Summed by the
-    // threads that fetch the queries, and handed over through LDS, it made 512 rows over 100 tokens, with rows of their own for the
-    // waves, 46.1 instead of 44.0 us.)
-    __shared__ float w_s[FOLD ? WG_ROWS * NB : 1];   // (waves that share rows write the same numbers)
-    CorrState<D, NT> corr;
-    corr.wide = 0;
-    float* const w_mine = w_s + (OWN ? wave * ROWS * NB : 0);
-    corr.w_s = w_mine;
-    if constexpr (FOLD) {
-        using CR = Corr<D>;
-        H8 ones;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ones.u[i] = 0x3c003c00u;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            float16v sum[NB];   // (the blocks' products in turn: a block's second waits for its first)
-            static_for<NB>([&](auto jc) {
-                constexpr int j = decltype(jc)::value;
-                mfma32_v0<j == 0, PARK>(sum[j], ones.h, qb[nt][j][0]);
-            });
-            static_for<NB>([&](auto jc) {
-                constexpr int j = decltype(jc)::value;
-                mfma32_v<false, PARK>(sum[j], ones.h, qb[nt][j][1]);
-            });
-            asm volatile("s_nop 11");
-            __builtin_amdgcn_sched_barrier(0);
-            float beyond[NB];
-            bool any = false;
-            _Float16 term[3][NB];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                float w = sum[j][0] * (-128.0f * p.qscale);
-                const bool far = !(fabsf(w) <= kCorrMax);
-                beyond[j] = far ? w : 0.0f;
-                w = far ? 0.0f : w;
-                any |= far;
-#pragma unroll
-                for (int x = 0; x < 3; ++x) {
-                    term[x][j] = (_Float16)w;
-                    w -= (float)term[x][j];
-                }
-            }
-            auto word = [&](int d) -> uint32_t {   // slots 2 d and 2 d + 1; zero beyond the terms (no reference yet)
-                if (2 * d >= 3 * NB) return 0u;
-                return __builtin_bit_cast(uint32_t, half2v{term[2 * d / NB][2 * d % NB], term[2 * d / NB][2 * d % NB + 1]});
-            };
-#pragma unroll
-            for (int op = 0; op < CR::ops; ++op) {
-                H8 x;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x.u[i] = h ? word(8 * op + 4 + i) : word(8 * op + i);
-                corr.b[nt][op] = x.h;
-            }
-            corr.wide |= __ballot(any);
-            if (h == 0) {   // (for every row: a reference beyond the range reads them too)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) w_mine[(32 * nt + n) * NB + j] = beyond[j];
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (a wave's LDS accesses complete in order)
-        __builtin_amdgcn_wave_barrier();
     }
 
     // The references themselves are only read where a row moves its reference and at the merge: they live in the
@@ -980,16 +802,15 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
 #pragma unroll
         for (int q = 0; q < TileReader<D, VC, KC, K16>::NQ; ++q) tr.vcodes(tile_off(0), q, cur.v[q]);
         pipeline_step<D, NT, VC, KC, K16, WPS, false, true, false, true, false>(cur, tr, tile_off(0), tile_off(1), tile_off(2), rest(0), kNoRebase,
-                                                                   qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
+                                                                   qscale, h == 1, qb, O, Lsum, m_ref, mneg, lc);
         // the rows' first references: the maxima of this first tile, taken here once instead of letting the first
         // step find out through infinite probabilities and compute its tile's probabilities twice
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const float m0 = xor32_max(max16(cur.S[nt])) * (FOLD ? 1.0f : qscale);
             m_ref[32 * nt + n] = m0;
-            if constexpr (!FOLD) mneg[nt] = -m0;
+            mneg[nt] = -m0;
             if constexpr (FOLD) {
-                corr.set_reference(nt, m0, h == 1);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) cur.S[nt][i] -= m0;
             }
@@ -1001,7 +822,7 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         const int pairs_end = min(my_count - 3, setting - 1);
         auto main_step = [&]() {
             pipeline_step<D, NT, VC, KC, K16, WPS, true, true, true, false, false>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
-                                                                              kTile, kNoRebase, qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
+                                                                              kTile, kNoRebase, qscale, h == 1, qb, O, Lsum, m_ref, mneg, lc);
             ++k;
         };
         while (k < pairs_end) {   // two steps a trip: the two tiles' scores swap registers without copies
@@ -1011,9 +832,9 @@ __device__ __forceinline__ void attend_mfma_block(const uint8_t* __restrict__ po
         for (; k + 1 < my_count; ++k)   // tile B may be the pool's last
             pipeline_step<D, NT, VC, KC, K16, WPS, true, true, true, true, true>(cur, tr, tile_off(k + 1), tile_off(k + 2), tile_off(k + 3),
                                                                             rest(k + 1), k > 0 && k >= setting ? kRebaseDown : kNoRebase,
-                                                                            qscale, h == 1, qb, corr, O, Lsum, m_ref, mneg, lc);
+                                                                            qscale, h == 1, qb, O, Lsum, m_ref, mneg, lc);
         const int down = k > 0 && k >= setting ? kRebaseDown : ragged ? 0 : kNoRebase;
-        pipeline_step<D, NT, VC, KC, K16, WPS, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, h == 1, qb, corr, O, Lsum,
+        pipeline_step<D, NT, VC, KC, K16, WPS, true, false, false, false, true>(cur, tr, 0, 0, 0, kTile, down, qscale, h == 1, qb, O, Lsum,
                                                                            m_ref, mneg, lc);
     }
 

@@ -69,3 +69,42 @@ def test_a_last_tile_that_is_not_full_sets_references_too(d, group):
         Q = _queries(pool, 15, 1, group, g)
         errors.append(_rms_error(pool, Q, pool.attend(Q, splits=1)))
     assert errors[1] <= 1.08 * errors[0], errors
+
+
+@pytest.mark.parametrize("d,heads,agents,q,block_rows,own", [
+    (64, 2, 5, 1, 32, 0), (128, 2, 5, 1, 32, 0), (256, 2, 5, 1, 32, 0), (64, 256, 12, 1, 64, 0), (128, 256, 12, 1, 64, 0),
+    (64, 40, 33, 4, 64, 1), (128, 40, 33, 4, 64, 1), (256, 40, 33, 4, 32, 1)])
+def test_a_massive_channel_in_every_key_block(d, heads, agents, q, block_rows, own):
+    """Key codes of 127 in one channel of every block, 1 or 2 in half of the others and -1 or -2 in the rest, which add up to zero;
+    queries near 1,000 there, with a standard deviation of 8.  Codes and queries are whole numbers and every product over a
+    block is far below 2^24, so that a kernel that forms them from the codes has exact ones and scores off by a few 2^-24 of
+    their size; what is left of the error is the fp16 rounding of the probabilities, each off by 2^-11 of itself at most and
+    independently of the others."""
+    pk, T, group = _pk(), 300, 4
+    g = torch.Generator(device="cuda").manual_seed(d + heads)
+    n = (1, heads, T, d // 32)
+    order = torch.rand(n + (31,), device="cuda", generator=g).argsort(-1)       # 15 up, 15 down and one zero, shuffled
+    size = torch.randint(1, 3, n + (1,), device="cuda", generator=g)
+    codes = torch.cat([torch.full(n + (1,), 127, device="cuda"), size * torch.sign(15 - order)], -1).reshape(1, heads, T, d)
+    K = (2.0 * codes).half()
+    V = torch.randn((1, heads, T, d), device="cuda", generator=g).half()
+    pool = pk.Pool(1, heads, d, T).bind()
+    pool.encode(K, V)
+    Kd, Vd = pool.decode(torch.float32)
+    assert bool((Kd == K.float()).all())
+    Q = torch.round(1000.0 + 8.0 * torch.randn((1, agents, q, heads * group, d), device="cuda", generator=g))
+    Q[..., ::32] = torch.randint(-3, 4, Q[..., ::32].shape, device="cuda", generator=g).float()
+    Q = Q.half()
+    choice = pool.attend_plan(Q, splits=0)
+    assert (choice.block_rows, choice.own_rows) == (block_rows, own)
+    scale = d ** -0.5 / 16.0                # (scores of a few units)
+    out, err, bound = pool.attend(Q, scale=scale), 0.0, 0.0
+    for h in range(heads):
+        rows = lambda t: t[0][:, :, h * group:(h + 1) * group].double().reshape(-1, d)  # noqa: E731, B023
+        v = Vd[0, h].double()
+        p = torch.softmax(rows(Q) @ Kd[0, h].double().t().contiguous() * scale, -1)
+        want = p @ v
+        err += float(((rows(out) - want) ** 2).sum())
+        bound += 2.0 ** -22 * float(((p ** 2) @ v ** 2 - 2 * (p ** 2 @ v) * want + (p ** 2).sum(-1, keepdim=True) * want ** 2).sum())
+    err, bound = (err / out.numel()) ** 0.5, (bound / out.numel()) ** 0.5
+    assert err <= bound + 2e-6, (err, bound)      # (2e-6: fp32 sums of the values, probabilities below fp16's normal numbers)

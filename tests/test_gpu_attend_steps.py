@@ -146,8 +146,8 @@ def test_splits_that_are_merged(d, codec):
         case.attend_check(Q, splits=splits)
 
 
-# Queries whose sum over a key block, and references, beyond what the correction's fp16 operands hold (60,000): such a row takes
-# a way of its own, its neighbours in the wave do not.
+# Queries with large sums over the key blocks, and references beyond what fp16 holds (60,000), in some of a wave's rows: their
+# neighbours do not notice.
 @pytest.mark.parametrize("d,heads,agents,q,own", [(64, 2, 5, 1, 0), (64, 2, 12, 1, 0), (128, 2, 5, 1, 0), (128, 2, 12, 1, 0),
                                                   (256, 2, 5, 1, 0), (64, 40, 33, 4, 1), (128, 40, 33, 4, 1), (256, 40, 33, 4, 1)])
 @pytest.mark.parametrize("what", ["sums", "references"])
@@ -208,7 +208,7 @@ def test_large_references_alone(d, heads, agents, q, block_rows, own, tails):
         gpu_kw = dict(tails=[(_pu().dev(k), _pu().dev(v), n) for (k, v), n in zip(pairs, lens)], splits=2)
     choice = case.pool.attend_plan(_pu().dev(Q), **gpu_kw)
     assert (choice.block_rows, choice.own_rows, choice.tails_in_pool_launch) == (block_rows, own, int(tails))
-    case.pool.attend(_pu().dev(Q + np.float16(300.0)), **gpu_kw)    # sums beyond the range leave other numbers in the LDS
+    case.pool.attend(_pu().dev(Q + np.float16(300.0)), **gpu_kw)    # (leaves other numbers in the LDS)
     case.attend_check(Q, **kw)
     out = case.pool.attend(_pu().dev(Q), **gpu_kw)
     # the other agents' rows do not notice
