@@ -338,7 +338,7 @@ class Pool:
         # one cached workspace per stream: calls on different streams may overlap and must not share one
         ws = workspace if workspace is not None else self._workspaces.get(sp)
         if ws is None:
-            ws = self._grow_workspace(p, sp)
+            ws = self._grow_workspace(p, sp, stream)
         p.workspace_dev = _dev_ptr(ws, torch.uint8, "workspace")
         p.workspace_bytes = ws.numel()
         if out is None:
@@ -346,17 +346,20 @@ class Pool:
         args = (self._h, _dev_ptr(Q, Q.dtype, "Q"), _dev_ptr(out, torch.float32, "out"), C.byref(p), sp)
         rc = lib.pool_attend(*args)
         if rc == ENOMEM and workspace is None:   # (nothing was launched) the cached one is too small: the size is asked for only then
-            ws = self._grow_workspace(p, sp)
+            ws = self._grow_workspace(p, sp, stream)
             p.workspace_dev, p.workspace_bytes = ws.data_ptr(), ws.numel()
             rc = lib.pool_attend(*args)
         _check(rc)
         return out
 
-    def _grow_workspace(self, p, sp):
+    def _grow_workspace(self, p, sp, stream):
         need = lib.pool_attend_workspace(self._h, C.byref(p))
         if need == 0:
             _check(lib.pool_attend(self._h, None, None, C.byref(p), None))  # surfaces the shape error
-        ws = self._workspaces[sp] = torch.empty(max(need, 256), dtype=torch.uint8, device=self.device)
+        # From the memory of the stream that uses it: the one it replaces may still be in use there, and goes to later work of
+        # that stream only.
+        with torch.cuda.stream(stream):
+            ws = self._workspaces[sp] = torch.empty(max(need, 256), dtype=torch.uint8, device=self.device)
         return ws
 
     # pool_attend_static(Q[agents], out): no workspace, nothing allocated by the library
