@@ -24,15 +24,22 @@ def _queries(pool, agents, q, group, g):
     return torch.randn((pool.layers, agents, q, pool.kv_heads * group, pool.head_dim), device="cuda", generator=g).half()
 
 
-def _rms_error(pool, Q, out):
+def _rms_error(pool, Q, out, bound=False):
+    """bound: also no more than probabilities that are each off by 2^-11 of themselves, independently, and a denominator that
+    is theirs or the unrounded ones', make of it."""
     K, V = pool.decode(torch.float32)
     L, A, q, qh, d = Q.shape
-    G, num = qh // pool.kv_heads, 0.0
+    G, num, most = qh // pool.kv_heads, 0.0, 0.0
     for l in range(L):
         for h in range(pool.kv_heads):
             rows = lambda t: t[l][:, :, h * G:(h + 1) * G].double().reshape(-1, d)  # noqa: E731, B023
-            want = torch.softmax(rows(Q) @ K[l, h].double().t().contiguous() / d ** 0.5, -1) @ V[l, h].double()
+            p, v = torch.softmax(rows(Q) @ K[l, h].double().t().contiguous() / d ** 0.5, -1), V[l, h].double()
+            want = p @ v
             num += float(((rows(out) - want) ** 2).sum())
+            if bound:
+                p = p ** 2
+                most += 2.0 ** -22 * float((p @ v ** 2 + 2 * (p @ v.abs()) * want.abs() + p.sum(-1, keepdim=True) * want ** 2).sum())
+    assert not bound or num <= most, ((num / out.numel()) ** 0.5, (most / out.numel()) ** 0.5)
     return (num / out.numel()) ** 0.5
 
 
@@ -52,7 +59,7 @@ def test_the_plan_does_not_show_in_the_error(layers, heads, d, T, agents, q, gro
     choice = pool.attend_plan(Q)
     assert choice.own_rows == own and choice.splits == 1 and choice.references > 1
     assert pool.attend_plan(Q, splits=splits).splits == splits and pool.attend_plan(Q, splits=splits).own_rows == 0
-    automatic, cut_up = (_rms_error(pool, Q, pool.attend(Q, splits=n)) for n in (0, splits))
+    automatic, cut_up = (_rms_error(pool, Q, pool.attend(Q, splits=n), bound=True) for n in (0, splits))
     assert automatic <= 1.05 * cut_up, (automatic, cut_up)
 
 

@@ -148,10 +148,11 @@ def test_splits_that_are_merged(d, codec):
 
 # Queries with large sums over the key blocks, and references beyond what fp16 holds (60,000), in some of a wave's rows: their
 # neighbours do not notice.
-@pytest.mark.parametrize("d,heads,agents,q,own", [(64, 2, 5, 1, 0), (64, 2, 12, 1, 0), (128, 2, 5, 1, 0), (128, 2, 12, 1, 0),
-                                                  (256, 2, 5, 1, 0), (64, 40, 33, 4, 1), (128, 40, 33, 4, 1), (256, 40, 33, 4, 1)])
+@pytest.mark.parametrize("d,heads,agents,q,block_rows,own", [
+    (64, 2, 5, 1, 32, 0), (64, 2, 12, 1, 32, 0), (64, 256, 12, 1, 64, 0), (128, 2, 5, 1, 32, 0), (128, 2, 12, 1, 32, 0),
+    (128, 256, 12, 1, 64, 0), (256, 2, 5, 1, 32, 0), (64, 40, 33, 4, 64, 1), (128, 40, 33, 4, 64, 1), (256, 40, 33, 4, 32, 1)])
 @pytest.mark.parametrize("what", ["sums", "references"])
-def test_rows_beyond_the_corrections_range(d, heads, agents, q, own, what):
+def test_rows_beyond_the_corrections_range(d, heads, agents, q, block_rows, own, what):
     rng = np.random.default_rng(d + agents)
     T, group = 32 * 9 + 5, 4
     cfg = W.PoolConfig(0, "range", 1, heads, heads * group, d, T, agents, q)
@@ -167,7 +168,8 @@ def test_rows_beyond_the_corrections_range(d, heads, agents, q, own, what):
         Q[:, far] = 200.0 * np.abs(Q[:, far]) + 500.0
     case = Case(cfg, K.astype(np.float16), V)
     Q = Q.astype(np.float16)
-    assert case.pool.attend_plan(_pu().dev(Q)).own_rows == own
+    choice = case.pool.attend_plan(_pu().dev(Q))
+    assert (choice.block_rows, choice.own_rows) == (block_rows, own)
     case.attend_check(Q)
     out = case.pool.attend(_pu().dev(Q))
     # the other agents' rows do not notice
@@ -241,3 +243,44 @@ def test_other_agents_references_do_not_show(d, heads, agents, q, block_rows, ow
     Q[:, far] = 0.0
     near = np.flatnonzero(~far)
     assert bool((pool.attend(half(Q), splits=1 if own == 0 else 0)[:, near] == out[:, near]).all())
+
+
+# The 64-row form with shared rows at head_dim 64, of which two workgroups share a CU: it takes 256 workgroups and more.
+def _two_a_cu(T, growing, **codec):
+    rng = np.random.default_rng(T)
+    K = rng.standard_normal((1, 256, T, 64))
+    if growing:
+        K *= np.linspace(0.2, 9.0, T)[None, None, :, None]
+    V = rng.standard_normal((1, 256, T, 64))
+    case = Case(W.PoolConfig(0, "two", 1, 256, 1024, 64, T, 10, 1), K.astype(np.float16), V.astype(np.float16), **codec)
+    return case, rng.standard_normal((1, 10, 1, 1024, 64)).astype(np.float16)
+
+
+def _plan_of(case, Q, **kw):
+    choice = case.pool.attend_plan(_pu().dev(Q), **kw)
+    return choice.block_rows, choice.own_rows, choice.splits
+
+
+@pytest.mark.parametrize("tiles", [1, 4, 5, 8, 13, 16, 20, 25, 28])
+def test_tiles_per_wave_with_two_workgroups_a_cu(tiles):
+    case, Q = _two_a_cu(32 * tiles - {0: 0, 1: 31, 2: 1}[tiles % 3], growing=tiles % 2 == 0)
+    assert _plan_of(case, Q) == (64, 0, 1)
+    case.attend_check(Q)
+
+
+@pytest.mark.parametrize("codec", [dict(), dict(value_bits=2), dict(key_per_tensor=True), dict(value_bits=2, key_per_tensor=True)])
+def test_codecs_with_two_workgroups_a_cu(codec):
+    case, Q = _two_a_cu(32 * 17 + 5, growing=True, **codec)
+    for splits in (1, 2):
+        assert _plan_of(case, Q, splits=splits) == (64, 0, splits)
+        case.attend_check(Q, splits=splits)
+    case.attend_check(Q[:, :9], splits=1)      # 36 rows
+
+
+def test_fp16_keys_with_two_workgroups_a_cu():
+    pk, pu = _pk(), _pu()
+    case, Q = _two_a_cu(32 * 17 + 5, growing=True)
+    kw = dict(key_precision=pk.KEY_PRECISION_FP16)
+    assert _plan_of(case, Q, **kw) == (64, 0, 1)
+    Kh, Vh = case.decoded()
+    pu.compare_attend(case.pool.attend(pu.dev(Q), **kw), O.pool_attend(O.keys_as_fp16(Kh), Vh, Q), 256)
