@@ -207,8 +207,10 @@ static int make_plan(const polykv_pool* pool, const polykv_attend_params* prm, A
             const uint32_t tiles = (uint32_t)cap_tiles, ways = (uint32_t)waves;
             auto per_wave = [&](uint32_t n) { return ((tiles + n - 1) / n + ways - 1) / ways; };
             // The merge kernel: about 4 us, and partials written and read at about 4 TB/s; a step is about 1.2 us.  (Of the 64-row
-            // form, one workgroup to a CU.  At head_dim 64 with up to 32 rows three share a CU and a step is shorter: rounds
-            // are overcounted there and the merge undercounted, which errs towards few splits.)
+            // form at head_dim 128, one workgroup to a CU.  At head_dim 64 three share a CU with up to 32 rows, two with 64, and a
+            // step is shorter: rounds are overcounted there and the merge undercounted, which errs towards few splits, and
+            // towards rows of their own: 8 layers x 32 heads x 600 tokens, 160 rows, 22.9 us with them and 17.8 with shared
+            // rows of one reference a wave.  24 x 32 x 1,851: 192 rows 99.6 shared, 256 rows 129.6 with rows of their own, 133.4 shared.)
             const double merge = 3.5, partials = rows * p.D * (8 / 4e12 / 1.2e-6);
             long best = 1;
             double least = (double)((groups + 255) / 256) * (per_wave(1) + 5);

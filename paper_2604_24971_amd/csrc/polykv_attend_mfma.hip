@@ -21,12 +21,12 @@
 // Why 32x32x16: a wave that interleaves MFMAs with vector work pays 5 to 8 issue cycles per MFMA whatever its shape and
 // 4 to 5 per vector instruction, so the larger tile halves the MFMA share of the issue time for the same arithmetic.
 //
-// What bounds it: with 64 rows a workgroup, the power that random operands take.  15 agents over 4,096 tokens are 84,000
-// cycles a wave (70,000 of them the loop), 45.8 us at 1.9 GHz where the pool comes out of the last-level cache, 52 us at 1.6
-// to 1.75 GHz where it comes from memory, whatever the loop's number of cycles: deeper requests (two sets of tile data, every
-// piece asked for two steps ahead) and a loop rearranged to 7 % fewer cycles both changed nothing or lost 1 to 2 %.  Leaving
-// out 8 of the 32 matrix instructions of a step is worth 10 % of the time of 1,024 rows, the fold's 128 vector instructions
-// 12 %.  With 32 rows, HBM (5.8 to 6.9 TB/s in the loop) and the fixed parts around it, 8 to 12 us of a call.
+// What bounds it: with 64 rows a workgroup, the issue of vector instructions by a lone wave per SIMD, at a clock that follows
+// the operands.  15 agents over 4,096 tokens are 93,800 cycles a wave (14,770 vector and 1,024 matrix instructions; the matrix
+// pipe is busy for 32,800, 17,600 are waits).  By its time that is a clock of 2.08 GHz behind the codec kernels of the bench
+// step (45.1 us), 1.92 back to back (48.9 us), 2.29 over zeros (41.0 us).  Fewer cycles alone do not shorten it: deeper requests
+// (two sets of tile data, every piece asked for two steps ahead) and a loop rearranged to 7 % fewer cycles changed nothing or
+// lost 1 to 2 %.  With 32 rows, HBM and the fixed parts around the loop, 8 to 12 us of a call.
 // What the forms of the scores took, us a call (15 agents x 4,096 tokens at R = 60; 64 agents x 4 queries x 7,194 tokens):
 //   the exact dequantized key, 18 bits, as two fp16 terms and two products     61.4    1,624
 //   codes less their offset (2 packed subtractions per 4 codes), fold          55      1,470 (1,165 in die order, 1,097 with own rows)
@@ -371,8 +371,9 @@ template <int D, int NT, int VC, int KC, bool K16> struct StepState {
 // Waves per SIMD the kernel is compiled for: one where it needs all 512 registers; three for 32-row blocks at
 // head_dim 64 (the small-row shape of the SmolLM2-sized pool: 768 workgroups, all resident at once on 256 CUs,
 // so that one workgroup's query fetch, pipeline ramp and merge overlap the others' main loops); two for 64-row blocks there
-// (24 layers x 32 heads x 1,851 tokens: 40 rows 54.6 us with one, 42.3 with two, 100 rows 97.8 and 72.4).  Value scales, 4-bit
-// values and waves with rows of their own take up to five registers more than that leaves.
+// (24 layers x 32 heads x 1,851 tokens: 40 rows 54.0 us with one, 43.0 with two, 100 rows 97.6 and 74.7).  Value scales take 268
+// to 308 of the 256 registers that leaves.  4-bit values and waves with rows of their own come out at 256 or less by themselves,
+// compiled for one; two workgroups then share a CU as well (256 rows, rows of their own: 168 -> 141 us).
 constexpr int kernel_waves_per_simd(int D, int NT, int VC, bool OWN) {
     if (D != 64 || vc_has_scale(VC) || OWN) return 1;
     return NT == 2 ? (vc_bits(VC) == 4 ? 1 : 2) : vc_bits(VC) == 3 ? 3 : 1;
@@ -450,8 +451,8 @@ __device__ __forceinline__ void pipeline_step(StepState<D, NT, VC, KC, K16>& cur
         }
     };
     // A tile that sets references does so before anything is taken relative to them, so that nothing is done twice (1,024 rows
-    // over 7,194 tokens 1,094 instead of 1,158 us, 512 over 300 tokens 57 instead of 59).  Without FOLD and with a tile B the registers do not hold it here, and it is
-    // done with the rows that outgrew their references, further down.
+    // over 7,194 tokens 1,094 instead of 1,158 us, 512 over 300 tokens 57 instead of 59).  Without FOLD and with a tile B the
+    // registers do not hold it here, and it is done with the rows that outgrew their references, further down.
     constexpr bool EARLY = REBASE && (FOLD || !HAS_B);
     if constexpr (EARLY) {
         if (__builtin_expect(down != kNoRebase, 0)) {   // (out of the way of the steps without)
@@ -1045,7 +1046,7 @@ static long tail_waves(const AttendPlan& plan) {
 }
 
 // Tails in the pool's launch: where the merge kernel runs anyway, with 32-row workgroups at head_dim 64 and 128 (of
-// which two fit a CU; the others have a CU to themselves and the tails would follow them), and no more of them than
+// which two fit a CU; a call of 64-row workgroups fills the CUs with them, and the tails would follow), and no more of them than
 // all CUs hold beside one pool workgroup each.
 bool matrix_kernel_takes_tails(const AttendPlan& plan) {
     return plan.has_tails && plan.kernel == POLYKV_KERNEL_MATRIX && !matrix_kernel_direct(plan) && plan.D != 256 &&
